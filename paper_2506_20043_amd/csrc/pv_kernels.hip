@@ -3,7 +3,7 @@
 //  * grid maps ("Kernel 1" of the paper: one map per ligand atom type over
 //    each pocket box, Methods "Accelerated Docking" and Supplementary
 //    Algorithm 2, first step): FP32 VALU, lattice tiles of 16x4x4 points per
-//    workgroup, receptor atoms culled per tile into LDS;
+//    workgroup and 4x4x4 per wave, receptor atoms culled for both;
 //  * pose evaluation (Eq. qvina_eq_1 forward kinematics, Eq. qvina_eq_3
 //    score): one wave64 per pose, lanes over fragments for the frame tree,
 //    over atoms for the trilinear gathers and over intra pairs, LDS force
@@ -1910,130 +1910,247 @@ __global__ __launch_bounds__(64) void output_kernel(OutputArgs a)
 }
 
 // ---------------------------------------------------------------- grid maps
-// One workgroup per 16x4x4 tile of one box (a wave writes 16-float = 64 B
-// rows).  A term enters the sum when r < 8 A, decided in binary32 where that
-// is unambiguous and in binary64 near the cutoff.  Receptor atoms near the box are
-// streamed in chunks of 256; those within reach of the tile's bounding box
-// are compacted into LDS in the atoms' order (a ballot per wave, the waves'
-// counts in wave order), so every point sums its terms in the same order on
-// every build and the maps are reproducible bit for bit; every lane adds the
-// candidates' terms to its point's 8 accumulators (one per ligand type).
-constexpr int kGridThreads = kTileX * kTileY * kTileZ;  // 256
+// One workgroup of four waves per 16x4x4 tile of one box, a wave per 4x4x4
+// points: a cube of 1.1 A edges at the usual spacing, so that the points of a
+// wave lie at nearly one distance of a receptor atom.
+// The receptor atoms near the box are streamed in chunks of 256; those within
+// reach of the tile are appended in the atoms' order (a ballot per wave, the
+// waves' counts in wave order) to a list in LDS.  Each wave then tests the
+// list 64 atoms at a time against its own cube and walks the bits of the
+// ballot.  Every point so sums its terms in the atoms' order on every build
+// and the maps are reproducible bit for bit.
+//
+// Bound by VALU issue (the VALU is busy throughout; 68 instructions per wave
+// and atom, 110 atoms per wave where 79 reach an average point).  A term of a
+// far atom needs one exponential per ligand radius (the second gaussian
+// alone), a near one two and the linear terms, so a wave branches on whether
+// any of its points is near.  16 pockets of 20-30 A (4.5e6 points, 8,000
+// atoms): 1,900 us with waves of 16x4x1 points that computed every term of
+// every atom, 955 us now; 32 boxes of 15-30 A (7.4e6 points): 3,190 -> 1,690.
+// Tiles of 8x4x4 take 17% longer, 16x8x4 2%, 16x8x8 54%; 8x8x8 2% less on
+// many boxes and 5% more on one.
+constexpr int kGridThreads = kTileX * kTileY * kTileZ;
+constexpr int kGridList = 2 * kGridThreads;             // LDS list entries
+constexpr int kGridRun = 4;                             // consecutive tiles one XCD takes (see below)
 
 // The 8 A cutoff of a map term as r < 8 on binary64 values: the lattice
 // point origin + h i, the differences, squares and sum each rounded on its
-// own (no contraction), then the correctly rounded square root.  Used for
-// the few (point, atom) pairs whose binary32 squared distance lies within
+// own (no contraction).  s < 64 decides as the correctly rounded sqrt(s) < 8
+// does: the largest binary64 s below 64 has a root that rounds below 8.  Used
+// for the few (point, atom) pairs whose binary32 squared distance lies within
 // 0.01 A^2 of 64, where binary32 rounding could decide the other way.
-__device__ __noinline__ bool within_cutoff_f64(int i, int j, int k, float ox, float oy, float oz, float h, float4 at)
+__device__ __forceinline__ bool within_cutoff_f64(int i, int j, int k, float ox, float oy, float oz, float h,
+                                                  float ax, float ay, float az)
 {
 #pragma clang fp contract(off)
     const double gx = (double)ox + (double)h * (double)i;
     const double gy = (double)oy + (double)h * (double)j;
     const double gz = (double)oz + (double)h * (double)k;
-    const double dx = gx - (double)at.x, dy = gy - (double)at.y, dz = gz - (double)at.z;
+    const double dx = gx - (double)ax, dy = gy - (double)ay, dz = gz - (double)az;
     const double s = dx * dx + dy * dy + dz * dz;
-    return __builtin_sqrt(s) < 8.0;
+    return s < 64.0;
 }
 
-__global__ __launch_bounds__(256) void gridmap_kernel(GridBuildArgs a)
+// The 8 maps' sums at one point, by ligand type (named registers: an array
+// here is copied whole where the branches below meet).
+struct MapSums {
+    float ch, cp, np, nd, na, oa, oda, sp;
+};
+
+// Adds one receptor atom's terms at distance r of this lane's point.  rt (the
+// atom's XS type) is wave-uniform; rs: its radius plus the ligand radii C, N,
+// O and S.
+// From d = 2.25 A on (kGridFar) a term is its second gaussian alone, bit for
+// bit: the first one's share, 0.0356 exp(-4 d^2), is below a quarter of a unit
+// in the last place of 0.00516 exp(-(d-3)^2/4) there (4 d^2 - (d-3)^2/4 > 19.3),
+// and the other terms are zero.
+constexpr float kGridFar = 2.25f;
+
+__device__ __forceinline__ void add_map_terms(float r, int rt, float4 rs, MapSums& m)
 {
-    __shared__ float4 cand[kGridThreads];
-    __shared__ int wave_n[kGridThreads / kWave];
-    const int wv = threadIdx.x / kWave;
-    // which box and which tile of it
-    const int tile = blockIdx.x;
-    int box = 0;
-    while (box + 1 < a.n_boxes && a.tile_off[box + 1] <= tile) ++box;
+#pragma clang fp contract(off)
+    constexpr float kE = 1.4426950408889634f;   // log2 e
+    const float dc = r - rs.x, dn = r - rs.y, dx = r - rs.z, ds = r - rs.w;
+    auto gauss2 = [](float d) {
+#pragma clang fp contract(off)
+        const float t = d - 3.f;
+        return kW2 * __builtin_amdgcn_exp2f(t * t * (-0.25f * kE));
+    };
+    float bc = gauss2(dc), bn = gauss2(dn), bo = gauss2(dx), bs = gauss2(ds);
+    if (__ballot(ds < kGridFar) == 0) {   // the S radius has the smallest d
+        m.ch += bc;
+        m.cp += bc;
+        m.np += bn;
+        m.nd += bn;
+        m.na += bn;
+        m.oa += bo;
+        m.oda += bo;
+        m.sp += bs;
+        // an opaque use of the sums: without it the compiler merges these
+        // additions with the near path's and moves every register there
+        asm volatile("" : "+v"(m.ch), "+v"(m.cp), "+v"(m.np), "+v"(m.nd), "+v"(m.na), "+v"(m.oa), "+v"(m.oda), "+v"(m.sp));
+        return;
+    }
+    auto gauss1 = [](float d, float b) {
+#pragma clang fp contract(off)
+        return __builtin_fmaf(__builtin_amdgcn_exp2f(d * d * (-4.f * kE)), kW1, b);
+    };
+    bc = gauss1(dc, bc); bn = gauss1(dn, bn); bo = gauss1(dx, bo); bs = gauss1(ds, bs);
+    if (__ballot(ds < 0.f)) {
+        auto repel = [](float d, float b) {
+#pragma clang fp contract(off)
+            const float v = __builtin_fmaf(kW3 * d, d, b);
+            return d < 0.f ? v : b;
+        };
+        bc = repel(dc, bc); bn = repel(dn, bn); bo = repel(dx, bo); bs = repel(ds, bs);
+    }
+    float vch = bc, vnd = bn, vna = bn, voa = bo, voda = bo;
+    if (rt == 0 && __ballot(dc < 1.5f)) {   // both hydrophobic
+        const float v = kW4 * (1.5f - dc);
+        const float w = dc < 1.5f ? v : 0.f;
+        vch += dc < 0.5f ? kW4 : w;
+    }
+    const bool don = rt == 3 || rt == 6, acc = rt == 4 || rt == 5 || rt == 6;
+    if ((don || acc) && __ballot(dn < 0.f)) {   // hydrogen bonds; the N radius has the smaller d
+        auto hbond = [](float d) {
+#pragma clang fp contract(off)
+            const float v = kW5 * (d * -(1.f / 0.7f));
+            const float w = d < 0.f ? v : 0.f;
+            return d < -0.7f ? kW5 : w;
+        };
+        const float hn = bn + hbond(dn), ho = bo + hbond(dx);
+        vnd = acc ? hn : bn;
+        vna = don ? hn : bn;
+        voa = don ? ho : bo;
+        voda = ho;
+    }
+    m.ch += vch;
+    m.cp += bc;
+    m.np += bn;
+    m.nd += vnd;
+    m.na += vna;
+    m.oa += voa;
+    m.oda += voda;
+    m.sp += bs;
+}
+
+// squared distance from an atom to the box [lo, hi]
+__device__ __forceinline__ float box_dist2(const float4& at, const float lo[3], const float hi[3])
+{
+    const float dx = fmaxf(fmaxf(lo[0] - at.x, at.x - hi[0]), 0.f);
+    const float dy = fmaxf(fmaxf(lo[1] - at.y, at.y - hi[1]), 0.f);
+    const float dz = fmaxf(fmaxf(lo[2] - at.z, at.z - hi[2]), 0.f);
+    return dx * dx + dy * dy + dz * dz;
+}
+
+__global__ __launch_bounds__(kGridThreads) void gridmap_kernel(GridBuildArgs a)
+{
+    constexpr int kWaves = kGridThreads / kWave;
+    __shared__ float4 list[kGridList], rsum[kGridList];   // atom records; their radii plus each ligand radius
+    __shared__ int wave_n[2][kWaves];
+    const int l = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // Workgroups go round robin to the 8 XCDs: each XCD takes runs of kGridRun
+    // consecutive tiles, so that tiles that share map lines write them through
+    // one L2.
+    const int q = blockIdx.x >> 3;
+    const int tile = (q / kGridRun) * (8 * kGridRun) + (blockIdx.x & 7) * kGridRun + q % kGridRun;
+    if (tile >= a.tile_off[a.n_boxes]) return;
+    // which box: the boxes whose first tile is at or before this one
+    int box = -1;
+    for (int b0 = 0; b0 < a.n_boxes; b0 += kWave)
+        box += __popcll(__ballot(b0 + l < a.n_boxes && a.tile_off[b0 + l] <= tile));
     const int nx = a.dims[4 * box], ny = a.dims[4 * box + 1], nz = a.dims[4 * box + 2];
     const float ox = a.geom[8 * box], oy = a.geom[8 * box + 1], oz = a.geom[8 * box + 2], h = a.geom[8 * box + 3];
     const int tx = (nx + kTileX - 1) / kTileX, ty = (ny + kTileY - 1) / kTileY;
     const int t = tile - a.tile_off[box];
-    const int bx = t % tx, by = (t / tx) % ty, bz = t / (tx * ty);
-    const int li = threadIdx.x % kTileX, lj = (threadIdx.x / kTileX) % kTileY, lk = threadIdx.x / (kTileX * kTileY);
-    const int i = bx * kTileX + li, j = by * kTileY + lj, k = bz * kTileZ + lk;
-    const bool valid = i < nx && j < ny && k < nz;
-    // the lattice point exactly as the cutoff test defines it
+    const int x0 = t % tx * kTileX, y0 = (t / tx) % ty * kTileY, z0 = t / (tx * ty) * kTileZ;
+    // this lane's point; points past the lattice repeat its last one and are not stored
+    constexpr int kWx = kTileX / 4, kWy = kTileY / 4;
+    const int cx = 4 * (wv % kWx), cy = 4 * (wv / kWx % kWy), cz = 4 * (wv / (kWx * kWy));   // the wave's cube in the tile
+    const int wx = x0 + cx, wy = y0 + cy, wz = z0 + cz;
+    const bool idle = wx >= nx || wy >= ny || wz >= nz;
+    const int i = min(wx + (l & 3), nx - 1), j = min(wy + ((l >> 2) & 3), ny - 1), k = min(wz + (l >> 4), nz - 1);
     const float gx = fmaf((float)i, h, ox), gy = fmaf((float)j, h, oy), gz = fmaf((float)k, h, oz);
-    // tile bounding box (points that exist)
-    const float lox = fmaf((float)(bx * kTileX), h, ox), loy = fmaf((float)(by * kTileY), h, oy),
-                loz = fmaf((float)(bz * kTileZ), h, oz);
-    const float hix = fmaf((float)min(bx * kTileX + kTileX - 1, nx - 1), h, ox);
-    const float hiy = fmaf((float)min(by * kTileY + kTileY - 1, ny - 1), h, oy);
-    const float hiz = fmaf((float)min(bz * kTileZ + kTileZ - 1, nz - 1), h, oz);
+    // bounding boxes of the tile's and of the wave's points
+    const float tlo[3] = {fmaf((float)x0, h, ox), fmaf((float)y0, h, oy), fmaf((float)z0, h, oz)};
+    const float thi[3] = {fmaf((float)(min(x0 + kTileX, nx) - 1), h, ox), fmaf((float)(min(y0 + kTileY, ny) - 1), h, oy),
+                          fmaf((float)(min(z0 + kTileZ, nz) - 1), h, oz)};
+    const float wlo[3] = {fmaf((float)wx, h, ox), fmaf((float)wy, h, oy), fmaf((float)wz, h, oz)};
+    const float whi[3] = {fmaf((float)(min(wx + 4, nx) - 1), h, ox), fmaf((float)(min(wy + 4, ny) - 1), h, oy),
+                          fmaf((float)(min(wz + 4, nz) - 1), h, oz)};
     const float reach2 = 8.01f * 8.01f;
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    MapSums acc = {0, 0, 0, 0, 0, 0, 0, 0};
     const int abeg = a.atom_off[box], aend = a.atom_off[box + 1];
-    // element radii C N O S and the receptor-type table
-    const float Rel[4] = {1.9f, 1.8f, 1.7f, 2.0f};
+    int n = 0, flip = 0;
+    float4 next = abeg + (int)threadIdx.x < aend ? a.atoms[abeg + threadIdx.x] : make_float4(0.f, 0.f, 0.f, 0.f);
     for (int base = abeg; base < aend; base += kGridThreads) {
-        const int ai = base + threadIdx.x;
-        bool keep = false;
-        float4 at = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ai < aend) {
-            at = a.atoms[ai];
-            const float ddx = fmaxf(fmaxf(lox - at.x, at.x - hix), 0.f);
-            const float ddy = fmaxf(fmaxf(loy - at.y, at.y - hiy), 0.f);
-            const float ddz = fmaxf(fmaxf(loz - at.z, at.z - hiz), 0.f);
-            keep = ddx * ddx + ddy * ddy + ddz * ddz < reach2;
-        }
-        // the barrier that ends each chunk has let every reader of the last
-        // chunk's wave_n and cand pass, so both may be rewritten here
+        const float4 at = next;
+        const int an = base + kGridThreads + (int)threadIdx.x;
+        if (an < aend) next = a.atoms[an];
+        const bool keep = base + (int)threadIdx.x < aend && box_dist2(at, tlo, thi) < reach2;
         const uint64_t m = __ballot(keep);
-        if ((threadIdx.x & (kWave - 1)) == 0) wave_n[wv] = __popcll(m);
+        if (l == 0) wave_n[flip][wv] = __popcll(m);
         __syncthreads();
-        int off = 0, nc = 0;
+        int off = n;
 #pragma unroll
-        for (int q = 0; q < kGridThreads / kWave; ++q) {
-            const int c = wave_n[q];
-            off += q < wv ? c : 0;
-            nc += c;
+        for (int w = 0; w < kWaves; ++w) {
+            const int c = wave_n[flip][w];
+            off += w < wv ? c : 0;
+            n += c;
         }
-        if (keep)
-            cand[off + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = at;
-        __syncthreads();
-        for (int c = 0; c < nc; ++c) {
-            const float4 at = cand[c];
-            const float dx = gx - at.x, dy = gy - at.y, dz = gz - at.z;
-            const float dz2 = dz * dz;
-            const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz2));
-            if (!(r2 < kCut2 + 0.01f)) continue;
-            if (r2 > kCut2 - 0.01f && !within_cutoff_f64(i, j, k, ox, oy, oz, h, at)) continue;
-            const float r = __builtin_amdgcn_sqrtf(r2);
-            const int rt = __float_as_uint(at.w) & 0xff;
+        // the next chunk writes the other counts, so those readers may lag
+        flip ^= 1;
+        if (keep) {
+            off += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            const int rt = __float_as_int(at.w) & 0xff;
             const float Rr = rt <= 1 ? 1.9f : rt <= 4 ? 1.8f : rt <= 6 ? 1.7f : 2.0f;
-            const bool r_hyd = rt == 0, r_don = rt == 3 || rt == 6, r_acc = rt == 4 || rt == 5 || rt == 6;
-            float base_e[4], hbv[4];
-            float hyd_c = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float d = r - (Rel[e] + Rr);
-                const float g1 = __expf(-4.f * d * d);
-                const float dm3 = d - 3.f;
-                const float g2 = __expf(-0.25f * dm3 * dm3);
-                float v = kW1 * g1 + kW2 * g2;
-                if (d < 0.f) v += kW3 * d * d;
-                base_e[e] = v;
-                hbv[e] = d < -0.7f ? 1.f : (d < 0.f ? -d * (1.f / 0.7f) : 0.f);
-                if (e == 0) hyd_c = d < 0.5f ? 1.f : (d < 1.5f ? 1.5f - d : 0.f);
-            }
-            acc[0] += base_e[0] + (r_hyd ? kW4 * hyd_c : 0.f);           // C_H
-            acc[1] += base_e[0];                                         // C_P
-            acc[2] += base_e[1];                                         // N_P
-            acc[3] += base_e[1] + (r_acc ? kW5 * hbv[1] : 0.f);          // N_D
-            acc[4] += base_e[1] + (r_don ? kW5 * hbv[1] : 0.f);          // N_A
-            acc[5] += base_e[2] + (r_don ? kW5 * hbv[2] : 0.f);          // O_A
-            acc[6] += base_e[2] + ((r_don || r_acc) ? kW5 * hbv[2] : 0.f); // O_DA
-            acc[7] += base_e[3];                                         // S_P
+            list[off] = at;
+            rsum[off] = make_float4(1.9f + Rr, 1.8f + Rr, 1.7f + Rr, 2.0f + Rr);
         }
+        if (n + kGridThreads <= kGridList && base + kGridThreads < aend) continue;   // room for one more chunk
+        __syncthreads();
+        for (int c0 = 0; c0 < n && !idle; c0 += kWave) {
+            uint64_t near = __ballot(c0 + l < n && box_dist2(list[min(c0 + l, n - 1)], wlo, whi) < reach2);
+            if (!near) continue;
+            // the next atom's record is read while this one is worked on
+            int q = c0 + __builtin_ctzll(near);
+            float4 nc = list[q], ns = rsum[q];
+            while (near) {
+                const float4 c = nc, rs = ns;
+                near &= near - 1;
+                q = near ? c0 + __builtin_ctzll(near) : c0;
+                nc = list[q];
+                ns = rsum[q];
+                const float dx = gx - c.x, dy = gy - c.y, dz = gz - c.z;
+                const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                bool in = r2 < kCut2 - 0.01f;
+                // from kCut2 - 0.01 to below kCut2 + 0.01, as one unsigned range (r2 >= 0)
+                const uint32_t lo = __float_as_uint(kCut2 - 0.01f), hi = __float_as_uint(kCut2 + 0.01f);
+                if (__float_as_uint(r2) - lo < hi - lo)
+                    in = r2 <= kCut2 - 0.01f || within_cutoff_f64(i, j, k, ox, oy, oz, h, c.x, c.y, c.z);
+                const int rt = __builtin_amdgcn_readfirstlane(__float_as_int(c.w)) & 0xff;
+                if (in) add_map_terms(__builtin_amdgcn_sqrtf(r2), rt, rs, acc);
+            }
+        }
+        n = 0;
         __syncthreads();
     }
-    if (valid) {
-        const int64_t msz = (int64_t)nx * ny * nz;
-        const int64_t idx = ((int64_t)k * ny + j) * nx + i;
-        float* out = a.maps + a.map_off[box];
+    // through LDS, so that the stores go out in rows of 16 points
+    float* stage = (float*)list;
+    static_assert(sizeof(list) >= 8 * kGridThreads * sizeof(float), "the list area holds the tile's maps");
+    const float sums[8] = {acc.ch, acc.cp, acc.np, acc.nd, acc.na, acc.oa, acc.oda, acc.sp};
 #pragma unroll
-        for (int tt = 0; tt < 8; ++tt) out[tt * msz + idx] = acc[tt];
+    for (int m = 0; m < 8; ++m)
+        stage[m * kGridThreads + ((cz + (l >> 4)) * kTileY + cy + ((l >> 2) & 3)) * kTileX + cx + (l & 3)] = sums[m];
+    __syncthreads();
+    const int si = x0 + (int)threadIdx.x % kTileX, sj = y0 + ((int)threadIdx.x / kTileX) % kTileY,
+              sk = z0 + (int)threadIdx.x / (kTileX * kTileY);
+    if (si < nx && sj < ny && sk < nz) {
+        const int64_t msz = (int64_t)nx * ny * nz;
+        float* out = a.maps + a.map_off[box] + ((int64_t)sk * ny + sj) * nx + si;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) out[m * msz] = stage[m * kGridThreads + threadIdx.x];
     }
 }
 
@@ -2241,7 +2358,9 @@ hipError_t launch_class_map(const int2* jobs, int32_t n_jobs, const DevLig* ligs
 hipError_t launch_build_grids(const GridBuildArgs& a, int64_t n_tiles, hipStream_t s)
 {
     if (n_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gridmap_kernel, dim3((unsigned)n_tiles), dim3(kGridThreads), 0, s, a);
+    const int64_t runs = 8 * kGridRun;   // whole runs for every XCD; workgroups past the last tile return
+    const int64_t grid = (n_tiles + runs - 1) / runs * runs;
+    hipLaunchKernelGGL(gridmap_kernel, dim3((unsigned)grid), dim3(kGridThreads), 0, s, a);
     return hipGetLastError();
 }
 

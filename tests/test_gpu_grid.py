@@ -206,3 +206,22 @@ def test_box_size_sweep_sampled(oracle, pv_ctx):
         for i, j, k in pts:
             ref = oracle.map_point(rx, rt, dims, org, box.spacing, i, j, k)
             _assert_maps_close(maps[b][:, k, j, i], ref, "box %d point %s" % (b, (i, j, k)))
+
+
+@pytest.mark.parametrize("dims, n_rec, cube", [
+    ((2, 2, 2), 1, 4.0),         # the smallest lattice and receptor
+    ((16, 4, 4), 256, 14.0),     # one whole tile, one whole chunk of atoms
+    ((17, 5, 9), 257, 14.0),     # one point and one atom past them
+    ((33, 3, 8), 600, 16.0),     # a chunk more than one tile's atom list keeps
+    ((19, 21, 6), 1500, 12.0),   # every atom reaches every tile: the list is emptied several times
+])
+def test_tile_and_list_edges(oracle, pv_ctx, dims, n_rec, cube):
+    """Every map value where tiles, wave cubes, atom chunks and the atom list end, from atoms at most
+    touching to many on one spot (all terms: near, far and at the cutoff)."""
+    g = np.random.default_rng(n_rec)
+    rx, rt = S.receptor(g, n_rec, cube)
+    box = S.Box(np.full(3, cube / 2, np.float32), np.float32([(n - 1.5) * 0.375 for n in dims]))
+    grids, maps = _gpu_maps(pv_ctx, rx, rt, [box])
+    d, org = grids.info(0)
+    assert tuple(d) == dims
+    _assert_maps_close(maps[0], oracle.build_maps(rx, rt, d, org, box.spacing), str(dims))
