@@ -1368,45 +1368,43 @@ pv_status pv_sas_build(pv_ctx* ctx, int32_t n_rec, const float* rec_xyz, const u
     h->ctx = ctx;
     h->n_rec = n_rec;
     hipStream_t s = (hipStream_t)stream;
-    const int bs = sas_block_size();
-    const int64_t n_blocks = (n_cand + bs - 1) / bs;
-    float* ddirs = nullptr;
-    float4* cand = nullptr;
-    uint8_t* keep = nullptr;
-    int32_t* bcount = nullptr;
-    int32_t* boff = nullptr;
-    auto cleanup = [&]() { dfree(ddirs); dfree(cand); dfree(keep); dfree(bcount); dfree(boff); };
+    // how far a candidate can lie from its atom, in units of the radius, and
+    // how far rounding can move a coordinate
+    double umax = 0.0, cmax = 0.0;
+    for (int32_t k = 0; k < n_dirs; ++k)
+        umax = std::max(umax, std::sqrt((double)dirs[3 * k] * dirs[3 * k] + (double)dirs[3 * k + 1] * dirs[3 * k + 1] +
+                                        (double)dirs[3 * k + 2] * dirs[3 * k + 2]));
+    for (int32_t k = 0; k < 3 * n_rec; ++k) cmax = std::max(cmax, (double)std::fabs(rec_xyz[k]));
+    const float um = (float)(umax * 1.00001), slack = (float)(0.01 + 1e-6 * (cmax + (2.0 + probe) * umax));
+    // one temporary block: the directions, the masks, the counts
+    const size_t words = (size_t)n_rec * ((n_dirs + 63) / 64);
+    const size_t off_count = (words + 1) * 8, off_dirs = off_count + 4 * ((size_t)n_rec + 2);
+    char* tmp = nullptr;
     if ((st = upload(&h->atoms, ha.data(), ha.size(), "receptor")) != PV_OK ||
-        (st = upload(&ddirs, dirs, (size_t)3 * n_dirs, "directions")) != PV_OK ||
-        (st = upload(&cand, (const float4*)nullptr, (size_t)std::max<int64_t>(n_cand, 1), "candidates")) != PV_OK ||
-        (st = upload(&keep, (const uint8_t*)nullptr, (size_t)std::max<int64_t>(n_cand, 1), "candidates")) != PV_OK ||
-        (st = upload(&bcount, (const int32_t*)nullptr, (size_t)std::max<int64_t>(n_blocks, 1), "counts")) != PV_OK) {
-        cleanup();
+        (st = upload(&tmp, (const char*)nullptr, off_dirs + 12 * (size_t)n_dirs, "surface workspace")) != PV_OK) {
         pv_sas_free(h);
         return st;
     }
-    hipError_t e = launch_sas_candidates(h->atoms, n_rec, ddirs, n_dirs, probe, n_cand, cand, keep, bcount, s);
-    std::vector<int32_t> hc((size_t)std::max<int64_t>(n_blocks, 1), 0);
-    if (e == hipSuccess && n_blocks > 0)
-        e = hipMemcpyAsync(hc.data(), bcount, sizeof(int32_t) * n_blocks, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) { cleanup(); pv_sas_free(h); return hip_fail(e, "surface candidates"); }
-    int64_t total = 0;
-    for (int64_t b = 0; b < n_blocks; ++b) {
-        const int32_t c = hc[b];
-        hc[b] = (int32_t)total;
-        total += c;
-    }
-    h->n_points = (int32_t)total;
-    if ((st = upload(&boff, hc.data(), hc.size(), "offsets")) != PV_OK ||
-        (st = upload(&h->pts, (const float4*)nullptr, (size_t)std::max<int64_t>(total, 1), "points")) != PV_OK) {
-        cleanup();
+    uint64_t* keep = (uint64_t*)tmp;
+    int32_t* count = (int32_t*)(tmp + off_count);
+    float* ddirs = (float*)(tmp + off_dirs);
+    int32_t total = 0;
+    hipError_t e = hipMemcpyAsync(ddirs, dirs, 12 * (size_t)n_dirs, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = launch_sas_keep(h->atoms, n_rec, ddirs, n_dirs, probe, um, slack, keep, count, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&total, count + n_rec, sizeof(total), hipMemcpyDeviceToHost, s);
+    // also where a call failed: the caller's arrays and `total` are free again
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    if (e != hipSuccess) { dfree(tmp); pv_sas_free(h); return hip_fail(e, "surface candidates"); }
+    h->n_points = total;
+    if ((st = upload(&h->pts, (const float4*)nullptr, (size_t)total, "points")) != PV_OK) {
+        dfree(tmp);
         pv_sas_free(h);
         return st;
     }
-    e = launch_sas_scatter(cand, keep, boff, n_cand, h->pts, s);
+    e = launch_sas_scatter(h->atoms, n_rec, ddirs, n_dirs, probe, keep, count, h->pts, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    cleanup();
+    dfree(tmp);
     if (e != hipSuccess) { pv_sas_free(h); return hip_fail(e, "surface points"); }
     *out = h;
     return PV_OK;
@@ -1426,11 +1424,7 @@ pv_status pv_sas_copy(const pv_sas* h, float* xyz, int32_t* atom, void* stream)
     pv_status st = set_device(h->ctx);
     if (st != PV_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    if (xyz)
-        HIP_TRY(hipMemcpy2DAsync(xyz, 12, h->pts, 16, 12, h->n_points, hipMemcpyDeviceToDevice, s), "copy points");
-    if (atom)
-        HIP_TRY(hipMemcpy2DAsync(atom, 4, (const char*)h->pts + 12, 16, 4, h->n_points, hipMemcpyDeviceToDevice, s),
-                "copy atoms");
+    HIP_TRY(launch_sas_split(h->pts, h->n_points, xyz, atom, s), "copy points");
     return PV_OK;
 }
 

@@ -221,13 +221,16 @@ hipError_t launch_job_reduce(const float* chain_best_e, const int64_t* chain_eva
                              int64_t* job_evals, int32_t* job_status, hipStream_t s);
 hipError_t launch_local_opt(const OptArgs& a, int n_cu, hipStream_t s);
 hipError_t launch_output(const OutputArgs& a, hipStream_t s);
-hipError_t launch_sas_candidates(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe,
-                                 int64_t n_cand, float4* cand, uint8_t* keep, int32_t* block_count, hipStream_t s);
-hipError_t launch_sas_scatter(const float4* cand, const uint8_t* keep, const int32_t* block_offset, int64_t n_cand,
-                              float4* pts, hipStream_t s);
+// Surface points: kept directions of every atom as bit masks (ceil(n_dirs / 64)
+// words per atom) and the exclusive sums of their numbers (count [n_rec + 1],
+// the total last); umax >= |u| of every direction, slack: see sas_keep_kernel.
+hipError_t launch_sas_keep(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe, float umax,
+                           float slack, uint64_t* keep, int32_t* count, hipStream_t s);
+hipError_t launch_sas_scatter(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe,
+                              const uint64_t* keep, const int32_t* offset, float4* pts, hipStream_t s);
+hipError_t launch_sas_split(const float4* pts, int n_pts, float* xyz, int32_t* atom, hipStream_t s);
 hipError_t launch_sas_features(const float4* atoms, int n_rec, const float4* pts, int n_pts, float* feat,
                                hipStream_t s);
-int sas_block_size();
 int output_lds_bytes(const LigDev& l, int chains, int modes);
 hipError_t launch_reset_times(uint64_t* t0, uint64_t* t1, int n, hipStream_t s);
 

@@ -2160,6 +2160,8 @@ __global__ __launch_bounds__(kGridThreads) void gridmap_kernel(GridBuildArgs a)
 // prank_eq_1 features.  Atom records are float4 (x, y, z, type bits) with
 // the expanded radius r = X-Score radius + probe computed in binary32.
 constexpr int kSasThreads = 256;
+constexpr int kSasWaves = kSasThreads / kWave;
+constexpr int kSasList = 320;    // neighbours collected per atom before they are tested (above 4 waves' worth)
 
 __device__ __forceinline__ float sas_radius(int t, float probe)
 {
@@ -2167,117 +2169,246 @@ __device__ __forceinline__ float sas_radius(int t, float probe)
     return R + probe;
 }
 
-// One thread per candidate c = x_a + r_a u_k (atom-major); the receptor is
-// streamed through LDS.  A candidate strictly inside another atom's
-// expanded sphere is dropped.  Writes the candidate, its keep flag and the
-// block's kept count.
-__global__ __launch_bounds__(kSasThreads) void sas_candidates_kernel(const float4* atoms, int n_rec, const float* dirs,
-                                                                     int n_dirs, float probe, int64_t n_cand,
-                                                                     float4* cand, uint8_t* keep, int32_t* block_count)
+// candidate c = x_a + r_a u
+__device__ __forceinline__ float3 sas_candidate(const float4& xa, float ra, const float* u)
 {
-    __shared__ float4 tile[kSasThreads];
-    __shared__ int count;
-    const int64_t idx = (int64_t)blockIdx.x * kSasThreads + threadIdx.x;
-    const bool valid = idx < n_cand;
-    int a = 0;
-    float cx = 0.f, cy = 0.f, cz = 0.f;
-    if (valid) {
-        a = (int)(idx / n_dirs);
-        const int k = (int)(idx % n_dirs);
-        const float4 xa = atoms[a];
-        const float ra = sas_radius(__float_as_uint(xa.w) & 0xff, probe);
-        cx = __builtin_fmaf(ra, dirs[3 * k], xa.x);
-        cy = __builtin_fmaf(ra, dirs[3 * k + 1], xa.y);
-        cz = __builtin_fmaf(ra, dirs[3 * k + 2], xa.z);
-    }
-    if (threadIdx.x == 0) count = 0;
-    __syncthreads();
-    bool buried = false;
-    for (int base = 0; base < n_rec; base += kSasThreads) {
-        __syncthreads();
-        const int b = base + threadIdx.x;
-        if (b < n_rec) {
-            const float4 xb = atoms[b];
-            const float rb = sas_radius(__float_as_uint(xb.w) & 0xff, probe);
-            tile[threadIdx.x] = make_float4(xb.x, xb.y, xb.z, rb * rb);
-        }
-        __syncthreads();
-        const int nb = min(kSasThreads, n_rec - base);
-        if (valid && !buried)
-            for (int j = 0; j < nb; ++j) {
-                const float4 t = tile[j];
-                const float dx = cx - t.x, dy = cy - t.y, dz = cz - t.z;
-                const float d2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
-                if (d2 < t.w && base + j != a) { buried = true; break; }
-            }
-    }
-    if (valid) {
-        cand[idx] = make_float4(cx, cy, cz, __int_as_float(a));
-        keep[idx] = buried ? 0 : 1;
-        if (!buried) atomicAdd(&count, 1);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) block_count[blockIdx.x] = count;
+    return make_float3(__builtin_fmaf(ra, u[0], xa.x), __builtin_fmaf(ra, u[1], xa.y), __builtin_fmaf(ra, u[2], xa.z));
 }
 
-// Kept candidates to their place: the block's offset plus the number of
-// kept candidates before this one in the block (in candidate order).
-__global__ __launch_bounds__(kSasThreads) void sas_scatter_kernel(const float4* cand, const uint8_t* keep,
-                                                                  const int32_t* block_offset, int64_t n_cand,
-                                                                  float4* pts)
+// Which candidates c = x_a + r_a u_k lie strictly inside no other atom's
+// expanded sphere, two atoms per wave.  Lanes run over the receptor and
+// collect, per atom, those whose sphere can reach a candidate (the candidates
+// lie within r_a max|u| of x_a; slack covers the rounding of their
+// coordinates); the candidates then meet these alone, both atoms' side by side
+// in the wave's halves when there are at most 32 directions, else 64
+// directions of one atom at a time.  Bound by VALU issue: 13 instructions per
+// atom and 64 atoms looked at, so the cost grows with n_rec^2 / 64 rather than
+// n_rec^2 n_dirs.  8,000 atoms x 30 directions: 807 us when every candidate
+// met every atom, 56 us now (36 us of them VALU issue); with the receptor
+// staged in LDS tiles, one atom per wave, 85-102 us.
+// Writes the kept directions as bit masks (ceil(n_dirs / 64) words per atom)
+// and their number.
+constexpr int kSasAtoms = 2;
+
+__global__ __launch_bounds__(kSasThreads) void sas_keep_kernel(const float4* atoms, int n_rec, const float* dirs,
+                                                               int n_dirs, float probe, float umax, float slack,
+                                                               uint64_t* keep, int32_t* count)
 {
-    __shared__ int pre[kSasThreads];
-    const int64_t idx = (int64_t)blockIdx.x * kSasThreads + threadIdx.x;
-    const int k = idx < n_cand ? keep[idx] : 0;
-    pre[threadIdx.x] = k;
-    __syncthreads();
-    for (int off = 1; off < kSasThreads; off <<= 1) {   // inclusive scan in the block
-        const int v = threadIdx.x >= off ? pre[threadIdx.x - off] : 0;
-        __syncthreads();
-        pre[threadIdx.x] += v;
-        __syncthreads();
+    __shared__ float4 lists[kSasWaves][kSasAtoms][kSasList];
+    const int l = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    float4(*list)[kSasList] = lists[wv];
+    const int a0 = (int)(blockIdx.x * kSasWaves + wv) * kSasAtoms;
+    if (a0 >= n_rec) return;
+    float4 xa[kSasAtoms];
+    float ra[kSasAtoms], reach2[kSasAtoms][4];   // squared reach by the neighbour's radius class
+    int n[kSasAtoms];
+    uint64_t buried[kSasAtoms];   // bit c: this lane's direction of chunk c
+#pragma unroll
+    for (int p = 0; p < kSasAtoms; ++p) {
+        xa[p] = atoms[min(a0 + p, n_rec - 1)];
+        ra[p] = sas_radius(__float_as_uint(xa[p].w) & 0xff, probe);
+        n[p] = 0;
+        buried[p] = 0;
+        const int first[4] = {0, 2, 5, 7};   // a type of each class
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float thr = fmaf(ra[p], umax, slack) + sas_radius(first[e], probe);
+            // a square that could overflow becomes NaN, which takes every atom
+            reach2[p][e] = thr > 1e18f ? __builtin_nanf("") : thr * thr * 1.0001f;
+        }
     }
-    if (k) pts[block_offset[blockIdx.x] + pre[threadIdx.x] - 1] = cand[idx];
+    const bool packed = n_dirs <= kWave / 2;
+    const int chunks = (n_dirs + kWave - 1) / kWave;   // at most 64 (PV_MAX_SAS_DIRS)
+    auto test = [&]() {
+        wave_sync();
+        for (int pass = 0; pass < (packed ? 1 : kSasAtoms * chunks); ++pass) {
+            const int p = packed ? l / (kWave / 2) : pass / chunks, c = packed ? 0 : pass % chunks;
+            const int k = packed ? l % (kWave / 2) : c * kWave + l;
+            const float4 xp = p ? xa[1] : xa[0];
+            const float3 x = sas_candidate(xp, p ? ra[1] : ra[0], dirs + 3 * min(k, n_dirs - 1));
+            const int np = p ? n[1] : n[0], nj = packed ? max(n[0], n[1]) : np;
+            bool in = false;
+#pragma unroll 4
+            for (int j = 0; j < nj; ++j) {
+                const float4 b = list[p][j];
+                const float ex = x.x - b.x, ey = x.y - b.y, ez = x.z - b.z;
+                in |= __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez)) < b.w && j < np;
+            }
+            if (p == 0) buried[0] |= (uint64_t)in << c;
+            else buried[1] |= (uint64_t)in << c;
+        }
+        n[0] = n[1] = 0;
+        wave_sync();
+    };
+    for (int base = 0; base < n_rec; base += 4 * kWave) {
+        float4 t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = base + u * kWave + l;
+            t[u] = b < n_rec ? atoms[b] : make_float4(__builtin_inff(), 0.f, 0.f, 0.f);   // past the end: far
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = base + u * kWave + l, ty = __float_as_uint(t[u].w) & 0xff;
+#pragma unroll
+            for (int p = 0; p < kSasAtoms; ++p) {
+                const float dx = xa[p].x - t[u].x, dy = xa[p].y - t[u].y, dz = xa[p].z - t[u].z;
+                const float thr2 = ty <= 1 ? reach2[p][0] : ty <= 4 ? reach2[p][1] : ty <= 6 ? reach2[p][2] : reach2[p][3];
+                const bool near = !(dx * dx + dy * dy + dz * dz >= thr2);
+                const uint64_t m = __ballot(near);
+                if (!m) continue;
+                if (near) {
+                    const float rb = sas_radius(ty, probe);
+                    list[p][n[p] + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+                        make_float4(t[u].x, t[u].y, t[u].z, b == a0 + p ? -1.f : rb * rb);   // itself buries nothing
+                }
+                n[p] += __popcll(m);
+            }
+        }
+        // test the lists when the next four loads could overflow them, and at the end
+        if (max(n[0], n[1]) > kSasList - 4 * kWave || base + 4 * kWave >= n_rec) test();
+    }
+#pragma unroll
+    for (int p = 0; p < kSasAtoms; ++p) {
+        if (a0 + p >= n_rec) break;
+        int total = 0;
+        for (int c = 0; c < chunks; ++c) {
+            uint64_t m;
+            if (packed)
+                m = (__ballot(!(buried[p] & 1)) >> (p * (kWave / 2))) & ((1ull << n_dirs) - 1);
+            else
+                m = __ballot(c * kWave + l < n_dirs && !((buried[p] >> c) & 1));
+            if (l == 0) keep[(int64_t)(a0 + p) * chunks + c] = m;
+            total += __popcll(m);
+        }
+        if (l == 0) count[a0 + p] = total;
+    }
+}
+
+// Exclusive sum of the atoms' counts in place; the total goes to count[n_rec].
+// One workgroup, a run of consecutive atoms per thread.
+__global__ __launch_bounds__(1024) void sas_scan_kernel(int32_t* count, int n_rec)
+{
+    __shared__ int wave_n[1024 / kWave];
+    const int t = threadIdx.x, per = (n_rec + 1023) / 1024;
+    const int b = min(t * per, n_rec), e = min(b + per, n_rec);
+    int sum = 0;
+#pragma unroll 8
+    for (int i = b; i < e; ++i) sum += count[i];
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int v = __shfl_up(incl, o);
+        if ((t & (kWave - 1)) >= o) incl += v;
+    }
+    if ((t & (kWave - 1)) == kWave - 1) wave_n[t / kWave] = incl;
+    __syncthreads();
+    int off = incl - sum, all = 0;
+    for (int w = 0; w < 1024 / kWave; ++w) {
+        off += w < t / kWave ? wave_n[w] : 0;
+        all += wave_n[w];
+    }
+#pragma unroll 8
+    for (int i = b; i < e; ++i) {
+        const int c = count[i];
+        count[i] = off;
+        off += c;
+    }
+    if (t == 0) count[n_rec] = all;
+}
+
+// The kept candidates in (atom, direction) order, one wave per atom.
+__global__ __launch_bounds__(kSasThreads) void sas_scatter_kernel(const float4* atoms, int n_rec, const float* dirs,
+                                                                  int n_dirs, float probe, const uint64_t* keep,
+                                                                  const int32_t* offset, float4* pts)
+{
+    const int l = threadIdx.x & (kWave - 1), a = blockIdx.x * kSasWaves + threadIdx.x / kWave;
+    if (a >= n_rec) return;
+    const float4 xa = atoms[a];
+    const float ra = sas_radius(__float_as_uint(xa.w) & 0xff, probe);
+    const int chunks = (n_dirs + kWave - 1) / kWave;
+    int off = offset[a];
+    for (int c = 0; c < chunks; ++c) {
+        const uint64_t m = keep[(int64_t)a * chunks + c];
+        if ((m >> l) & 1) {
+            const float3 x = sas_candidate(xa, ra, dirs + 3 * (c * kWave + l));
+            pts[off + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+                make_float4(x.x, x.y, x.z, __int_as_float(a));
+        }
+        off += __popcll(m);
+    }
+}
+
+// Point records (x, y, z, atom bits) into separate arrays (either may be NULL).
+__global__ __launch_bounds__(kSasThreads) void sas_split_kernel(const float4* pts, int n_pts, float* xyz, int32_t* atom)
+{
+    const int p = blockIdx.x * kSasThreads + threadIdx.x;
+    if (p >= n_pts) return;
+    const float4 v = pts[p];
+    if (xyz) { xyz[3 * (int64_t)p] = v.x; xyz[3 * (int64_t)p + 1] = v.y; xyz[3 * (int64_t)p + 2] = v.z; }
+    if (atom) atom[p] = __float_as_int(v.w);
 }
 
 // Eq. prank_eq_1 per point: channels 0..7 the one-hot XS type, 8..10 the
 // hydrophobic, donor and acceptor flags, each summing max(0, 1 - d/6) over
 // atoms with d^2 < 36; channel 11 counts the atoms with d^2 < 100 (the
-// protrusion).  One thread per point, receptor streamed through LDS.
+// protrusion).  One wave per kSasPoints points, lanes over atoms, four loads
+// in flight; the weights are summed only where some lane has an atom within
+// 6 A, the flags are sums of their types' channels.  Bound by VALU issue (ten
+// instructions per point and 64 atoms).  6,439 points x 8,000 atoms: 765 us
+// with one point per thread, which filled 26 of the 256 CUs, 39 us now.
+constexpr int kSasPoints = 2;
+
 __global__ __launch_bounds__(kSasThreads) void sas_features_kernel(const float4* atoms, int n_rec, const float4* pts,
                                                                    int n_pts, float* feat)
 {
-    __shared__ float4 tile[kSasThreads];
-    const int p = blockIdx.x * kSasThreads + threadIdx.x;
-    const bool valid = p < n_pts;
-    const float4 c = valid ? pts[p] : make_float4(0.f, 0.f, 0.f, 0.f);
-    float f[12];
+    const int l = threadIdx.x & (kWave - 1);
+    const int p0 = (int)__builtin_amdgcn_readfirstlane(blockIdx.x * kSasWaves + threadIdx.x / kWave) * kSasPoints;
+    if (p0 >= n_pts) return;
+    float4 c[kSasPoints];
+    float f[kSasPoints][8];
+    int near[kSasPoints];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) f[k] = 0.f;
-    for (int base = 0; base < n_rec; base += kSasThreads) {
-        __syncthreads();
-        if (base + threadIdx.x < n_rec) tile[threadIdx.x] = atoms[base + threadIdx.x];
-        __syncthreads();
-        const int nb = min(kSasThreads, n_rec - base);
-        for (int j = 0; j < nb; ++j) {
-            const float4 t = tile[j];
-            const float dx = c.x - t.x, dy = c.y - t.y, dz = c.z - t.z;
-            const float d2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
-            f[11] += d2 < 100.f ? 1.f : 0.f;
-            if (d2 < 36.f) {
-                const float w = 1.f - __builtin_amdgcn_sqrtf(d2) * (1.f / 6.f);
-                const int ty = __float_as_uint(t.w) & 0xff;
+    for (int p = 0; p < kSasPoints; ++p) {
+        c[p] = pts[min(p0 + p, n_pts - 1)];
+        near[p] = 0;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) f[k] += ty == k ? w : 0.f;
-                f[8] += ty == 0 ? w : 0.f;
-                f[9] += (ty == 3 || ty == 6) ? w : 0.f;
-                f[10] += (ty == 4 || ty == 5 || ty == 6) ? w : 0.f;
+        for (int k = 0; k < 8; ++k) f[p][k] = 0.f;
+    }
+    for (int base = 0; base < n_rec; base += 4 * kWave) {
+        float4 t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = base + u * kWave + l;
+            t[u] = b < n_rec ? atoms[b] : make_float4(__builtin_inff(), 0.f, 0.f, 0.f);   // past the end: far
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+            for (int p = 0; p < kSasPoints; ++p) {
+                const float dx = c[p].x - t[u].x, dy = c[p].y - t[u].y, dz = c[p].z - t[u].z;
+                const float d2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
+                near[p] += __popcll(__ballot(d2 < 100.f));
+                if (__ballot(d2 < 36.f)) {
+                    const float w = d2 < 36.f ? 1.f - __builtin_amdgcn_sqrtf(d2) * (1.f / 6.f) : 0.f;
+                    const int ty = __float_as_uint(t[u].w) & 0xff;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) f[p][k] += ty == k ? w : 0.f;
+                }
             }
         }
     }
-    if (valid)
 #pragma unroll
-        for (int k = 0; k < 12; ++k) feat[(int64_t)p * 12 + k] = f[k];
+    for (int p = 0; p < kSasPoints; ++p) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) f[p][k] = wsum(f[p][k]);
+        if (p0 + p < n_pts && l < 12) {
+            float v = l == 8 ? f[p][0] : l == 9 ? f[p][3] + f[p][6] : l == 10 ? f[p][4] + f[p][5] + f[p][6] : (float)near[p];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v = l == k ? f[p][k] : v;
+            feat[(int64_t)(p0 + p) * 12 + l] = v;
+        }
+    }
 }
 
 // ---------------------------------------------------------------- allocation-free scratch
@@ -2518,23 +2649,33 @@ int output_lds_bytes(const LigDev& l, int chains, int modes)
            modes * kSlot * 4 + 5 * round_up(modes, 4) * 4;
 }
 
-hipError_t launch_sas_candidates(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe,
-                                 int64_t n_cand, float4* cand, uint8_t* keep, int32_t* block_count, hipStream_t s)
+hipError_t launch_sas_keep(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe, float umax,
+                           float slack, uint64_t* keep, int32_t* count, hipStream_t s)
 {
-    if (n_cand <= 0) return hipSuccess;
-    const int64_t blocks = (n_cand + kSasThreads - 1) / kSasThreads;
-    hipLaunchKernelGGL(sas_candidates_kernel, dim3((unsigned)blocks), dim3(kSasThreads), 0, s, atoms, n_rec, dirs,
-                       n_dirs, probe, n_cand, cand, keep, block_count);
+    if (n_rec > 0) {
+        hipLaunchKernelGGL(sas_keep_kernel, dim3((n_rec + kSasWaves * kSasAtoms - 1) / (kSasWaves * kSasAtoms)),
+                           dim3(kSasThreads), 0, s, atoms, n_rec, dirs, n_dirs, probe, umax, slack, keep, count);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(sas_scan_kernel, dim3(1), dim3(1024), 0, s, count, n_rec);
     return hipGetLastError();
 }
 
-hipError_t launch_sas_scatter(const float4* cand, const uint8_t* keep, const int32_t* block_offset, int64_t n_cand,
-                              float4* pts, hipStream_t s)
+hipError_t launch_sas_scatter(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe,
+                              const uint64_t* keep, const int32_t* offset, float4* pts, hipStream_t s)
 {
-    if (n_cand <= 0) return hipSuccess;
-    const int64_t blocks = (n_cand + kSasThreads - 1) / kSasThreads;
-    hipLaunchKernelGGL(sas_scatter_kernel, dim3((unsigned)blocks), dim3(kSasThreads), 0, s, cand, keep, block_offset,
-                       n_cand, pts);
+    if (n_rec <= 0) return hipSuccess;
+    hipLaunchKernelGGL(sas_scatter_kernel, dim3((n_rec + kSasWaves - 1) / kSasWaves), dim3(kSasThreads), 0, s, atoms,
+                       n_rec, dirs, n_dirs, probe, keep, offset, pts);
+    return hipGetLastError();
+}
+
+hipError_t launch_sas_split(const float4* pts, int n_pts, float* xyz, int32_t* atom, hipStream_t s)
+{
+    if (n_pts <= 0 || (!xyz && !atom)) return hipSuccess;
+    hipLaunchKernelGGL(sas_split_kernel, dim3((n_pts + kSasThreads - 1) / kSasThreads), dim3(kSasThreads), 0, s, pts,
+                       n_pts, xyz, atom);
     return hipGetLastError();
 }
 
@@ -2542,11 +2683,10 @@ hipError_t launch_sas_features(const float4* atoms, int n_rec, const float4* pts
                                hipStream_t s)
 {
     if (n_pts <= 0) return hipSuccess;
-    const int blocks = (n_pts + kSasThreads - 1) / kSasThreads;
-    hipLaunchKernelGGL(sas_features_kernel, dim3(blocks), dim3(kSasThreads), 0, s, atoms, n_rec, pts, n_pts, feat);
+    const int per = kSasWaves * kSasPoints;
+    hipLaunchKernelGGL(sas_features_kernel, dim3((n_pts + per - 1) / per), dim3(kSasThreads), 0, s, atoms, n_rec, pts,
+                       n_pts, feat);
     return hipGetLastError();
 }
-
-int sas_block_size() { return kSasThreads; }
 
 }  // namespace pv

@@ -50,6 +50,19 @@ def test_multi_pocket_receptor_full_size(oracle, pv_ctx):
     _check(oracle, pv_ctx, rx, rt, S.sphere_directions(30), sample=3000)
 
 
+@pytest.mark.parametrize("n_rec, cube, n_dirs, scale", [
+    (2, 3.0, 1, 1.0),        # the smallest neighbourhood
+    (257, 12.0, 64, 1.0),    # one atom past a tile; one whole chunk of directions
+    (300, 5.0, 65, 1.0),     # every atom a neighbour: the list is emptied several times; two chunks of directions
+    (1030, 24.0, 30, 1.0),   # more atoms than the scan has threads
+    (400, 30.0, 33, 2.5),    # directions longer than 1 reach further
+])
+def test_neighbour_lists(oracle, pv_ctx, n_rec, cube, n_dirs, scale):
+    g = np.random.default_rng(n_rec)
+    rx, rt = S.receptor(g, n_rec, cube)
+    _check(oracle, pv_ctx, rx, rt, S.sphere_directions(n_dirs) * np.float32(scale))
+
+
 def test_degenerate_receptors(oracle, pv_ctx):
     import paper_2506_20043_amd as pv
     one = np.array([[1.0, 2.0, 3.0]], np.float32)
