@@ -404,7 +404,7 @@ pv_status pv_local_opt(pv_ctx* ctx, const pv_grids* grids, const pv_ligands* lig
  * rescored: its energy E = e_inter + e_intra and the reported affinity
  * e_inter / (1 + affinity_w T).  The refined poses are sorted by E (ties to
  * the earlier kept pose), filtered by r.m.s.d. the same way, and written in
- * that order.  One wave per job.
+ * that order.  One workgroup per job.
  *
  * plan: the jobs, grids, ligands, chains and BFGS settings of a dock plan.
  * chain_best_e [n_jobs][chains], chain_best_dof [n_jobs][chains][in_stride]:

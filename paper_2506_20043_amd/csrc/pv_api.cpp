@@ -1329,9 +1329,9 @@ pv_status pv_output_stage(pv_plan* P, const float* chain_best_e, const float* ch
     a.mode_affinity = out->mode_affinity;
     a.mode_dof = out->mode_dof;
     a.out_stride = out->dof_stride;
-    if (output_lds_bytes(a.l, a.chains, a.modes) > P->ctx->lds_per_block)
+    if (output_lds_bytes(a.l, a.chains, a.modes, 1) > P->ctx->lds_per_block)
         return fail(PV_E_RANGE, "chains, modes and ligand size need more LDS than one workgroup has");
-    hipError_t e = launch_output(a, (hipStream_t)stream);
+    hipError_t e = launch_output(a, P->ctx->n_cu, P->ctx->lds_per_block, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "output-stage launch");
     return PV_OK;
 }

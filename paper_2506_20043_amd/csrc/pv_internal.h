@@ -220,7 +220,7 @@ hipError_t launch_job_reduce(const float* chain_best_e, const int64_t* chain_eva
                              int32_t n_jobs, int32_t chains, float* job_best_e, int32_t* job_best_chain,
                              int64_t* job_evals, int32_t* job_status, hipStream_t s);
 hipError_t launch_local_opt(const OptArgs& a, int n_cu, hipStream_t s);
-hipError_t launch_output(const OutputArgs& a, hipStream_t s);
+hipError_t launch_output(const OutputArgs& a, int n_cu, int lds_per_block, hipStream_t s);
 // Surface points: kept directions of every atom as bit masks (ceil(n_dirs / 64)
 // words per atom) and the exclusive sums of their numbers (count [n_rec + 1],
 // the total last); umax >= |u| of every direction, slack: see sas_keep_kernel.
@@ -231,7 +231,8 @@ hipError_t launch_sas_scatter(const float4* atoms, int n_rec, const float* dirs,
 hipError_t launch_sas_split(const float4* pts, int n_pts, float* xyz, int32_t* atom, hipStream_t s);
 hipError_t launch_sas_features(const float4* atoms, int n_rec, const float4* pts, int n_pts, float* feat,
                                hipStream_t s);
-int output_lds_bytes(const LigDev& l, int chains, int modes);
+// LDS of an output-stage workgroup of `waves` waves (1: the least a job needs)
+int output_lds_bytes(const LigDev& l, int chains, int modes, int waves);
 hipError_t launch_reset_times(uint64_t* t0, uint64_t* t1, int n, hipStream_t s);
 
 // Scratch of the allocation-free dock entry point, one file-scope device

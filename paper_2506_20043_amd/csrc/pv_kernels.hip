@@ -1776,19 +1776,34 @@ __device__ __forceinline__ float sq_dev(const Topo<A, SL>& T, const Lds& S, cons
     return wsum(s);
 }
 
-// One wave per job (Methods, end of "Accelerated Docking with QuickVina
+// One workgroup per job (Methods, end of "Accelerated Docking with QuickVina
 // 2-GPU 2.1"; last steps of Supplementary Algorithm 2): the chains' best
 // poses in ascending energy; greedy r.m.s.d. clustering keeps a pose unless
 // it lies within rmsd_cut of a kept one, up to `modes`; each kept pose is
 // refined by BFGS and rescored (E, and the affinity e_inter / (1 + w T));
 // the refined poses are sorted again, filtered by r.m.s.d. the same way and
 // written out.  r.m.s.d. < cut is tested as sum |dx|^2 < cut^2 N.
+//
+// Bound by the latency of one wave's chain of evaluations, so a job's work is
+// spread over up to kOutWaves waves (threadIdx.y), each with its own LDS
+// tables: they take the clustering's poses a batch at a time (each wave its
+// pose against the kept ones and against the batch's earlier ones, then the
+// batch is decided in order from the recorded conflicts), the refinements and
+// the rows of the final filter's conflict table.  Every comparison and every
+// refinement is the one a single wave makes, so the results do not depend on
+// the number of waves.  One wave -> this: 5 jobs x 256 chains, 20 modes 718 ->
+// 141 us; 1,024 jobs x 32 chains 1,275 -> 1,128 us; 256 jobs of 65-80 atoms x
+// 16 chains 1,294 -> 359 us.
+constexpr int kOutWaves = 8;
+
 template <int A>
-__global__ __launch_bounds__(64) void output_kernel(OutputArgs a)
+__global__ __launch_bounds__(kWave * kOutWaves) void output_kernel(OutputArgs a)
 {
     extern __shared__ __align__(16) char smem[];
-    const Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOutput, A, false));
-    char* ext = smem + lds_bytes(a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOutput, A, false));
+    const int W = (int)blockDim.y, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+    const int one = lds_bytes(a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOutput, A, false));
+    const Lds S = carve(smem + wv * one, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOutput, A, false));
+    char* ext = smem + W * one;
     const int ma = S.ma, M = a.modes, C = a.chains;
     int* order = (int*)ext;     ext += round_up(C, 4) * 4;
     float4* rep = (float4*)ext; ext += M * ma * 16;
@@ -1797,8 +1812,12 @@ __global__ __launch_bounds__(64) void output_kernel(OutputArgs a)
     float* ra = (float*)ext;    ext += round_up(M, 4) * 4;
     int* kc = (int*)ext;        ext += round_up(M, 4) * 4;
     int* fo = (int*)ext;        ext += round_up(M, 4) * 4;
-    int* so = (int*)ext;
-    const int l = lane_id();
+    uint32_t* conf = (uint32_t*)ext;   // conflict masks of the final filter
+    // and of a clustering batch, in a pose slot of the first wave that the output stage does not use otherwise
+    uint32_t* flags = (uint32_t*)((float*)(smem + ((char*)S.pose - S.base)) + SLOT_CUR * kSlot);
+    static_assert(kOutWaves + 1 <= kSlot, "room for the conflict masks");
+    constexpr uint32_t kStands = 0x80000000u;   // a pose of the batch that no kept pose excludes
+    const int l = lane_id(), tid = wv * kWave + l, nthr = W * kWave;
     const int job = blockIdx.x;
     Topo<A, false> T;
     T.lig = -1;
@@ -1809,36 +1828,56 @@ __global__ __launch_bounds__(64) void output_kernel(OutputArgs a)
     const float cut2n = a.rmsd_cut * a.rmsd_cut * (float)T.n;
     float* x = S.pose + SLOT_X * kSlot;
     // 1. chains in ascending energy (rank of each chain by counting)
-    for (int c = l; c < C; c += kWave) {
+    for (int c = tid; c < C; c += nthr) {
         const float ec = ce[c];
         int rank = 0;
+#pragma unroll 8
         for (int c2 = 0; c2 < C; ++c2) rank += precedes(ce[c2], c2, ec, c) ? 1 : 0;
         order[rank] = c;
     }
-    wave_sync();
-    // 2. greedy clustering in that order
+    if (tid == 0) flags[kOutWaves] = 0;   // the next pose to refine
+    __syncthreads();
+    // 2. greedy clustering in that order, W poses at a time
     int nk = 0;
-    for (int r = 0; r < C && nk < M; ++r) {
-        const int c = order[r];
-        const float* src = a.chain_dof + ((int64_t)job * C + c) * a.in_stride;
-        if (l < 7 + T.nt) x[l] = src[l];
-        wave_sync();
-        pose_positions(T, S, x);
-        bool keep = true;
-        for (int q = 0; q < nk && keep; ++q) keep = !(sq_dev(T, S, rep + q * ma) < cut2n);
-        if (keep) {
+    for (int r0 = 0; r0 < C && nk < M; r0 += W) {
+        const int r = r0 + wv;
+        bool stands = r < C;
+        if (stands) {
+            const float* src = a.chain_dof + ((int64_t)job * C + order[r]) * a.in_stride;
+            if (l < 7 + T.nt) x[l] = src[l];
+            wave_sync();
+            pose_positions(T, S, x);
+            for (int q = 0; q < nk && stands; ++q) stands = !(sq_dev(T, S, rep + q * ma) < cut2n);
+        }
+        __syncthreads();   // every wave's positions are in place
+        uint32_t f = stands ? kStands : 0u;
+        for (int w = 0; w < wv && stands; ++w)
+            if (sq_dev(T, S, (const float4*)(smem + w * one + ((char*)S.pos - S.base))) < cut2n) f |= 1u << w;
+        if (l == 0) flags[wv] = f;
+        __syncthreads();
+        uint32_t kept = 0;
+        for (int w = 0; w < W && nk < M; ++w) {
+            const uint32_t fw = flags[w];
+            if (!(fw & kStands) || (fw & kept)) continue;
+            kept |= 1u << w;
+            if (w == wv) {
 #pragma unroll
-            for (int aa = 0; aa < A; ++aa) {
-                const int i = l * A + aa;
-                if (i < T.n) rep[nk * ma + i] = S.pos[i];
+                for (int aa = 0; aa < A; ++aa) {
+                    const int i = l * A + aa;
+                    if (i < T.n) rep[nk * ma + i] = S.pos[i];
+                }
+                if (l == 0) kc[nk] = order[r];
             }
-            if (l == 0) kc[nk] = c;
             ++nk;
         }
-        wave_sync();
+        __syncthreads();   // the batch's flags and positions are read, its kept poses stored
     }
-    // 3. refine and rescore every kept pose
-    for (int q = 0; q < nk; ++q) {
+    // 3. refine and rescore every kept pose, each wave the next one when it is free
+    while (true) {
+        uint32_t v0 = 0;
+        if (l == 0) v0 = atomicAdd(&flags[kOutWaves], 1u);
+        const int q = lane_i((int)v0, 0);
+        if (q >= nk) break;
         const float* src = a.chain_dof + ((int64_t)job * C + kc[q]) * a.in_stride;
         if (l < 7 + T.nt) x[l] = src[l];
         wave_sync();
@@ -1864,49 +1903,56 @@ __global__ __launch_bounds__(64) void output_kernel(OutputArgs a)
         }
         wave_sync();
     }
+    __syncthreads();
     // 4. final sort of the refined poses, r.m.s.d. filter, output
-    if (l < nk) {
+    if (tid < nk) {
         int rank = 0;
-        for (int q2 = 0; q2 < nk; ++q2) rank += precedes(re[q2], q2, re[l], l) ? 1 : 0;
-        fo[rank] = l;
+        for (int q2 = 0; q2 < nk; ++q2) rank += precedes(re[q2], q2, re[tid], tid) ? 1 : 0;
+        fo[rank] = tid;
     }
-    wave_sync();
-    const int64_t o0 = (int64_t)job * M;
-    int no = 0;
-    for (int r = 0; r < nk; ++r) {
-        const int q = fo[r];
-        // S.pos <- refined pose q, compared with the poses already written
+    __syncthreads();
+    for (int r = wv; r < nk; r += W) {
 #pragma unroll
         for (int aa = 0; aa < A; ++aa) {
             const int i = l * A + aa;
-            if (i < T.n) S.pos[i] = rep[q * ma + i];
+            if (i < T.n) S.pos[i] = rep[fo[r] * ma + i];
         }
         wave_sync();
-        bool keep = true;
-        for (int s2 = 0; s2 < no && keep; ++s2) keep = !(sq_dev(T, S, rep + so[s2] * ma) < cut2n);
-        if (keep) {
+        uint32_t m = 0;
+        for (int s2 = 0; s2 < r; ++s2)
+            if (sq_dev(T, S, rep + fo[s2] * ma) < cut2n) m |= 1u << s2;
+        if (l == 0) conf[r] = m;
+        wave_sync();
+    }
+    __syncthreads();
+    const int64_t o0 = (int64_t)job * M;
+    int no = 0;
+    uint32_t kept = 0;
+    for (int r = 0; r < nk; ++r) {
+        if (conf[r] & kept) continue;
+        kept |= 1u << r;
+        if (no % W == wv) {
+            const int q = fo[r];
             if (l == 0) {
-                so[no] = q;
                 a.mode_chain[o0 + no] = kc[q];
                 a.mode_e[o0 + no] = re[q];
                 if (a.mode_affinity) a.mode_affinity[o0 + no] = ra[q];
             }
             if (a.mode_dof && l < a.out_stride)
                 a.mode_dof[(o0 + no) * a.out_stride + l] = l < 7 + T.nt ? rdof[q * kSlot + l] : 0.f;
-            ++no;
         }
-        wave_sync();
+        ++no;
     }
     const float nanv = __int_as_float(0x7fc00000);
-    for (int o = no + l; o < M; o += kWave) {
+    for (int o = no + tid; o < M; o += nthr) {
         a.mode_chain[o0 + o] = -1;
         a.mode_e[o0 + o] = nanv;
         if (a.mode_affinity) a.mode_affinity[o0 + o] = nanv;
     }
     if (a.mode_dof)
-        for (int o = no; o < M; ++o)
+        for (int o = no + wv; o < M; o += W)
             if (l < a.out_stride) a.mode_dof[(o0 + o) * a.out_stride + l] = 0.f;
-    if (l == 0) a.n_modes[job] = no;
+    if (tid == 0) a.n_modes[job] = no;
 }
 
 // ---------------------------------------------------------------- grid maps
@@ -2630,23 +2676,28 @@ hipError_t launch_local_opt(const OptArgs& a, int n_cu, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_output(const OutputArgs& a, hipStream_t s)
+hipError_t launch_output(const OutputArgs& a, int n_cu, int lds_per_block, hipStream_t s)
 {
     if (a.n_jobs <= 0) return hipSuccess;
-    const int lds = output_lds_bytes(a.l, a.chains, a.modes);
+    // Few jobs: all the waves a workgroup may have (8 fill a CU at 2 per SIMD),
+    // for the latency.  More jobs than CUs: 4, two workgroups a CU, whose
+    // serial parts overlap and which divide the usual 20 modes evenly.  Fewer
+    // where LDS has no room for their tables.
+    int waves = a.n_jobs <= n_cu ? kOutWaves : kOutWaves / 2;
+    while (waves > 1 && output_lds_bytes(a.l, a.chains, a.modes, waves) > lds_per_block) --waves;
+    const int lds = output_lds_bytes(a.l, a.chains, a.modes, waves);
     if (a.l.max_atoms <= 64)
-        hipLaunchKernelGGL((output_kernel<1>), dim3(a.n_jobs), dim3(64), lds, s, a);
+        hipLaunchKernelGGL((output_kernel<1>), dim3(a.n_jobs), dim3(kWave, waves), lds, s, a);
     else
-        hipLaunchKernelGGL((output_kernel<2>), dim3(a.n_jobs), dim3(64), lds, s, a);
+        hipLaunchKernelGGL((output_kernel<2>), dim3(a.n_jobs), dim3(kWave, waves), lds, s, a);
     return hipGetLastError();
 }
 
-int output_lds_bytes(const LigDev& l, int chains, int modes)
+int output_lds_bytes(const LigDev& l, int chains, int modes, int waves)
 {
     const int ma = lds_atoms(l.max_atoms);
-    return lds_bytes(l.max_atoms, l.max_pairs, l.max_ell, kernel_needs(kKindOutput, l.max_atoms > 64 ? 2 : 1, false)) +
-           round_up(chains, 4) * 4 + modes * ma * 16 +
-           modes * kSlot * 4 + 5 * round_up(modes, 4) * 4;
+    return waves * lds_bytes(l.max_atoms, l.max_pairs, l.max_ell, kernel_needs(kKindOutput, l.max_atoms > 64 ? 2 : 1, false)) +
+           round_up(chains, 4) * 4 + modes * ma * 16 + modes * kSlot * 4 + 5 * round_up(modes, 4) * 4;
 }
 
 hipError_t launch_sas_keep(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe, float umax,

@@ -162,6 +162,32 @@ def test_output_of_a_dock_is_valid(oracle, pv_ctx):
                 assert _rmsd(xs[o], xs[p]) >= 1.0 - 1e-3
 
 
+@pytest.mark.parametrize("n_atoms, chains, modes", [(20, 1, 1), (20, 7, 3), (20, 9, 20), (20, 65, 32), (70, 33, 20)])
+def test_output_independent_of_the_waves(oracle, pv_ctx, n_atoms, chains, modes):
+    """A few jobs run eight waves each, more jobs than CUs four: batches of the clustering, refinements and filter
+    rows fall on other waves, and every job's modes stay the same bit for bit."""
+    import paper_2506_20043_amd as pv
+    cfg = S.CONFIGS["tiny"]
+    rx, rt, bxs = S.make_receptor(cfg)
+    mols = [S.tree_ligand(np.random.default_rng(5), n_atoms, 6)]
+    grids, ligs, G = _setup(oracle, pv_ctx, rx, rt, bxs[0], mols)
+    params = pv.dock_params(chains=chains, steps=8, seed=3)
+    dock = pv.dock(pv_ctx, grids, ligs, [(0, 0)], params)
+    # pairs of near copies among the chains, so that the clustering drops some
+    dof, e = dock["chain_best_dof"].cpu().numpy(), dock["chain_best_e"].cpu().numpy()
+    dof[1::3, :] = dof[:-1:3, :][:len(dof[1::3])]
+    dof[1::3, 0] += np.float32(0.2)
+    runs = []
+    for n in (2, 300):
+        res = _run(pv, pv_ctx, grids, ligs, [(0, 0)] * n, chains, np.stack([dof] * n), np.stack([e] * n), modes=modes)
+        for k, v in res.items():
+            assert np.array_equal(v, np.stack([v[0]] * n), equal_nan=v.dtype.kind == "f"), k
+        runs.append(res)
+    for k in runs[0]:
+        assert np.array_equal(runs[0][k][0], runs[1][k][0], equal_nan=runs[0][k].dtype.kind == "f"), k
+    assert 1 <= runs[0]["n_modes"][0] <= modes
+
+
 def test_output_rejects(pv_ctx):
     import paper_2506_20043_amd as pv
     cfg = S.CONFIGS["tiny"]
