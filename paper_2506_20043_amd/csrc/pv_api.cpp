@@ -454,6 +454,9 @@ pv_status pv_ligands_create(pv_ctx* ctx, int32_t n_lig, const int32_t* atom_off,
         D.rounds = M.rounds;
         D.ell_base = (int32_t)ell.size();
         D.ell_w = M.ell_w;
+        D.n_plain = M.n_plain;
+        D.n_hyd = M.n_hyd;
+        D.intra_lb = M.intra_lb;
         for (int a = 0; a < 3; ++a) D.anchor[a] = M.anchor[a];
         D.rot_amp_scale = (float)(1.0 / std::max((double)M.rg, 1e-3));
         atoms.insert(atoms.end(), M.ref.begin(), M.ref.end());

@@ -25,9 +25,12 @@ struct alignas(16) DevLig {
     int32_t rounds;      // pointer-doubling rounds to compose the frame tree
     int32_t ell_base;    // first word of the atom -> pair table
     int32_t ell_w;       // entries per atom row (the largest row)
-    int32_t pad0;
+    int32_t n_plain;     // pairs below it are plain,
     float anchor[3];     // reference centroid of the root fragment
     float rot_amp_scale; // 1 / max(R_g, 1e-3)
+    int32_t n_hyd;       // below this one hydrophobic, the rest hydrogen bonds
+    float intra_lb;      // a lower bound of the intra energy
+    int32_t pad0, pad1;
 };
 
 // One rigid fragment.  Fragment 0 is the root (parent -1).
@@ -49,9 +52,9 @@ struct alignas(16) DevFrag {
 // row of its first atom | in the row of its second atom << 16 (force-slot
 // layout: slot s of atom a at s * (n | 1) + a, slots below ell_w).
 // Atom -> pair table (ELL, [n][ell_w] words, rows 16-byte aligned): entry k of atom i is
-// p | j << 16, the k-th pair p (index into the pair list) that holds atom i
-// and its partner j; rows shorter than ell_w are padded with p = n_pairs
-// (a zero coefficient) and j = i.
+// 4 p | 16 j << 16, the k-th pair p (index into the pair list) that holds atom
+// i and its partner j, both as byte offsets; rows shorter than ell_w are padded
+// with p = n_pairs (a zero coefficient) and j = i.
 
 // Host model of one ligand (built by build_ligand_model).
 struct LigModel {
@@ -65,6 +68,8 @@ struct LigModel {
     std::vector<uint32_t> ell;      // [n][ell_w]
     std::vector<uint32_t> pslot;    // per pair: slot in row i | slot in row j << 16
     int ell_w = 0;
+    int n_plain = 0, n_hyd = 0;     // ends of the plain and of the hydrophobic pairs in the list
+    float intra_lb = 0.f;           // sum over the pairs of their class's least pair energy
     float anchor[3] = {0, 0, 0};
     float rg = 0.f;
 };
@@ -73,6 +78,10 @@ struct LigModel {
 int build_ligand_model(int n, const float* xyz, const uint8_t* type, int nb, const int32_t* bonds,
                        const uint8_t* rot, LigModel& out, std::string& err);
 
+
+// Least energy of an intra pair of class 0 (plain), 1 (hydrophobic) or 2
+// (hydrogen bond) over all distances.
+float least_pair_energy(uint32_t cls);
 
 // ------------------------------------------------------------ launchers
 struct GridDev {

@@ -45,6 +45,12 @@ __device__ __forceinline__ float lane_f(float v, int lane)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+// lane `src4 / 4`'s value
+__device__ __forceinline__ float from_lane(int src4, float v)
+{
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(src4, __float_as_int(v)));
+}
+
 __device__ __forceinline__ int lane_i(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 
 // sum over the 64 lanes, identical in every lane
@@ -54,20 +60,26 @@ __device__ __forceinline__ float wsum(float v)
     v += dpp0<0x4E>(v);   // quad_perm(2,3,0,1): lane ^ 2
     v += dpp0<0x141>(v);  // row_half_mirror: the other quad of each 8 lanes
     v += dpp0<0x140>(v);  // row_mirror: the other half of each row
-    return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
+    // the rows' sums: (row 0 + row 1) + (row 2 + row 3) ends in lane 63
+    v += dpp0<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp0<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return lane_f(v, 63);
 }
 
-// sum over lanes 0..n-1 of v, where every lane from n up holds zero (n is
-// wave-uniform): rows past the last non-zero one are not read
-__device__ __forceinline__ float wsum_n(float v, int n)
+// sum over lanes 0..n-1 of a b, where every lane from n up holds zero (n is
+// wave-uniform): rows past the last non-zero one are not read.  A lane's own
+// product is fused onto its neighbour's rounded one.
+__device__ __forceinline__ float wdot_n(float a, float b, int n)
 {
-    v += dpp0<0xB1>(v);
+    float v = fmaf(a, b, dpp0<0xB1>(a * b));
     v += dpp0<0x4E>(v);
     v += dpp0<0x141>(v);
     v += dpp0<0x140>(v);
     if (n <= 16) return lane_f(v, 0);
-    if (n <= 32) return lane_f(v, 0) + lane_f(v, 16);
-    return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
+    v += dpp0<0x142, 0xA>(v);
+    if (n <= 32) return lane_f(v, 31);
+    v += dpp0<0x143, 0xC>(v);
+    return lane_f(v, 63);
 }
 
 // integer sum over the 64 lanes, identical in every lane
@@ -267,13 +279,19 @@ __device__ __forceinline__ float trilinear(const BoxView& B, int t, float x, flo
 }
 
 // ---------------------------------------------------------------- LDS carving
-// Pose slots hold [t(3), q(4), psi(T)] = up to 39 floats; 40 with padding.
+// A pose [t(3), q(4), psi(T)] has up to 39 entries and lives in a register,
+// entry l in lane l: a chain alone on its SIMD spends a third of its time
+// waiting, mostly for LDS, and every step of a pose through LDS (stored, copied
+// between slots, read back entry by entry) was such a wait.  With the poses in
+// registers, frames composed in place and the tail passes of the slot form: one
+// ligand's dock (8 chains) 27.9 -> 25.4 ms, a screening slice 414 -> 402 ms, the
+// local optimisation of 16,384 poses 3.31 -> 3.22 ms, and the searches the same
+// bit for bit.
 constexpr int kSlot = 40;
-enum { SLOT_X = 0, SLOT_XT = 1, SLOT_XA = 2, SLOT_CUR = 3, SLOT_BEST = 4, kNSlots = 5 };
 
 struct Lds {
-    char* base;        // start of the workgroup's dynamic LDS
-    float* pose;       // [kNSlots][kSlot]
+    char* base;        // start of the wave's LDS
+    uint32_t pos0;     // LDS byte address of pos
     float* frame;      // [kMaxFrag][12] frames, then [kMaxFrag] ancestor links / torsion derivatives
                        // (without the frames: the [kMaxFrag] torsion derivatives only)
     float4* pos;       // [ma + 1]; entry ma: a point far outside every box
@@ -281,7 +299,7 @@ struct Lds {
     float* pre;        // [6][max_atoms]
     uint4* pairs;      // [max_pairs rounded up to kPairPass] pair records, slot layout (see stage_ligand)
     float* cp;         // [max_pairs rounded up to kWave] per-pair force coefficient, gather layout
-    uint32_t* pw;      // [max_pairs rounded up to kWave] pair words, gather layout (padding: the far point)
+    uint32_t* pw;      // [max_pairs rounded up to kWave] pair words, gather layout (see stage_ligand)
     float4* fs;        // [max_ell + 1] pair forces in slot rows of n | 1 atoms (slot-major), then one
                        // write-only slot for the padding records, slot layout
     int ma;
@@ -328,10 +346,16 @@ struct LdsNeeds {
     bool pw;   // gather layout: the pair words in LDS too (one atom per lane), else read from global memory
 };
 
+// Bytes that no region uses.  They keep the sizes, and with them the choice
+// between the two layouts (launch_shape), what they were when the poses were
+// held here: the layouts sum forces in another order, so another choice would
+// change the searches' last bits.
+constexpr int kLdsSpare = 5 * kSlot * 4;
+
 __host__ __device__ inline int lds_bytes(int max_atoms, int max_pairs, int max_ell, LdsNeeds nd)
 {
     const int ma = lds_atoms(max_atoms);
-    int b = kNSlots * kSlot * 4 + (ma + 1) * 16 + 6 * ma * 4;
+    int b = kLdsSpare + (ma + 1) * 16 + 6 * ma * 4;
     b += nd.frames ? kMaxFrag * 13 * 4 + 12 : round_up(kMaxFrag, 4) * 4;
     if (nd.frc) b += ma * 16;
     if (nd.slots) b += round_up(max_pairs < 1 ? 1 : max_pairs, kPairPass) * 16 + (max_ell + 1) * 16;
@@ -345,8 +369,8 @@ __device__ __forceinline__ Lds carve(char* base, int max_atoms, int max_pairs, i
     const int ma = lds_atoms(max_atoms);
     char* p = base;
     s.base = base;
+    s.pos0 = 0;   // the kernels have no static LDS, so the dynamic LDS starts at address 0
     s.pos = (float4*)p; p += (ma + 1) * 16;
-    s.pose = (float*)p; p += kNSlots * kSlot * 4;
     s.pre = (float*)p; p += 6 * ma * 4;
     s.frc = nullptr;
     if (nd.frc) { s.frc = (float4*)p; p += ma * 16; }
@@ -384,19 +408,24 @@ __host__ __device__ inline LdsNeeds kernel_needs(int kind, int A, bool slots)
 // bond at d = -0.466), rounded down in the fourth digit.
 constexpr float kPairMin0 = -0.03615f, kPairMin1 = -0.07125f, kPairMin2 = -0.22356f;
 
+float least_pair_energy(uint32_t cls) { return cls == 0 ? kPairMin0 : (cls == 1 ? kPairMin1 : kPairMin2); }
+
 // ---------------------------------------------------------------- staged ligand
 // Topology lives in registers: atoms blocked A per lane (atom = lane*A + a),
 // fragments one per lane, and for lane 6+k the fragment of torsion k.
 template <int A, bool SL>
 struct Topo {
     int n, nf, nt, np, rounds, lig, ell_w, fs_stride;
-    float anc_x, anc_y, anc_z, rot_scale;
+    float rot_scale;
     float4 ref[A];
-    int f_parent, f_tors, f_child, f_a0, f_end;
-    uint64_t links;   // the ancestor a fragment lane composes with in each pointer-doubling round, 6 bits per
-                      // round (63: none): fragments 0..32 and up to 6 rounds
-    float ax, ay, az, cx, cy, cz;
-    int dof_frag;
+    int psi_src;      // 4 x the lane of this fragment lane's torsion angle in the pose
+    int f_child, f_a0, f_end;
+    uint32_t link0, link1;   // 4 x the lane of the ancestor a fragment lane composes with in each
+                             // pointer-doubling round (itself: none), a byte per round: rounds 0..3, 4..5
+    float ax, ay, az; // unit axis of the fragment's torsion
+    float cx, cy, cz; // a point of that axis (the child atom's reference position); the root: its anchor
+    int dof_src;      // 4 x the fragment lane of this tangent lane's torsion
+    int np0, np1;     // pairs below np0 are plain, below np1 hydrophobic, the rest hydrogen bonds
     float lb;   // a lower bound of the intra energy: the sum over the pairs of their class's least pair energy
     const uint32_t* gpairs;   // pair list and atom -> pair table in global
     const uint32_t* gell;     // memory (read from there when A > 1)
@@ -414,52 +443,47 @@ __device__ void stage_ligand(Topo<A, SL>& T, const LigDev& L, int lig, const Lds
     // the gather are contiguous, and the slots of one atom fall in different
     // LDS banks
     T.fs_stride = T.n | 1;
-    T.anc_x = d.anchor[0]; T.anc_y = d.anchor[1]; T.anc_z = d.anchor[2]; T.rot_scale = d.rot_amp_scale;
+    T.rot_scale = d.rot_amp_scale;
 #pragma unroll
     for (int a = 0; a < A; ++a) {
         int i = l * A + a;
         T.ref[a] = i < T.n ? L.atoms[d.atom_base + i] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
+    int parent = -1;
+    T.psi_src = 0; T.f_child = 0; T.f_a0 = 0; T.f_end = 0;
+    T.ax = T.ay = T.az = T.cx = T.cy = T.cz = 0.f;
     if (l < T.nf) {
         const DevFrag F = L.frags[d.frag_base + l];
-        T.f_parent = F.parent; T.f_tors = F.tors; T.f_child = F.child_atom; T.f_a0 = F.a0; T.f_end = F.sub_end;
+        parent = F.parent;
+        T.psi_src = 4 * (7 + max(F.tors, 0)); T.f_child = F.child_atom; T.f_a0 = F.a0; T.f_end = F.sub_end;
         T.ax = F.axis[0]; T.ay = F.axis[1]; T.az = F.axis[2];
-        T.cx = F.xc[0]; T.cy = F.xc[1]; T.cz = F.xc[2];
-    } else {
-        T.f_parent = -1; T.f_tors = -1; T.f_child = 0; T.f_a0 = 0; T.f_end = 0;
-        T.ax = T.ay = T.az = T.cx = T.cy = T.cz = 0.f;
+        T.cx = l == 0 ? d.anchor[0] : F.xc[0];
+        T.cy = l == 0 ? d.anchor[1] : F.xc[1];
+        T.cz = l == 0 ? d.anchor[2] : F.xc[2];
     }
-    T.dof_frag = (l >= 6 && l < 6 + T.nt) ? (int)L.tors_frag[d.tors_base + l - 6] : 0;
+    T.dof_src = (l >= 6 && l < 6 + T.nt) ? 4 * (int)L.tors_frag[d.tors_base + l - 6] : 0;
     {
         // the links do not depend on the pose: jumped once here (a lane
         // with an ancestor takes that ancestor's link after each round)
-        static_assert(kMaxFrag <= 63, "a link holds a fragment index below 63");
-        int anc = (l >= 1 && l < T.nf) ? T.f_parent : -1;
-        T.links = 0;
+        static_assert(kMaxFrag <= 63, "a link holds 4 x a fragment lane in a byte");
+        int anc = (l >= 1 && l < T.nf) ? parent : -1;
+        T.link0 = T.link1 = 0;
         for (int r = 0; r < T.rounds; ++r) {
-            T.links |= (uint64_t)(anc >= 0 ? anc : 63) << (6 * r);
+            const uint32_t src = (uint32_t)(4 * (anc >= 0 ? anc : l)) << (8 * (r & 3));
+            if (r < 4) T.link0 |= src;
+            else T.link1 |= src;
             const int panc = __builtin_amdgcn_ds_bpermute((anc >= 0 ? anc : l) << 2, anc);
             if (anc >= 0) anc = panc;
         }
     }
     T.gpairs = L.pairs + d.pair_base;
     T.gell = L.ell + d.ell_base;
-    {
-        // least pair energy of each class (plain, hydrophobic, hydrogen
-        // bond) over all distances, rounded down; a pair past the cutoff
-        // adds 0, which is above them
-        float lbl = 0.f;
-        for (int p = l; p < T.np; p += kWave) {
-            const uint32_t c = T.gpairs[p] >> 24;
-            lbl += c == 0 ? kPairMin0 : (c == 1 ? kPairMin1 : kPairMin2);
-        }
-        T.lb = wsum(lbl);
-    }
+    T.np0 = d.n_plain; T.np1 = d.n_hyd; T.lb = d.intra_lb;
     if (l == 0) S.pos[S.ma] = make_float4(1e18f, 1e18f, 1e18f, 0.f);
     if (SL) {
         // Pair record, everything the pair loop needs without decoding:
         //   x: LDS byte addresses of both positions (i | j << 16; S.pos opens
-        //      the LDS, so both fit) | class << 30
+        //      the LDS, so both fit)
         //   y, z: LDS byte addresses of the pair's force slots in the rows of
         //         i and of j (slot * row stride + atom)
         //   w: the radius sum 3.4 + 0.1 rk (bits)
@@ -469,19 +493,19 @@ __device__ void stage_ligand(Topo<A, SL>& T, const LigDev& L, int lig, const Lds
         const uint32_t* ps = L.pslot + d.pair_base;
         const uint32_t ns = (uint32_t)T.fs_stride;
         const int nfs = T.ell_w * T.fs_stride;
-        const uint32_t fs0 = lds_addr(S.fs), pos0 = lds_addr(S.pos);
+        const uint32_t fs0 = lds_addr(S.fs), pos0 = S.pos0;
         const int npad = round_up(T.np < 1 ? 1 : T.np, kPairPass);
         for (int p = l; p < npad; p += kWave) {
             uint4 r;
             if (p < T.np) {
                 const uint32_t pk = T.gpairs[p], sl = ps[p];
                 const uint32_t i = pk & 0xff, j = (pk >> 8) & 0xff;
-                r.x = (pos0 + (i << 4)) | (pos0 + (j << 4)) << 16 | ((pk >> 24) << 30);
+                r.x = (pos0 + (i << 4)) | (pos0 + (j << 4)) << 16;
                 r.y = fs0 + (((sl & 0xffff) * ns + i) << 4);
                 r.z = fs0 + (((sl >> 16) * ns + j) << 4);
                 r.w = __float_as_uint(fmaf((float)((pk >> 16) & 7u), 0.1f, 3.4f));
             } else {
-                r.x = pos0 + ((uint32_t)S.ma << 4);
+                r.x = (pos0 + ((uint32_t)S.ma << 4)) | pos0 << 16;
                 r.y = r.z = fs0 + ((uint32_t)nfs << 4);
                 r.w = __float_as_uint(3.4f);
             }
@@ -491,7 +515,9 @@ __device__ void stage_ligand(Topo<A, SL>& T, const LigDev& L, int lig, const Lds
     } else {
         // one atom per lane: pair words up to a whole pass of 64 in LDS; the padding pairs join the far
         // point to atom 0, so they fall outside the cutoff and store c = 0
-        // (which also serves the atom -> pair table's padding entries, p = np)
+        // (which also serves the atom -> pair table's padding entries, p = np).
+        // A word holds 16 i | 16 j << 12 (byte offsets in S.pos) | the
+        // radius-sum code << 24, so that each part is one instruction away.
         if (A == 1) {
             // eight loads per lane in flight before their stores
             const int npad = round_up(T.np + 1, kWave);
@@ -504,7 +530,8 @@ __device__ void stage_ligand(Topo<A, SL>& T, const LigDev& L, int lig, const Lds
                 }
 #pragma unroll
                 for (int q = 0; q < 8; ++q)
-                    if (p0 + q * kWave < npad) S.pw[p0 + q * kWave] = w[q];
+                    if (p0 + q * kWave < npad)
+                        S.pw[p0 + q * kWave] = (w[q] & 0xffu) << 4 | (w[q] & 0xff00u) << 8 | (w[q] & 0xff0000u) << 8;
             }
         }
         if (l == 0) S.cp[T.np] = 0.f;   // not written by the pair loop when np is a multiple of 64
@@ -525,8 +552,13 @@ struct Eval {
 // starts from its local map (the root's pose map, or the rotation by psi
 // about its torsion axis) and composes with its ancestors by pointer
 // doubling; after `rounds` rounds every frame is world-absolute.
+// y_first: the order in which the dock kernels of at most kShortM history pairs
+// sum a line-search trial's frame offsets; every other evaluation starts from
+// the x terms.  The searches are chaotic, so the last bits matter: each
+// evaluation keeps the order it has always had, written out here because the
+// compiler's own choice of fused products changes with the code around it.
 template <int A, bool SL>
-__device__ __forceinline__ void frames(const Topo<A, SL>& T, const Lds& S, const float* pose, float R[9], float b[3])
+__device__ __forceinline__ void frames(const Topo<A, SL>& T, float pose, bool y_first, float R[9], float b[3])
 {
     const int l = lane_id();
     // Local map of every fragment lane, one formula for the root and the
@@ -534,51 +566,57 @@ __device__ __forceinline__ void frames(const Topo<A, SL>& T, const Lds& S, const
     //   root:     unit q = (qw, v): s = 2 qw v, w = sqrt(2) v; p = t, a = anchor
     //   torsion:  angle psi about unit axis u through c: with h = psi / 2,
     //             s = 2 sin h cos h u, w = sqrt(2) sin h u; p = a = c
-    const float qw = pose[3], qx = pose[4], qy = pose[5], qz = pose[6];
-    const float qi = __builtin_amdgcn_rsqf(qw * qw + qx * qx + qy * qy + qz * qz);
+    const float psi = from_lane(T.psi_src, pose);
+    const float t0 = lane_f(pose, 0), t1 = lane_f(pose, 1), t2 = lane_f(pose, 2);
+    const float qw = lane_f(pose, 3), qx = lane_f(pose, 4), qy = lane_f(pose, 5), qz = lane_f(pose, 6);
+    const float qi = __builtin_amdgcn_rsqf(fmaf(qz, qz, fmaf(qy, qy, fmaf(qw, qw, qx * qx))));
     const bool root = l == 0;
     float sh, ch;
-    __sincosf(0.5f * pose[7 + (root ? 0 : T.f_tors)], &sh, &ch);
+    __sincosf(0.5f * psi, &sh, &ch);
     const float ux = root ? qx * qi : T.ax, uy = root ? qy * qi : T.ay, uz = root ? qz * qi : T.az;
     const float k1 = root ? 2.f * qw * qi : 2.f * sh * ch;
     const float k2 = root ? 1.41421356f : 1.41421356f * sh;
     const float sx = k1 * ux, sy = k1 * uy, sz = k1 * uz;
     const float wx = k2 * ux, wy = k2 * uy, wz = k2 * uz;
-    const float c0 = 1.f - (wx * wx + wy * wy + wz * wz);
-    R[0] = c0 + wx * wx; R[1] = wx * wy - sz;  R[2] = wx * wz + sy;
-    R[3] = wy * wx + sz; R[4] = c0 + wy * wy;  R[5] = wy * wz - sx;
-    R[6] = wz * wx - sy; R[7] = wz * wy + sx;  R[8] = c0 + wz * wz;
-    const float px = root ? pose[0] : T.cx, py = root ? pose[1] : T.cy, pz = root ? pose[2] : T.cz;
-    const float ax = root ? T.anc_x : T.cx, ay = root ? T.anc_y : T.cy, az = root ? T.anc_z : T.cz;
-    b[0] = px - (R[0] * ax + R[1] * ay + R[2] * az);
-    b[1] = py - (R[3] * ax + R[4] * ay + R[5] * az);
-    b[2] = pz - (R[6] * ax + R[7] * ay + R[8] * az);
+    const float c0 = 1.f - fmaf(wz, wz, fmaf(wx, wx, wy * wy));
+    R[0] = fmaf(wx, wx, c0);  R[1] = fmaf(wx, wy, -sz); R[2] = fmaf(wx, wz, sy);
+    R[3] = fmaf(wx, wy, sz);  R[4] = fmaf(wy, wy, c0);  R[5] = fmaf(wy, wz, -sx);
+    R[6] = fmaf(wx, wz, -sy); R[7] = fmaf(wy, wz, sx);  R[8] = fmaf(wz, wz, c0);
+    const float px = root ? t0 : T.cx, py = root ? t1 : T.cy, pz = root ? t2 : T.cz;
+    b[0] = px - fmaf(R[2], T.cz, fmaf(R[1], T.cy, R[0] * T.cx));
+    // (x, y) or (y, x): the first product is rounded, the second fused onto it
+    const float f1 = y_first ? R[4] : R[3], f2 = y_first ? R[7] : R[6], fc = y_first ? T.cy : T.cx;
+    const float g1 = y_first ? R[3] : R[4], g2 = y_first ? R[6] : R[7], gc = y_first ? T.cx : T.cy;
+    b[1] = py - fmaf(R[5], T.cz, fmaf(g1, gc, f1 * fc));
+    b[2] = pz - fmaf(R[8], T.cz, fmaf(g2, gc, f2 * fc));
     // pointer doubling across lanes: every round each fragment fetches the
     // partial frame of its ancestor of that round (links jumped at staging)
     // straight from that lane's registers (ds_bpermute, all lanes taking
-    // part), then composes; a lane without an ancestor fetches its own
-    // values and keeps its frame
+    // part), then composes, column by column in place; a lane without an
+    // ancestor fetches its own values and keeps its frame
+    uint32_t link = T.link0;
     for (int r = 0; r < T.rounds; ++r) {
-        const int anc = (int)(T.links >> (6 * r)) & 63;
-        const int src = (anc != 63 ? anc : l) << 2;
+        if (r == 4) link = T.link1;
+        const int src = (int)(link & 0xffu);
+        link >>= 8;
         float P[9], pb[3];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) P[k] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(R[k])));
+        for (int k = 0; k < 9; ++k) P[k] = from_lane(src, R[k]);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) pb[k] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(b[k])));
-        if (anc != 63) {
-            float N[9], nb[3];
+        for (int k = 0; k < 3; ++k) pb[k] = from_lane(src, b[k]);
+        if (src != 4 * l) {
+            auto turn = [&](float& x, float& y, float& z) {
+                const float u = fmaf(P[0], x, P[1] * y), v = fmaf(P[3], x, P[4] * y), w = fmaf(P[6], x, P[7] * y);
+                x = fmaf(P[2], z, u);
+                y = fmaf(P[5], z, v);
+                z = fmaf(P[8], z, w);
+            };
+            turn(R[0], R[3], R[6]);
+            turn(R[1], R[4], R[7]);
+            turn(R[2], R[5], R[8]);
+            turn(b[0], b[1], b[2]);
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    N[3 * i + j] = P[3 * i] * R[j] + P[3 * i + 1] * R[3 + j] + P[3 * i + 2] * R[6 + j];
-                nb[i] = P[3 * i] * b[0] + P[3 * i + 1] * b[1] + P[3 * i + 2] * b[2] + pb[i];
-            }
-#pragma unroll
-            for (int k = 0; k < 9; ++k) R[k] = N[k];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) b[k] = nb[k];
+            for (int k = 0; k < 3; ++k) b[k] += pb[k];
         }
     }
 }
@@ -598,15 +636,15 @@ __device__ __forceinline__ void frames(const Topo<A, SL>& T, const Lds& S, const
 typedef float f3v __attribute__((ext_vector_type(3)));
 constexpr float kLog2e = 1.4426950408889634f;
 
-// One pass of U pairs per lane starting at pair p0 (this lane's first);
+// One pass of U pairs per lane starting at pair c0 (the first lane's; uniform);
 // adds this lane's energy to e and its pairs inside the cutoff to cnt.
 template <int A, bool SL, int U>
-__device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, int p0, float& e, int& cnt,
+__device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, int c0, float& e, int& cnt,
                                           const uint32_t* words = nullptr)
 {
-    const uint32_t pos0 = lds_addr(S.pos);
-    // position addresses; slot addresses; radius sum bits (slots) or
-    // the pair word's upper half, radius-sum code | class << 8 (gather)
+    const int p0 = c0 + lane_id();
+    // position addresses; slot addresses; radius sum bits (slots) or the
+    // radius-sum code (gather)
     uint32_t ai[U], aj[U], ya[U], za[U], rc[U];
     bool v[U];
     float4 xi[U], xj[U];
@@ -615,7 +653,7 @@ __device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, in
         const int p = p0 + u * kWave;
         if (SL) {
             const uint4 w = S.pairs[p];
-            ai[u] = w.x & 0xffffu; aj[u] = w.x >> 16;   // the class sits above bit 29: kept for the test
+            ai[u] = w.x & 0xffffu; aj[u] = w.x >> 16;
             ya[u] = w.y; za[u] = w.z; rc[u] = w.w;
             v[u] = true;
         } else {
@@ -623,23 +661,24 @@ __device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, in
             // pairs; with two atoms per lane the caller brings the words
             // from global memory (a lane past the end holds pair 0 and
             // discards it)
-            uint32_t g;
             if (A == 1) {
-                g = S.pw[p];
+                const uint32_t g = S.pw[p];
                 v[u] = true;
+                ai[u] = S.pos0 + (g & 0xff0u); aj[u] = S.pos0 + ((g >> 12) & 0xfffu);
+                rc[u] = g >> 24;
             } else {
+                const uint32_t g = words[u];
                 v[u] = p < T.np;
-                g = words[u];
+                ai[u] = S.pos0 + ((g & 0xffu) << 4); aj[u] = S.pos0 + ((g >> 4) & 0xff0u);
+                rc[u] = (g >> 16) & 0xffu;
             }
-            ai[u] = pos0 + ((g & 0xffu) << 4); aj[u] = pos0 + (((g >> 8) & 0xffu) << 4);
-            rc[u] = g >> 16;
             ya[u] = za[u] = 0u;
         }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         xi[u] = *(const float4*)lds_ptr<const float4>(ai[u]);
-        xj[u] = *(const float4*)lds_ptr<const float4>(SL ? aj[u] & 0x3fffu : aj[u]);
+        xj[u] = *(const float4*)lds_ptr<const float4>(aj[u]);
     }
     float dx[U], dy[U], dz[U], d[U], en[U], de[U], rinv[U];
     bool in[U];
@@ -653,7 +692,7 @@ __device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, in
         // zeroes the force
         const float r2c = fmaxf(r2, 1e-12f);
         rinv[u] = __builtin_amdgcn_rsqf(r2c);
-        const float rs = SL ? __uint_as_float(rc[u]) : fmaf((float)(rc[u] & 0xffu), 0.1f, 3.4f);
+        const float rs = SL ? __uint_as_float(rc[u]) : fmaf((float)rc[u], 0.1f, 3.4f);
         const float dd = r2c * rinv[u] - rs;
         d[u] = dd;
         // exp(-(d/0.5)^2) and exp(-((d-3)/2)^2), the second exponent
@@ -670,10 +709,11 @@ __device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, in
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         // class 1 (both hydrophobic) adds the hydrophobic term, class 2
-        // (donor with acceptor) the hydrogen-bond term
-        const uint32_t cls = SL ? aj[u] >> 14 : rc[u] >> 8;
-        if (__ballot(cls != 0u)) {
-            const float wy = cls == 1u ? kW4 : 0.f, wz = cls == 2u ? kW5 : 0.f;
+        // (donor with acceptor) the hydrogen-bond term; the classes follow
+        // one another in the pair list
+        if (c0 + (u + 1) * kWave > T.np0 && c0 + u * kWave < T.np) {
+            const int p = p0 + u * kWave;
+            const float wy = p >= T.np0 && p < T.np1 ? kW4 : 0.f, wz = p >= T.np1 ? kW5 : 0.f;
             const float dd = d[u];
             const float hv = fminf(fmaxf(1.5f - dd, 0.f), 1.f);            // 1 below 0.5, 0 above 1.5
             const float bv = fminf(fmaxf(dd * -(1.f / 0.7f), 0.f), 1.f);   // 1 below -0.7, 0 above 0
@@ -717,49 +757,48 @@ __device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, in
 template <int A, bool SL>
 __device__ __forceinline__ float pair_loop(const Topo<A, SL>& T, const Lds& S, int& cnt)
 {
-    const int l = lane_id();
     const int np = T.np;
     float e = 0.f;
-    int p0 = l;
-    if (SL) {
-        for (; p0 - l < np; p0 += kPairPass) pair_pass<A, SL, kPairUnroll>(T, S, p0, e, cnt);
-    } else {
-        if (A > 1) {
-            // two atoms per lane (ligands of 65 to 128 atoms, long pair
-            // lists): whole passes only; the pair words come from global
-            // memory, each pass's loaded during the pass before (a lane past
-            // the end reads pair 0, np >= 1 here, and discards it)
-            uint32_t w[kPairUnroll], nw[kPairUnroll];
-            if (np > 0) {
+    int c0 = 0;
+    if (A > 1) {
+        // two atoms per lane (ligands of 65 to 128 atoms, long pair lists):
+        // whole passes only; the pair words come from global memory, each
+        // pass's loaded during the pass before (a lane past the end reads
+        // pair 0, np >= 1 here, and discards it)
+        const int l = lane_id();
+        uint32_t w[kPairUnroll], nw[kPairUnroll];
+        if (np > 0) {
 #pragma unroll
-                for (int u = 0; u < kPairUnroll; ++u) {
-                    const int p = p0 + u * kWave;
-                    w[u] = T.gpairs[p < np ? p : 0];
-                }
+            for (int u = 0; u < kPairUnroll; ++u) {
+                const int p = l + u * kWave;
+                w[u] = T.gpairs[p < np ? p : 0];
             }
-            for (; p0 - l < np; p0 += kPairPass) {
-#pragma unroll
-                for (int u = 0; u < kPairUnroll; ++u) {
-                    const int p = p0 + kPairPass + u * kWave;
-                    nw[u] = T.gpairs[p < np ? p : 0];
-                }
-                pair_pass<A, SL, kPairUnroll>(T, S, p0, e, cnt, w);
-#pragma unroll
-                for (int u = 0; u < kPairUnroll; ++u) w[u] = nw[u];
-            }
-        } else {
-            for (; p0 - l + kPairPass <= np; p0 += kPairPass) pair_pass<A, SL, kPairUnroll>(T, S, p0, e, cnt);
-            for (; p0 - l + 2 * kWave <= np; p0 += 2 * kWave) pair_pass<A, SL, 2>(T, S, p0, e, cnt);
-            for (; p0 - l < np; p0 += kWave) pair_pass<A, SL, 1>(T, S, p0, e, cnt);
         }
+        for (; c0 < np; c0 += kPairPass) {
+#pragma unroll
+            for (int u = 0; u < kPairUnroll; ++u) {
+                const int p = c0 + l + kPairPass + u * kWave;
+                nw[u] = T.gpairs[p < np ? p : 0];
+            }
+            pair_pass<A, SL, kPairUnroll>(T, S, c0, e, cnt, w);
+#pragma unroll
+            for (int u = 0; u < kPairUnroll; ++u) w[u] = nw[u];
+        }
+        return e;
     }
+    // the slot form, a few waves per SIMD, pays more for another pass's
+    // latency than for one chunk of padding: three chunks take a whole pass
+    const int whole = SL ? kPairPass - kWave : kPairPass;
+    for (; c0 + whole <= np || (SL && c0 + 2 * kWave < np); c0 += kPairPass) pair_pass<A, SL, kPairUnroll>(T, S, c0, e, cnt);
+    for (; c0 + 2 * kWave <= np || (SL && c0 + kWave < np); c0 += 2 * kWave) pair_pass<A, SL, 2>(T, S, c0, e, cnt);
+    for (; c0 < np; c0 += kWave) pair_pass<A, SL, 1>(T, S, c0, e, cnt);
     return e;
 }
 
 // dE/dx_i of the intra term.  LDS tables: the sum of atom i's row of pair
 // forces (independent reads, rows padded to a multiple of four with zeros).
 // Global tables: sum over the pairs holding atom i of c_p (x_i - x_j); an
-// entry holds p in its low half and j's byte offset in S.pos in its high half.
+// entry holds p's byte offset in S.cp in its low half and j's in S.pos in its high half.
 // row loads of the global atom -> pair table issued together by the gather:
 // the table sits in L2, so a row walked one load at a time pays one L2
 // round trip per four entries
@@ -810,7 +849,7 @@ __device__ __forceinline__ void gather_pair_forces(const Topo<A, SL>& T, const L
             float4 xj[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                c[u] = S.cp[e[u] & 0xffff];
+                c[u] = *(const float*)((const char*)S.cp + (e[u] & 0xffff));
                 xj[u] = *(const float4*)((const char*)S.pos + (e[u] >> 16));
             }
 #pragma unroll
@@ -836,20 +875,20 @@ __device__ __forceinline__ float4 atom_position(float4 ref, const Lds& S)
     return make_float4(x, y, z, 0.f);
 }
 
-// Score and tangent gradient of the pose in `pose` (an LDS slot).  Leaves
+// Score and tangent gradient of the pose (entry l in lane l).  Leaves
 // atom positions in S.pos and dE/dx in S.frc.  When the energy exceeds
 // e_limit (a line-search trial that fails the sufficient-decrease test,
 // whose gradient nobody reads) it returns after the energy, with g = 0 and
 // S.frc not written.  use_bound lets such a trial try the intra lower bound
 // before its pair loop.
 template <int A, bool SL>
-__device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, const float* pose,
-                         float e_limit = __builtin_inff(), bool use_bound = true)
+__device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, float pose,
+                         float e_limit = __builtin_inff(), bool use_bound = true, bool y_first = false)
 {
     const int l = lane_id();
     Eval out;
     float R[9], b[3];
-    frames(T, S, pose, R, b);
+    frames(T, pose, y_first, R, b);
     // the world axis of this fragment lane's torsion, the one use of the
     // frame after the atom positions (so R and b need not stay live)
     const float awx = R[0] * T.ax + R[1] * T.ay + R[2] * T.az;
@@ -983,7 +1022,7 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, c
     for (int a = 0; a < A; ++a)
         if (l * A + a < T.n) gather_pair_forces(T, S, l * A + a, X4[a], G[a][0], G[a][1], G[a][2]);
     // per-atom force (inter + intra) and torque about t, blocked scan over atoms
-    const float tx = pose[0], ty = pose[1], tz = pose[2];
+    const float tx = lane_f(pose, 0), ty = lane_f(pose, 1), tz = lane_f(pose, 2);
     float v[A][6];
     float run[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll
@@ -1040,7 +1079,7 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, c
     const int last = T.n - 1;
     float g = 0.f;
     if (l < 6) g = S.pre[l * S.ma + last];
-    else if (l < 6 + T.nt) g = dps[T.dof_frag];
+    else if (l < 6 + T.nt) g = *(const float*)((const char*)dps + T.dof_src);
     out.g = g;
     wave_sync();
     return out;
@@ -1079,40 +1118,34 @@ __device__ Eval evaluate_xyz(const Topo<A, SL>& T, const BoxView& B, const Lds& 
     return out;
 }
 
-// ---------------------------------------------------------------- pose slots
-__device__ __forceinline__ void slot_copy(const Lds& S, int dst, int src, int len)
+// ---------------------------------------------------------------- pose registers
+// the value one lane below / above (whole-wave shifts)
+__device__ __forceinline__ float lane_below(float v) { return dpp0<0x138>(v); }   // wave_shr:1
+__device__ __forceinline__ float lane_above(float v) { return dpp0<0x130>(v); }   // wave_shl:1
+
+// pose entries 3..6 replaced by the quaternion q
+__device__ __forceinline__ float with_quat(float v, const float q[4])
 {
     const int l = lane_id();
-    if (l < len) S.pose[dst * kSlot + l] = S.pose[src * kSlot + l];
-    wave_sync();
+    v = l == 6 ? q[3] : v;
+    v = l == 5 ? q[2] : v;
+    v = l == 4 ? q[1] : v;
+    return l == 3 ? q[0] : v;
 }
 
 // x (+) lam d : t + lam d_t, exp(lam d_theta) q, psi + lam d_psi.  d is the
 // lane-distributed tangent vector.
-__device__ __forceinline__ void retract(const Lds& S, int dst, int src, float d, float lam, int nt)
+__device__ __forceinline__ float retract(float x, float d, float lam)
 {
     const int l = lane_id();
-    const float* x = S.pose + src * kSlot;
-    float* o = S.pose + dst * kSlot;
-    const int np = 7 + nt;
-    // one LDS read: lane k holds pose entry k; the quaternion comes from
-    // lanes 3..6 by readlane (dst and src are distinct slots)
-    const float xv = l < np ? x[l] : 0.f;
     const float th0 = lane_f(d, 3) * lam, th1 = lane_f(d, 4) * lam, th2 = lane_f(d, 5) * lam;
-    float dq[4], q[4] = {lane_f(xv, 3), lane_f(xv, 4), lane_f(xv, 5), lane_f(xv, 6)}, nq[4];
+    float dq[4], q[4] = {lane_f(x, 3), lane_f(x, 4), lane_f(x, 5), lane_f(x, 6)}, nq[4];
     rotvec_quat(th0, th1, th2, dq);
     quat_mul(dq, q, nq);
     quat_normalize(nq);
     // pose entries 0..2 move by tangent lanes 0..2, entry k >= 7 (a torsion)
-    // by tangent lane k - 1, brought over by a whole-wave shift (DPP wave_shr:1)
-    const float dprev = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(d), 0x138, 0xF, 0xF, false));
-    float v = xv + lam * (l < 3 ? d : dprev);
-    v = l == 6 ? nq[3] : v;
-    v = l == 5 ? nq[2] : v;
-    v = l == 4 ? nq[1] : v;
-    v = l == 3 ? nq[0] : v;
-    if (l < np) o[l] = v;
-    wave_sync();
+    // by tangent lane k - 1
+    return with_quat(fmaf(lam, l < 3 ? d : lane_below(d), x), nq);
 }
 
 // ---------------------------------------------------------------- RILC-BFGS
@@ -1121,6 +1154,7 @@ constexpr int kShortM = 5;   // the dock kernel is also built for at most this m
                              // lives in registers, and room for 8 pairs cost the shift and copies of 3 more
 
 struct BfgsOut {
+    float x;          // this lane's pose entry at the result
     float f;
     float g;          // this lane's tangent gradient component at the result
     int evals;
@@ -1132,39 +1166,39 @@ struct BfgsOut {
 };
 
 // The neighbour of a mutated pose for the first-order consistency check:
-// the current pose (LDS slot SLOT_CUR), its energy and this lane's tangent
+// the current pose x, its energy and this lane's tangent
 // gradient component, and the tangent coordinates [p_lo, p_hi) the
 // mutation moved.
 struct CheckIn {
-    float f, g;
+    float x, f, g;
     int p_lo, p_hi;
 };
 
 __device__ __forceinline__ float fsgn(float v) { return (float)((v > 0.f) - (v < 0.f)); }
 
-// Eqs. qvina_eq_4 and qvina_eq_5 for the pose in `x` (energy fx, this
+// Eqs. qvina_eq_4 and qvina_eq_5 for the pose x (energy fx, this
 // lane's gradient gx) against its neighbour: true (optimise) when in some
 // tested coordinate the derivative changes sign between the two poses or
 // disagrees with the secant slope.  Tangent differences: translation, the
 // rotation vector of q_x conj(q_cur) (only its sign is used), torsions
 // wrapped to (-pi, pi].
-__device__ __forceinline__ bool consistency_passes(const Lds& S, const float* x, float fx, float gx, const CheckIn& ck)
+__device__ __forceinline__ bool consistency_passes(float x, float fx, float gx, const CheckIn& ck)
 {
     const int l = lane_id();
-    const float* y = S.pose + SLOT_CUR * kSlot;
+    const float y = ck.x, xa = lane_above(x), ya = lane_above(y);
     float dl = 0.f;
     if (l < 3) {
-        dl = x[l] - y[l];
+        dl = x - y;
     } else if (l < 6) {
-        const float qx[4] = {x[3], x[4], x[5], x[6]};
-        const float cy[4] = {y[3], -y[4], -y[5], -y[6]};
+        const float qx[4] = {lane_f(x, 3), lane_f(x, 4), lane_f(x, 5), lane_f(x, 6)};
+        const float cy[4] = {lane_f(y, 3), -lane_f(y, 4), -lane_f(y, 5), -lane_f(y, 6)};
         float qd[4];
         quat_mul(qx, cy, qd);
         const float v = l == 3 ? qd[1] : (l == 4 ? qd[2] : qd[3]);
         dl = qd[0] < 0.f ? -v : v;
     } else if (l + 1 < kSlot) {
         const float kPi = 3.14159265358979f, k2Pi = 6.28318530717959f;
-        float d = x[l + 1] - y[l + 1];
+        float d = xa - ya;
         d -= k2Pi * floorf((d + kPi) * (1.f / k2Pi));
         dl = d == -kPi ? kPi : d;
     }
@@ -1174,132 +1208,112 @@ __device__ __forceinline__ bool consistency_passes(const Lds& S, const float* x,
     return __ballot(in && hold) != 0;
 }
 
-// Minimises from the pose in SLOT_X; the result is left in SLOT_X.  Written
-// as one loop around a single evaluation (the first at x0, then one per
-// line-search trial) so the kernel carries one copy of the evaluation code.
+// Minimises from the pose x (entry l in lane l); the result is out.x.  The
+// start's evaluation and the line search's are two copies of the evaluation
+// code; the line search is a loop of its own, so that the state of the outer
+// iteration (the history above all) stays in its registers across the trials.
 template <int A, bool SL, int MM = kMaxM>
 __device__ BfgsOut bfgs(const Topo<A, SL>& T, const BoxView& B, const Lds& S, const SearchParams& P, int max_iter,
-                        bool check = false, CheckIn ck = CheckIn{0.f, 0.f, 0, 0})
+                        float x, bool check = false, CheckIn ck = CheckIn{0.f, 0.f, 0.f, 0, 0})
 {
     static_assert(MM >= 1 && MM <= kMaxM, "history capacity");
     const int l = lane_id();
     const int nd = 6 + T.nt;
     const bool act = l < nd;
     BfgsOut out;
-    out.evals = 0;
-    out.grads = 0;
+    const Eval e0 = evaluate(T, B, S, x);
+    float f = e0.e, g = act ? e0.g : 0.f;
+    out.evals = out.grads = 1;
     out.bounded = 0;
-    out.pairs = 0;
-    out.skipped = false;
-    out.outside0 = false;
+    out.pairs = e0.pairs_in;
+    out.outside0 = e0.outside;
+    out.skipped = check && !consistency_passes(x, f, g, ck);
     float Sh[MM], Yh[MM], rh[MM];
 #pragma unroll
     for (int h = 0; h < MM; ++h) { Sh[h] = 0.f; Yh[h] = 0.f; rh[h] = 0.f; }
-    int hn = 0, it = 0, tr = 0;
+    int hn = 0;
     const int m = P.m;
-    float f = 0.f, g = 0.f, d = 0.f, gd = 0.f, gn = 0.f;
-    float lo = 0.f, lam = 1.f, beta = 0.f, fa = 0.f, ga = 0.f;
     float sy_new = 0.f, yy_new = 1.f;   // s.y and y.y of the newest stored pair (the H0 scale)
-    bool beta_inf = true, initial = true;
-    while (true) {
-        // a trial above the sufficient-decrease bound needs no gradient.  The
-        // intra bound decides an iteration's first trial (the full step) less
-        // often than the later ones, and with one atom per lane trying it costs
-        // the corner loads their cover by the pair loop: that form tries it
-        // once a trial of the iteration has failed, and while no history pair
-        // is stored, when the full step is the unscaled gradient step
-        const float armijo = initial ? __builtin_inff() : f + P.rho * lam * gd;
-        const Eval ev = evaluate(T, B, S, S.pose + (initial ? SLOT_X : SLOT_XT) * kSlot, armijo,
-                                 !(P.flags & kDockNoIntraBound) && (A > 1 || tr > 0 || hn == 0));
-        ++out.evals;
-        out.grads += ev.e > armijo ? 0 : 1;
-        out.bounded += ev.bounded ? 1 : 0;
-        out.pairs += ev.pairs_in;
-        const float ft = ev.e, gt = act ? ev.g : 0.f;
-        bool begin = false;
-        if (initial) {
-            f = ft; g = gt; initial = false; begin = true;
-            out.outside0 = ev.outside;
-            if (check && !consistency_passes(S, S.pose + SLOT_X * kSlot, ft, gt, ck)) {
-                out.skipped = true;
-                break;
+    for (int it = 0; it < max_iter && !out.skipped; ++it) {
+        const float gn = __builtin_amdgcn_sqrtf(wdot_n(g, g, nd));
+        if (gn <= P.eps_g) break;                 // Eq. qvina_eq_12
+        // two-loop recursion: d = -H g (d = -g with no pairs, Eq. qvina_eq_6)
+        float q = g, al[MM];
+#pragma unroll
+        for (int h = MM - 1; h >= 0; --h) {
+            al[h] = 0.f;
+            if (h < hn) {
+                al[h] = rh[h] * wdot_n(Sh[h], q, nd);
+                q = fmaf(-Yh[h], al[h], q);
             }
-        } else {
-            // Lewis-Overton trial at step lam (Eqs. qvina_eq_7 and qvina_eq_8)
+        }
+        if (hn > 0) q *= sy_new * __builtin_amdgcn_rcpf(yy_new);
+#pragma unroll
+        for (int h = 0; h < MM; ++h) {
+            if (h < hn) {
+                const float bb = rh[h] * wdot_n(Yh[h], q, nd);
+                q = fmaf(Sh[h], al[h] - bb, q);
+            }
+        }
+        const float d = -q;
+        const float gd = wdot_n(g, d, nd);
+        if (!(gd < 0.f)) break;                   // not a descent direction
+        // Lewis-Overton search (Eqs. qvina_eq_7 and qvina_eq_8): lam between
+        // lo, the largest step at or below the sufficient-decrease bound, and
+        // beta, the least above it
+        float lo = 0.f, lam = 1.f, beta = 0.f, fn = 0.f, gnw = 0.f, xn = x, lam_ok = 0.f;
+        bool beta_inf = true;
+        for (int tr = 0;; ) {
+            const float xt = retract(x, d, lam);
+            // a trial above the sufficient-decrease bound needs no gradient.  The
+            // intra bound decides an iteration's first trial (the full step) less
+            // often than the later ones, and with one atom per lane trying it costs
+            // the corner loads their cover by the pair loop: that form tries it
+            // once a trial of the iteration has failed, and while no history pair
+            // is stored, when the full step is the unscaled gradient step
+            const float armijo = fmaf(P.rho * lam, gd, f);
+            const Eval ev = evaluate(T, B, S, xt, armijo, !(P.flags & kDockNoIntraBound) && (A > 1 || tr > 0 || hn == 0),
+                                     MM <= kShortM);
+            const float ft = ev.e, gt = act ? ev.g : 0.f;
+            const bool above = ft > armijo;
+            ++out.evals;
+            out.grads += above ? 0 : 1;
+            out.bounded += ev.bounded ? 1 : 0;
+            out.pairs += ev.pairs_in;
             bool accepted = false;
-            if (ft > armijo) {
+            if (above) {
                 beta = lam; beta_inf = false;
-            } else if (wsum_n(gt * d, nd) < P.sigma * gd) {
-                lo = lam;
-                slot_copy(S, SLOT_XA, SLOT_XT, 7 + T.nt);
-                fa = ft; ga = gt;
             } else {
-                accepted = true;
+                // kept as the fallback too, should the trials run out
+                accepted = !(wdot_n(gt, d, nd) < P.sigma * gd);
+                lo = lam_ok = lam;
+                fn = ft; gnw = gt; xn = xt;
             }
-            float lam_ok = lam, fn = ft, gnw = gt;
-            if (!accepted) {
-                ++tr;
-                if (tr < P.ls_max) {
-                    lam = beta_inf ? 2.f * lam : 0.5f * (lo + beta);
-                    retract(S, SLOT_XT, SLOT_X, d, lam, T.nt);
-                    continue;
-                }
-                if (!(lo > 0.f)) break;
-                lam_ok = lo;
-                slot_copy(S, SLOT_XT, SLOT_XA, 7 + T.nt);
-                fn = fa; gnw = ga;
-            }
-            // s = lam d, y = g+ - g; cautious update (Eqs. qvina_eq_10, qvina_eq_11)
-            const float sv = lam_ok * d, yv = gnw - g;
-            const float ys = wsum_n(yv * sv, nd), ss = wsum_n(sv * sv, nd), yy = wsum_n(yv * yv, nd);
-            if (ys * __builtin_amdgcn_rcpf(ss) > P.eps_c * gn) {
-                sy_new = ys;
-                yy_new = yy;
-                if (hn == m) {
-#pragma unroll
-                    for (int h = 0; h < MM - 1; ++h) { Sh[h] = Sh[h + 1]; Yh[h] = Yh[h + 1]; rh[h] = rh[h + 1]; }
-                    --hn;
-                }
-#pragma unroll
-                for (int h = 0; h < MM; ++h)
-                    if (h == hn) { Sh[h] = sv; Yh[h] = yv; rh[h] = __builtin_amdgcn_rcpf(ys); }
-                ++hn;
-            }
-            slot_copy(S, SLOT_X, SLOT_XT, 7 + T.nt);   // Eq. qvina_eq_9
-            f = fn;
-            g = gnw;
-            ++it;
-            begin = true;
+            if (accepted || ++tr >= P.ls_max) break;
+            lam = beta_inf ? 2.f * lam : 0.5f * (lo + beta);
         }
-        if (begin) {
-            if (it >= max_iter) break;
-            gn = __builtin_amdgcn_sqrtf(wsum_n(g * g, nd));
-            if (gn <= P.eps_g) break;                 // Eq. qvina_eq_12
-            // two-loop recursion: d = -H g (d = -g with no pairs, Eq. qvina_eq_6)
-            float q = g, al[MM];
+        if (!(lam_ok > 0.f)) break;
+        // s = lam d, y = g+ - g; cautious update (Eqs. qvina_eq_10, qvina_eq_11)
+        const float sv = lam_ok * d, yv = gnw - g;
+        const float ys = wdot_n(yv, sv, nd), ss = wdot_n(sv, sv, nd), yy = wdot_n(yv, yv, nd);
+        if (ys * __builtin_amdgcn_rcpf(ss) > P.eps_c * gn) {
+            sy_new = ys;
+            yy_new = yy;
+            if (hn == m) {
 #pragma unroll
-            for (int h = MM - 1; h >= 0; --h) {
-                al[h] = 0.f;
-                if (h < hn) {
-                    al[h] = rh[h] * wsum_n(Sh[h] * q, nd);
-                    q -= al[h] * Yh[h];
-                }
+                for (int h = 0; h < MM - 1; ++h) { Sh[h] = Sh[h + 1]; Yh[h] = Yh[h + 1]; rh[h] = rh[h + 1]; }
+                --hn;
             }
-            if (hn > 0) q *= sy_new * __builtin_amdgcn_rcpf(yy_new);
 #pragma unroll
-            for (int h = 0; h < MM; ++h) {
-                if (h < hn) {
-                    const float bb = rh[h] * wsum_n(Yh[h] * q, nd);
-                    q += Sh[h] * (al[h] - bb);
-                }
-            }
-            d = -q;
-            gd = wsum_n(g * d, nd);
-            if (!(gd < 0.f)) break;                   // not a descent direction
-            lo = 0.f; lam = 1.f; beta = 0.f; beta_inf = true; tr = 0;
-            retract(S, SLOT_XT, SLOT_X, d, lam, T.nt);
+            for (int h = 0; h < MM; ++h)
+                if (h == hn) { Sh[h] = sv; Yh[h] = yv; rh[h] = __builtin_amdgcn_rcpf(ys); }
+            ++hn;
         }
+        x = xn;   // Eq. qvina_eq_9
+        f = fn;
+        g = gnw;
     }
+    out.x = x;
     out.f = f;
     out.g = g;
     return out;
@@ -1307,6 +1321,7 @@ __device__ BfgsOut bfgs(const Topo<A, SL>& T, const BoxView& B, const Lds& S, co
 
 // ---------------------------------------------------------------- Monte Carlo
 struct ChainOut {
+    float best_x;                  // this lane's entry of the best pose
     float best_e;
     int64_t evals, grads, bounded, pairs;   // pairs: this lane's share
     int status;                    // PV_JOB_BUDGET | PV_JOB_OUTSIDE bits
@@ -1315,8 +1330,7 @@ struct ChainOut {
 constexpr int kStatusBudget = 2, kStatusOutside = 4;   // the PV_JOB_* bits of the ABI
 
 template <int A, bool SL>
-__device__ void init_pose(const Topo<A, SL>& T, const BoxView& B, const Lds& S, int slot, uint64_t seed, int job,
-                          int chain)
+__device__ float init_pose(const Topo<A, SL>& T, const BoxView& B, uint64_t seed, int job, int chain)
 {
     const int l = lane_id();
     // lane l draws uniform l (block l/4, word l%4) of step 0
@@ -1326,24 +1340,22 @@ __device__ void init_pose(const Topo<A, SL>& T, const BoxView& B, const Lds& S, 
     float sa, ca, sb, cb;
     sincosf(2.f * kPi * u4, &sa, &ca);
     sincosf(2.f * kPi * u5, &sb, &cb);
-    float* o = S.pose + slot * kSlot;
-    if (l == 0) o[0] = B.ox + u * B.ex;
-    if (l == 1) o[1] = B.oy + u * B.ey;
-    if (l == 2) o[2] = B.oz + u * B.ez;
-    if (l == 3) o[3] = s2 * cb;
-    if (l == 4) o[4] = s1 * sa;
-    if (l == 5) o[5] = s1 * ca;
-    if (l == 6) o[6] = s2 * sb;
-    if (l >= 6 && l < 6 + T.nt) o[l + 1] = -kPi + 2.f * kPi * u;
-    wave_sync();
+    // entry k >= 7 takes uniform k - 1
+    const float w = lane_below(u);
+    float x = l >= 7 && l < 7 + T.nt ? -kPi + 2.f * kPi * w : 0.f;
+    if (l == 0) x = B.ox + u * B.ex;
+    if (l == 1) x = B.oy + u * B.ey;
+    if (l == 2) x = B.oz + u * B.ez;
+    const float q[4] = {s2 * cb, s1 * sa, s1 * ca, s2 * sb};
+    return with_quat(x, q);
 }
 
-// Mutation of one POT entity (Eq. qvina_eq_2) from the 8 words w of the step.
+// The pose x with one POT entity mutated (Eq. qvina_eq_2) from the 8 words w
+// of the step.
 template <int A, bool SL>
-__device__ void mutate(const Topo<A, SL>& T, const Lds& S, int slot, const SearchParams& P, const uint64_t w[8])
+__device__ float mutate(const Topo<A, SL>& T, float x, const SearchParams& P, const uint64_t w[8])
 {
     const int l = lane_id();
-    float* x = S.pose + slot * kSlot;
     const uint64_t n_ent = (uint64_t)(2 + T.nt);
     const int ent = (int)(((w[0] >> 32) * n_ent) >> 32);
     const float u1 = u01(w[1]), u2 = u01(w[2]), u3 = u01(w[3]), u4 = u01(w[4]);
@@ -1357,27 +1369,21 @@ __device__ void mutate(const Topo<A, SL>& T, const Lds& S, int slot, const Searc
     float dx = 0.f, dy = 0.f, dz = 1.f;
     if (vn2 > 0.f) { const float inv = 1.f / sqrtf(vn2); dx = vx * inv; dy = vy * inv; dz = vz * inv; }
     const float rad = cbrtf(ur);
-    wave_sync();
     if (ent == 0) {
         const float a = P.pos_amp * rad;
-        if (l == 0) x[0] += a * dx;
-        if (l == 1) x[1] += a * dy;
-        if (l == 2) x[2] += a * dz;
+        const float mv = l == 0 ? dx : (l == 1 ? dy : dz);
+        if (l < 3) x += a * mv;
     } else if (ent == 1) {
         const float amp = P.rot_amp * T.rot_scale * rad;
-        float dq[4], q[4] = {x[3], x[4], x[5], x[6]}, nq[4];
+        float dq[4], q[4] = {lane_f(x, 3), lane_f(x, 4), lane_f(x, 5), lane_f(x, 6)}, nq[4];
         rotvec_quat(amp * dx, amp * dy, amp * dz, dq);
         quat_mul(dq, q, nq);
         quat_normalize(nq);
-        wave_sync();
-        if (l == 3) x[3] = nq[0];
-        if (l == 4) x[4] = nq[1];
-        if (l == 5) x[5] = nq[2];
-        if (l == 6) x[6] = nq[3];
+        x = with_quat(x, nq);
     } else {
-        if (l == 7 + (ent - 2)) x[l] = -kPi + 2.f * kPi * ua;
+        if (l == 7 + (ent - 2)) x = -kPi + 2.f * kPi * ua;
     }
-    wave_sync();
+    return x;
 }
 
 // Wave priority from the chain's predicted remaining work: its evaluations
@@ -1405,9 +1411,10 @@ __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& 
     out.bounded = 0;
     out.pairs = 0;
     out.status = 0;
-    init_pose(T, B, S, SLOT_X, P.seed, job, chain);
+    float x = init_pose(T, B, P.seed, job, chain), best = x;
     float e_cur = 0.f, e_best = 0.f, um = 0.f;
-    CheckIn ck;            // the current pose as the consistency check's neighbour
+    CheckIn ck;            // the current pose, also the consistency check's neighbour
+    ck.x = x;
     ck.g = 0.f;
     ck.p_lo = ck.p_hi = 0;
     // 0 initial pose, 1 step optimisation, 2 refinement, 3 the closing
@@ -1416,7 +1423,7 @@ __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& 
     while (true) {
         const int iters = mode == 0 || mode == 3 ? 0 : (mode == 1 ? P.max_iter : P.refine_max_iter);
         ck.f = e_cur;
-        const BfgsOut bo = bfgs<A, SL, MM>(T, B, S, P, iters, mode == 1 && P.consistency, ck);
+        const BfgsOut bo = bfgs<A, SL, MM>(T, B, S, P, iters, x, mode == 1 && P.consistency, ck);
         if (mode == 3) {
             if (bo.outside0) out.status |= kStatusOutside;
             break;
@@ -1429,21 +1436,19 @@ __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& 
         if (mode == 0) {
             e_cur = e_best = bo.f;
             ck.g = bo.g;
-            slot_copy(S, SLOT_CUR, SLOT_X, 7 + T.nt);
-            slot_copy(S, SLOT_BEST, SLOT_X, 7 + T.nt);
+            ck.x = best = bo.x;
         } else if (mode == 1) {
             if (!bo.skipped) {
                 const float e_o = bo.f;
                 if (e_o < e_cur || um < __expf((e_cur - e_o) / P.temperature)) {   // Eq. qvina_eq_13
-                    slot_copy(S, SLOT_CUR, SLOT_X, 7 + T.nt);
+                    ck.x = bo.x;
                     e_cur = e_o;
                     ck.g = bo.g;
                 }
-                if (e_o < e_best) { mode = 2; next = false; }
+                if (e_o < e_best) { mode = 2; next = false; x = bo.x; }
             }
         } else {
-            slot_copy(S, SLOT_BEST, SLOT_X, 7 + T.nt);
-            slot_copy(S, SLOT_CUR, SLOT_X, 7 + T.nt);
+            ck.x = best = bo.x;
             e_best = bo.f;
             e_cur = bo.f;
             ck.g = bo.g;
@@ -1452,7 +1457,7 @@ __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& 
         const bool spent = P.max_evals > 0 && out.evals >= P.max_evals;
         if (spent) out.status |= kStatusBudget;
         if (s >= P.steps || spent) {
-            slot_copy(S, SLOT_X, SLOT_BEST, 7 + T.nt);
+            x = best;
             mode = 3;
             continue;
         }
@@ -1470,13 +1475,13 @@ __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& 
         const int ent = (int)(((w[0] >> 32) * (uint64_t)(2 + T.nt)) >> 32);
         ck.p_lo = ent == 0 ? 0 : (ent == 1 ? 3 : 4 + ent);
         ck.p_hi = ent <= 1 ? ck.p_lo + 3 : ck.p_lo + 1;
-        slot_copy(S, SLOT_X, SLOT_CUR, 7 + T.nt);
-        mutate(T, S, SLOT_X, P, w);
+        x = mutate(T, ck.x, P, w);
         ++s;
         mode = 1;
         chain_priority(out.evals, s, P.steps);
     }
     __builtin_amdgcn_s_setprio(0);
+    out.best_x = best;
     out.best_e = e_best;
     return out;
 }
@@ -1516,7 +1521,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 
         const int64_t pairs = wsum_i64(co.pairs);
         const int64_t ci = (int64_t)job * chains + chain;
         if (a.chain_best_dof && l < a.dof_stride)
-            a.chain_best_dof[ci * a.dof_stride + l] = l < 7 + T.nt ? S.pose[SLOT_BEST * kSlot + l] : 0.f;
+            a.chain_best_dof[ci * a.dof_stride + l] = l < 7 + T.nt ? co.best_x : 0.f;
         if (l == 0) {
             if (a.chain_best_e) a.chain_best_e[ci] = co.best_e;
             if (a.chain_evals) a.chain_evals[ci] = co.evals;
@@ -1638,9 +1643,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(A == 1 && !S
         const int16_t* perm = a.l.perm + a.l.ligs[lig].atom_base;
         Eval ev;
         if (!a.from_xyz) {
-            if (l < 7 + T.nt) S.pose[SLOT_X * kSlot + l] = dof_l;
-            wave_sync();
-            ev = evaluate(T, B, S, S.pose + SLOT_X * kSlot);
+            ev = evaluate(T, B, S, dof_l);
         } else {
             for (int i = l; i < T.n; i += kWave) {
                 const float* src = a.dof + ((int64_t)pose * a.xyz_stride + perm[i]) * 3;
@@ -1653,10 +1656,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(A == 1 && !S
         if (a.e_parts && l < 2) a.e_parts[2 * (int64_t)pose + l] = l == 0 ? ev.e_inter : ev.e_intra;
         if (a.grad_dof && !a.from_xyz) {
             // dE/dt, dE/d(raw q) = 2 ((0, torque) (x) q)/|p|, dE/dpsi
-            const float* x = S.pose + SLOT_X * kSlot;
             const float tq0 = lane_f(ev.g, 3), tq1 = lane_f(ev.g, 4), tq2 = lane_f(ev.g, 5);
             const float dpsi = __shfl(ev.g, l - 1 < 0 ? 0 : (l - 1 > 63 ? 63 : l - 1));
-            float p[4] = {x[3], x[4], x[5], x[6]};
+            float p[4] = {lane_f(dof_l, 3), lane_f(dof_l, 4), lane_f(dof_l, 5), lane_f(dof_l, 6)};
             const float pn = sqrtf(p[0] * p[0] + p[1] * p[1] + p[2] * p[2] + p[3] * p[3]);
             float qh[4] = {p[0] / pn, p[1] / pn, p[2] / pn, p[3] / pn};
             float t4[4] = {0.f, tq0, tq1, tq2}, gq[4];
@@ -1713,10 +1715,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 
         float q0 = lane_f(v, 3), q1 = lane_f(v, 4), q2 = lane_f(v, 5), q3 = lane_f(v, 6);
         const float qn = rsqrtf(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
         if (l >= 3 && l < 7) v *= qn;
-        if (l < 7 + T.nt) S.pose[SLOT_X * kSlot + l] = v;
-        wave_sync();
-        BfgsOut bo = bfgs(T, B, S, a.sp, a.sp.max_iter);
-        if (l < a.dof_stride) a.dof_out[(int64_t)pose * a.dof_stride + l] = l < 7 + T.nt ? S.pose[SLOT_X * kSlot + l] : 0.f;
+        const BfgsOut bo = bfgs(T, B, S, a.sp, a.sp.max_iter, v);
+        if (l < a.dof_stride) a.dof_out[(int64_t)pose * a.dof_stride + l] = l < 7 + T.nt ? bo.x : 0.f;
         if (l == 0) {
             if (a.energy) a.energy[pose] = bo.f;
             if (a.n_evals) a.n_evals[pose] = bo.evals;
@@ -1726,13 +1726,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 
 }
 
 // ---------------------------------------------------------------- output stage
-// Atom positions of the pose in `pose` (an LDS slot) into S.pos.
+// Atom positions of the pose (entry l in lane l) into S.pos.
 template <int A, bool SL>
-__device__ void pose_positions(const Topo<A, SL>& T, const Lds& S, const float* pose)
+__device__ void pose_positions(const Topo<A, SL>& T, const Lds& S, float pose)
 {
     const int l = lane_id();
     float R[9], b[3];
-    frames(T, S, pose, R, b);
+    frames(T, pose, false, R, b);
     if (l < T.nf) {
         float* fr = S.frame + 12 * l;
 #pragma unroll
@@ -1802,7 +1802,8 @@ __global__ __launch_bounds__(kWave * kOutWaves) void output_kernel(OutputArgs a)
     extern __shared__ __align__(16) char smem[];
     const int W = (int)blockDim.y, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
     const int one = lds_bytes(a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOutput, A, false));
-    const Lds S = carve(smem + wv * one, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOutput, A, false));
+    Lds S = carve(smem + wv * one, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOutput, A, false));
+    S.pos0 = lds_addr(S.pos);
     char* ext = smem + W * one;
     const int ma = S.ma, M = a.modes, C = a.chains;
     int* order = (int*)ext;     ext += round_up(C, 4) * 4;
@@ -1812,10 +1813,11 @@ __global__ __launch_bounds__(kWave * kOutWaves) void output_kernel(OutputArgs a)
     float* ra = (float*)ext;    ext += round_up(M, 4) * 4;
     int* kc = (int*)ext;        ext += round_up(M, 4) * 4;
     int* fo = (int*)ext;        ext += round_up(M, 4) * 4;
-    uint32_t* conf = (uint32_t*)ext;   // conflict masks of the final filter
-    // and of a clustering batch, in a pose slot of the first wave that the output stage does not use otherwise
-    uint32_t* flags = (uint32_t*)((float*)(smem + ((char*)S.pose - S.base)) + SLOT_CUR * kSlot);
-    static_assert(kOutWaves + 1 <= kSlot, "room for the conflict masks");
+    // conflict masks of the final filter; before it, the next pose to refine
+    uint32_t* conf = (uint32_t*)ext;
+    // conflict masks of a clustering batch, in the first wave's scan area (no evaluation runs meanwhile)
+    uint32_t* flags = (uint32_t*)(smem + ((char*)S.pre - S.base));
+    static_assert(kOutWaves <= 6 * 4, "the scan area holds 6 x 4 words at least");
     constexpr uint32_t kStands = 0x80000000u;   // a pose of the batch that no kept pose excludes
     const int l = lane_id(), tid = wv * kWave + l, nthr = W * kWave;
     const int job = blockIdx.x;
@@ -1826,7 +1828,6 @@ __global__ __launch_bounds__(kWave * kOutWaves) void output_kernel(OutputArgs a)
     const BoxView B = box_view(a.g, jb.y);
     const float* ce = a.chain_e + (int64_t)job * C;
     const float cut2n = a.rmsd_cut * a.rmsd_cut * (float)T.n;
-    float* x = S.pose + SLOT_X * kSlot;
     // 1. chains in ascending energy (rank of each chain by counting)
     for (int c = tid; c < C; c += nthr) {
         const float ec = ce[c];
@@ -1835,7 +1836,7 @@ __global__ __launch_bounds__(kWave * kOutWaves) void output_kernel(OutputArgs a)
         for (int c2 = 0; c2 < C; ++c2) rank += precedes(ce[c2], c2, ec, c) ? 1 : 0;
         order[rank] = c;
     }
-    if (tid == 0) flags[kOutWaves] = 0;   // the next pose to refine
+    if (tid == 0) conf[0] = 0;
     __syncthreads();
     // 2. greedy clustering in that order, W poses at a time
     int nk = 0;
@@ -1844,9 +1845,7 @@ __global__ __launch_bounds__(kWave * kOutWaves) void output_kernel(OutputArgs a)
         bool stands = r < C;
         if (stands) {
             const float* src = a.chain_dof + ((int64_t)job * C + order[r]) * a.in_stride;
-            if (l < 7 + T.nt) x[l] = src[l];
-            wave_sync();
-            pose_positions(T, S, x);
+            pose_positions(T, S, l < 7 + T.nt ? src[l] : 0.f);
             for (int q = 0; q < nk && stands; ++q) stands = !(sq_dev(T, S, rep + q * ma) < cut2n);
         }
         __syncthreads();   // every wave's positions are in place
@@ -1875,22 +1874,18 @@ __global__ __launch_bounds__(kWave * kOutWaves) void output_kernel(OutputArgs a)
     // 3. refine and rescore every kept pose, each wave the next one when it is free
     while (true) {
         uint32_t v0 = 0;
-        if (l == 0) v0 = atomicAdd(&flags[kOutWaves], 1u);
+        if (l == 0) v0 = atomicAdd(&conf[0], 1u);
         const int q = lane_i((int)v0, 0);
         if (q >= nk) break;
         const float* src = a.chain_dof + ((int64_t)job * C + kc[q]) * a.in_stride;
-        if (l < 7 + T.nt) x[l] = src[l];
-        wave_sync();
-        if (a.refine_max_iter > 0) bfgs(T, B, S, a.sp, a.refine_max_iter);
+        float v = l < 7 + T.nt ? src[l] : 0.f;
+        if (a.refine_max_iter > 0) v = bfgs(T, B, S, a.sp, a.refine_max_iter, v).x;
         // a unit quaternion, then the rescoring evaluation
-        float v = l < 7 + T.nt ? x[l] : 0.f;
+        if (l >= 7 + T.nt) v = 0.f;
         const float q0 = lane_f(v, 3), q1 = lane_f(v, 4), q2 = lane_f(v, 5), q3 = lane_f(v, 6);
         const float qn = 1.f / sqrtf(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
         if (l >= 3 && l < 7) v *= qn;
-        wave_sync();
-        if (l < 7 + T.nt) x[l] = v;
-        wave_sync();
-        const Eval ev = evaluate(T, B, S, x);
+        const Eval ev = evaluate(T, B, S, v);
 #pragma unroll
         for (int aa = 0; aa < A; ++aa) {
             const int i = l * A + aa;

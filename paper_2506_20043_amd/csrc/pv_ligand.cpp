@@ -235,14 +235,30 @@ int build_ligand_model(int n, const float* xyz, const uint8_t* type, int nb, con
         M.pairs.push_back((uint32_t)i | ((uint32_t)j << 8) | ((uint32_t)rk << 16) |
                           ((uint32_t)cls(pl[idx]) << 24));
     }
+    // ends of the classes in the list, and a lower bound of the intra energy:
+    // the sum of every pair's class's least value (a pair past the cutoff adds
+    // 0, which is above them), summed as a wave sums it: 64 lanes over the
+    // pairs, then pairwise
+    {
+        float lane[64] = {};
+        for (int q = 0; q < P; ++q) {
+            const uint32_t c = M.pairs[q] >> 24;
+            lane[q % 64] += least_pair_energy(c);
+            M.n_plain += c == 0;
+            M.n_hyd += c <= 1;
+        }
+        for (int w = 1; w < 64; w *= 2)
+            for (int a = 0; a + w < 64; a += 2 * w) lane[a] += lane[a + w];
+        M.intra_lb = lane[0];
+    }
     // atom -> pair rows (partners in ascending pair order), padded to the longest;
-    // an entry is the pair index | the partner's byte offset in the kernels'
-    // LDS position array (16 B per atom) << 16
+    // an entry is the pair's byte offset in the kernels' LDS coefficient array
+    // (4 B per pair) | the partner's in the position array (16 B per atom) << 16
     std::vector<std::vector<uint32_t>> rows(n);
     for (int q = 0; q < P; ++q) {
         const uint32_t i = M.pairs[q] & 0xff, j = (M.pairs[q] >> 8) & 0xff;
-        rows[i].push_back((uint32_t)q | ((j * 16) << 16));
-        rows[j].push_back((uint32_t)q | ((i * 16) << 16));
+        rows[i].push_back((uint32_t)q * 4 | ((j * 16) << 16));
+        rows[j].push_back((uint32_t)q * 4 | ((i * 16) << 16));
     }
     int w = 0;
     for (int i = 0; i < n; ++i) w = std::max(w, (int)rows[i].size());
@@ -285,7 +301,7 @@ int build_ligand_model(int n, const float* xyz, const uint8_t* type, int nb, con
     for (int i = 0; i < n; ++i)
         for (int k = 0; k < w; ++k)
             M.ell[(size_t)i * w + k] =
-                k < (int)rows[i].size() ? rows[i][k] : ((uint32_t)P | ((uint32_t)(i * 16) << 16));
+                k < (int)rows[i].size() ? rows[i][k] : ((uint32_t)P * 4 | ((uint32_t)(i * 16) << 16));
     return PV_OK;
 }
 

@@ -247,3 +247,35 @@ def test_max_size_ligand_dock(oracle, pv_ctx, big):
     out, e, ne = pv.local_opt(pv_ctx, big.grids, ligs, lig, box, dof, pv.dock_params())
     e = e.cpu().numpy()
     assert np.all(np.isfinite(e)) and np.all(e <= start + e_tol(start))
+
+
+def test_pair_chunk_remainders(oracle, pv_ctx):
+    """Pair lists that end everywhere in a pass of 256: none, whole chunks of 64, one past them.  Chains without
+    steps keep their initial pose's energy, which does not depend on the order of the forces: slots and gather agree
+    bit for bit, both with the oracle's."""
+    import paper_2506_20043_amd as pv
+    cfg = S.CONFIGS["tiny"]
+    rx, rt, bxs = S.make_receptor(cfg)
+    g = np.random.default_rng(19)
+    mols, left = [S.tree_ligand(g, 1, 0), S.tree_ligand(g, 5, 0)], {0: 1}
+    for n in range(8, 64):   # at most one ligand for each eighth of a pass
+        m = S.tree_ligand(g, n, 4 + n // 8)
+        p = pv.describe_ligand(m.xyz, m.types, m.bonds, m.rotatable)[0][3]
+        if left.setdefault((p % 256) // 32 + 1, len(mols)) == len(mols):
+            mols.append(m)
+    assert len(left) == 9
+    st = Setup(oracle, pv_ctx, rx, rt, bxs[:1], mols)
+    plan = pv.Plan(pv_ctx, st.grids, st.ligs, [(i, 0) for i in range(len(mols))], pv.dock_params(chains=4, steps=0))
+    assert plan.groups() == 1
+    res = []
+    for v in (pv.VARIANT_SLOTS, pv.VARIANT_GATHER):
+        plan.set_schedule(0, v)
+        out = plan.run()
+        res.append({k: out[k].cpu().numpy().copy() for k in ("chain_best_e", "chain_best_dof", "chain_pairs")})
+    plan.close()
+    for k in res[0]:
+        assert np.array_equal(res[0][k], res[1][k]), k
+    for c, e in enumerate(res[0]["chain_best_e"]):
+        L = st.ol[c // 4]
+        r = L.score_grad(st.og[0], cpu_dof(res[0]["chain_best_dof"][c, :L.ndof]))
+        assert abs(e - r["e"]) <= e_tol(r["e"]) + (0.01 if r["min_cut"] < 1e-4 else 0.0)
