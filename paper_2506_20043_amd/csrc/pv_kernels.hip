@@ -1540,7 +1540,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 
     }
 }
 
-__global__ void reset_queue_kernel(uint32_t* q) { if (threadIdx.x == 0) *q = 0u; }
+// zeroes both size classes' queue counters
+__global__ void reset_queue_kernel(uint32_t* q) { if (threadIdx.x < 2) q[threadIdx.x] = 0u; }
 
 // Measurement aid, the VALU FP32 issue rate: every thread runs 16 independent
 // multiply-add chains for `iters` rounds with no memory traffic and stores

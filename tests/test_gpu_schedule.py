@@ -251,3 +251,48 @@ def test_ligands_without_intra_pairs(oracle, pv_ctx, setup):
                 r = L.score_grad(setup["og"], cpu_dof(cbd[j, c, :L.ndof]))
                 slack = 0.01 if r["min_cut"] < 1e-4 else 0.0
                 assert abs(r["e"] - cbe[j, c]) <= e_tol(r["e"]) + slack, (variant, j, c, cbe[j, c], r["e"])
+
+
+@pytest.mark.parametrize("form", ["plain", "side stream", "graph flag", "captured by the caller"])
+def test_two_classes_side_by_side(pv_ctx, form):
+    """Ligands of both size classes: their launches overlap on two streams and join the caller's again, eagerly, on
+    another stream, as a replayed graph and inside a capture of the caller's.  Every run gives the outputs of the
+    classes docked one after the other, bit for bit, with other work on the stream between the runs."""
+    import torch
+
+    import paper_2506_20043_amd as pv
+    cfg = S.CONFIGS["tiny"]
+    rx, rt, bxs = S.make_receptor(cfg)
+    g = np.random.default_rng(23)
+    mols = [S.tree_ligand(g, n, t) for n, t in ((20, 4), (70, 6), (12, 2), (90, 8), (64, 9))]
+    grids, ligs = pv.build_grids(pv_ctx, rx, rt, bxs[:1]), pv.Ligands(pv_ctx, mols)
+    jobs = [(i % 5, 0) for i in range(20)]
+    keys = ("chain_best_e", "chain_best_dof", "chain_evals", "job_best_e", "job_best_chain", "job_evals")
+    p = dict(chains=6, steps=6, seed=5)
+    ref = pv.dock(pv_ctx, grids, ligs, jobs, pv.dock_params(**p), plain=True)
+    ref = {k: ref[k].cpu().numpy().copy() for k in keys}
+    plan = pv.Plan(pv_ctx, grids, ligs, jobs, pv.dock_params(flags=pv.PV_DOCK_GRAPH if form == "graph flag" else 0, **p))
+    assert plan.groups() == 2
+    out = plan.outputs()
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    if form == "captured by the caller":
+        with torch.cuda.graph(graph, stream=stream):
+            plan.run()
+    for _ in range(4):
+        for t in out.values():
+            t.zero_()
+        other = torch.ones(1 << 20, device="cuda").sum()
+        if form == "captured by the caller":
+            graph.replay()
+        elif form == "side stream":
+            plan.run(stream=stream)
+            stream.synchronize()
+        else:
+            plan.run()
+        copies = {k: out[k].clone() for k in keys}   # ordered on the caller's stream after both classes
+        torch.cuda.synchronize()
+        assert float(other) == 1 << 20
+        for k in keys:
+            assert np.array_equal(copies[k].cpu().numpy(), ref[k]), (form, k)
+    plan.close()
