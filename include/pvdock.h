@@ -153,7 +153,8 @@ pv_status pv_ligand_describe(int32_t n_atoms, const float* ref_xyz, const uint8_
  * lig_of_pose, box_of_pose: device [B]; an out-of-range index sets that
  * pose's outputs to NaN.
  * grad_energy: device [B] upstream factor for a backward pass, or NULL (= 1).
- * Outputs (device, any may be NULL):
+ * Outputs (device, any may be NULL; without a gradient output the gradient
+ * is not computed):
  *   energy [B]; e_parts [B][2] = (e_inter, e_intra);
  *   grad_dof [B][dof_stride]: grad_energy * dSF/d(t, q, psi), where the
  *   quaternion part is the derivative with respect to the raw input q;
@@ -173,6 +174,16 @@ pv_status pv_score_grad_xyz(pv_ctx* ctx, const pv_grids* grids, const pv_ligands
                             const int32_t* lig_of_pose, const int32_t* box_of_pose, const float* xyz,
                             int32_t xyz_stride, const float* grad_energy, float* energy, float* e_parts,
                             float* grad_xyz, void* stream);
+
+/* The backward pass of a score whose gradient was taken along: out = grad,
+ * each row's own values (7 + T of a pose vector, 3 per atom of coordinates)
+ * times its pose's upstream factor scale [B], as pv_score_grad's grad_energy
+ * gives them; values past them, and rows of out-of-range poses, as they are.
+ * grad, out: device [B][row], a grad_dof (of_xyz = 0, row = dof_stride) or a
+ * grad_xyz (of_xyz = 1, row = 3 xyz_stride) computed with grad_energy NULL. */
+pv_status pv_scale_grad(pv_ctx* ctx, const pv_ligands* ligs, int32_t n_poses, const int32_t* lig_of_pose,
+                        const float* grad, int32_t row, int32_t of_xyz, const float* scale, float* out,
+                        void* stream);
 
 /* -------------------------------------------------------------------- search
  * Parameters of RILC-BFGS (Eqs. qvina_eq_6 .. qvina_eq_12) and of the Monte

@@ -105,6 +105,7 @@ SIGNATURES = {
     "pv_ligand_describe": (C.c_int, [_i32, _vp, _vp, _i32, _vp, _vp, _ip, _ip, _i32, _ip]),
     "pv_score_grad": (C.c_int, [_vp, _vp, _vp, _i32, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _i32, _vp]),
     "pv_score_grad_xyz": (C.c_int, [_vp, _vp, _vp, _i32, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp]),
+    "pv_scale_grad": (C.c_int, [_vp, _vp, _i32, _vp, _vp, _i32, _i32, _vp, _vp, _vp]),
     "pv_dock_params_default": (None, [C.POINTER(DockParams)]),
     "pv_dock_plan": (C.c_int, [_vp, _vp, _vp, C.POINTER(Job), _i32, C.POINTER(DockParams), C.POINTER(_vp)]),
     "pv_dock_run": (C.c_int, [_vp, C.POINTER(DockOut), _vp]),
@@ -409,6 +410,20 @@ def score_grad_xyz(ctx: Context, grids: Grids, ligs: Ligands, lig_of_pose, box_o
     return out
 
 
+def _scale_grad(ctx: Context, ligs: Ligands, lig_of_pose, grad, of_xyz, scale):
+    """Each pose's gradient row times its upstream factor (pv_scale_grad)."""
+    torch = _torch()
+    lp = _dev_tensor(lig_of_pose, torch.int32, ctx.torch_device)
+    ge = _dev_tensor(scale, torch.float32, ctx.torch_device)
+    grad = _dev_tensor(grad, torch.float32, ctx.torch_device)
+    out = torch.empty_like(grad)
+    B = grad.shape[0]
+    row = grad[0].numel() if B else 0
+    _check(lib().pv_scale_grad(ctx.h, ligs.h, int(B), _ptr(lp), _ptr(grad), int(row), int(of_xyz), _ptr(ge), _ptr(out),
+                               _stream()), "pv_scale_grad")
+    return out
+
+
 def _autograd_classes():
     torch = _torch()
 
@@ -416,21 +431,23 @@ def _autograd_classes():
         """E(pose) with the hand-written gradient kernel as its backward.
 
         apply(dof [B, stride], handles) -> energy [B]; the gradient reaches
-        dof as dE/d(t, raw q, psi)."""
+        dof as dE/d(t, raw q, psi).  One launch computes the energy and, where
+        dof needs it, the gradient, which the backward scales."""
 
         @staticmethod
         def forward(fctx, dof, handles):
             ctx, grids, ligs, lp, bp = handles
-            fctx.save_for_backward(dof)
-            fctx.handles = handles
-            return score_grad(ctx, grids, ligs, lp, bp, dof.detach(), grad=False)["energy"]
+            r = score_grad(ctx, grids, ligs, lp, bp, dof.detach(), grad=fctx.needs_input_grad[0])
+            # dof too: a change of it in place before the backward stays an error
+            fctx.save_for_backward(dof, r.get("grad_dof"))
+            fctx.handles = (ctx, ligs, lp)
+            return r["energy"]
 
         @staticmethod
         def backward(fctx, g):
-            (dof,) = fctx.saved_tensors
-            ctx, grids, ligs, lp, bp = fctx.handles
-            r = score_grad(ctx, grids, ligs, lp, bp, dof.detach(), grad=True, grad_energy=g.contiguous())
-            return r["grad_dof"], None
+            grad = fctx.saved_tensors[1]
+            ctx, ligs, lp = fctx.handles
+            return _scale_grad(ctx, ligs, lp, grad, False, g), None
 
     class ScoreGradXYZ(torch.autograd.Function):
         """E(xyz) with dE/dxyz from the same kernel."""
@@ -438,16 +455,16 @@ def _autograd_classes():
         @staticmethod
         def forward(fctx, xyz, handles):
             ctx, grids, ligs, lp, bp = handles
-            fctx.save_for_backward(xyz)
-            fctx.handles = handles
-            return score_grad_xyz(ctx, grids, ligs, lp, bp, xyz.detach())["energy"]
+            r = score_grad_xyz(ctx, grids, ligs, lp, bp, xyz.detach())
+            fctx.save_for_backward(xyz, r["grad_xyz"])
+            fctx.handles = (ctx, ligs, lp)
+            return r["energy"]
 
         @staticmethod
         def backward(fctx, g):
-            (xyz,) = fctx.saved_tensors
-            ctx, grids, ligs, lp, bp = fctx.handles
-            r = score_grad_xyz(ctx, grids, ligs, lp, bp, xyz.detach(), grad_energy=g.contiguous())
-            return r["grad_xyz"], None
+            grad = fctx.saved_tensors[1]
+            ctx, ligs, lp = fctx.handles
+            return _scale_grad(ctx, ligs, lp, grad, True, g), None
 
     return ScoreGrad, ScoreGradXYZ
 

@@ -631,6 +631,25 @@ pv_status pv_score_grad_xyz(pv_ctx* ctx, const pv_grids* grids, const pv_ligands
     return PV_OK;
 }
 
+pv_status pv_scale_grad(pv_ctx* ctx, const pv_ligands* ligs, int32_t n_poses, const int32_t* lig_of_pose,
+                        const float* grad, int32_t row, int32_t of_xyz, const float* scale, float* out, void* stream)
+{
+    if (!ctx_ok(ctx)) return fail(PV_E_STATE, "invalid context");
+    if (!ligs) return fail(PV_E_INVALID, "ligands are NULL");
+    if (ligs->ctx != ctx) return fail(PV_E_STATE, "handles belong to another context");
+    if (n_poses < 0) return fail(PV_E_INVALID, "n_poses < 0");
+    if (n_poses == 0) return PV_OK;
+    if (!lig_of_pose || !grad || !scale || !out) return fail(PV_E_INVALID, "arrays are NULL");
+    if (row < (of_xyz ? 3 * ligs->max_atoms : 7 + ligs->max_tors)) return fail(PV_E_INVALID, "row shorter than the largest ligand's");
+    const int64_t n = (int64_t)n_poses * row;
+    if (n > (int64_t)INT32_MAX * 256) return fail(PV_E_RANGE, "too many values");
+    pv_status st = set_device(ctx);
+    if (st != PV_OK) return st;
+    HIP_TRY(launch_scale_grad(lig_view(ligs), n, row, lig_of_pose, of_xyz != 0, grad, scale, out, (hipStream_t)stream),
+            "gradient scaling launch");
+    return PV_OK;
+}
+
 // ------------------------------------------------------------------ search
 void pv_dock_params_default(pv_dock_params* p)
 {

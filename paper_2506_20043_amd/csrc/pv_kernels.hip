@@ -1085,9 +1085,9 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
     return out;
 }
 
-// Score on given coordinates already in S.pos: forces in S.frc.
+// Score on given coordinates already in S.pos: forces in S.frc (with grads).
 template <int A, bool SL>
-__device__ Eval evaluate_xyz(const Topo<A, SL>& T, const BoxView& B, const Lds& S)
+__device__ Eval evaluate_xyz(const Topo<A, SL>& T, const BoxView& B, const Lds& S, bool grads)
 {
     const int l = lane_id();
     Eval out;
@@ -1103,8 +1103,10 @@ __device__ Eval evaluate_xyz(const Topo<A, SL>& T, const BoxView& B, const Lds& 
             const float4 p = S.pos[i];
             float gx, gy, gz;
             e_in += trilinear(B, ty, p.x, p.y, p.z, gx, gy, gz);
-            gather_pair_forces(T, S, i, p, gx, gy, gz);
-            if (S.frc) S.frc[i] = make_float4(gx, gy, gz, 0.f);
+            if (grads) {
+                gather_pair_forces(T, S, i, p, gx, gy, gz);
+                if (S.frc) S.frc[i] = make_float4(gx, gy, gz, 0.f);
+            }
         }
     }
     wave_sync();
@@ -1612,7 +1614,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(A == 1 && !S
     const int p_end = (int)(((int64_t)(blockIdx.x + 1) * a.n_poses) / (int64_t)gridDim.x);
     // the next pose's indices and pose vector are loaded while this one is
     // evaluated (lane l holds pose entry l)
-    const bool dof_in = !a.from_xyz;
+    const bool dof_in = !a.from_xyz, grads = a.grad_dof || a.grad_xyz;
     int n_lig = 0, n_box = 0;
     float n_dof = 0.f;
     if (p_begin < p_end) {
@@ -1644,14 +1646,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(A == 1 && !S
         const int16_t* perm = a.l.perm + a.l.ligs[lig].atom_base;
         Eval ev;
         if (!a.from_xyz) {
-            ev = evaluate(T, B, S, dof_l);
+            // without a gradient output the evaluation ends with the energy,
+            // as a rejected line-search trial's does
+            ev = evaluate(T, B, S, dof_l, grads ? __builtin_inff() : -__builtin_inff(), false);
         } else {
             for (int i = l; i < T.n; i += kWave) {
                 const float* src = a.dof + ((int64_t)pose * a.xyz_stride + perm[i]) * 3;
                 S.pos[i] = make_float4(src[0], src[1], src[2], 0.f);
             }
             wave_sync();
-            ev = evaluate_xyz(T, B, S);
+            ev = evaluate_xyz(T, B, S, grads);
         }
         if (l == 0 && a.energy) a.energy[pose] = ev.e;
         if (a.e_parts && l < 2) a.e_parts[2 * (int64_t)pose + l] = l == 0 ? ev.e_inter : ev.e_intra;
@@ -1693,6 +1697,32 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(A == 1 && !S
         }
         wave_sync();
     }
+}
+
+// The backward of a score whose gradient the forward computed: each row times
+// its pose's upstream factor, one thread per value.  Values past the ligand's
+// own (7 + torsions of a pose vector, 3 per atom of coordinates) are 0, or NaN
+// where the pose's ligand or box does not exist, and stay so whatever the
+// factor.  16,384 poses of 17 values take 3 us; evaluating them again took 63.
+__global__ __launch_bounds__(256) void scale_grad_kernel(LigDev L, int64_t n, int row, const int32_t* lig_of_pose,
+                                                         bool of_xyz, const float* grad, const float* scale, float* out)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int pose = (int)(i / row), k = (int)(i % row), lig = lig_of_pose[pose];
+    const float v = grad[i];
+    int own = 0;
+    if (lig >= 0 && lig < L.n_lig) own = of_xyz ? 3 * L.ligs[lig].n_atoms : 7 + L.ligs[lig].n_tors;
+    out[i] = k < own ? v * scale[pose] : v;
+}
+
+hipError_t launch_scale_grad(const LigDev& l, int64_t n, int row, const int32_t* lig_of_pose, bool of_xyz,
+                             const float* grad, const float* scale, float* out, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(scale_grad_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, l, n, row, lig_of_pose,
+                       of_xyz, grad, scale, out);
+    return hipGetLastError();
 }
 
 template <int A, bool SL>

@@ -283,3 +283,42 @@ def test_ring_ligands_score_and_gradient(oracle, pv_ctx):
         z = np.zeros(B, np.int32)
         out = pv.score_grad(pv_ctx, st.grids, st.ligs, lig, z, dof, parts=True, xyz=True)
         compare(st, lig, z, dof, out, range(B))
+
+
+@pytest.mark.parametrize("of_xyz", [False, True])
+def test_autograd_scaling_matches_the_kernel(pv_ctx, of_xyz):
+    """The backward scales the gradient that the forward kept: bit for bit the score kernel's own gradient with the
+    upstream factors as grad_energy, for ragged ligands, poses of no ligand or box, zero, infinite and NaN factors; the
+    energy alone (no gradient wanted) is the same too, and an input changed in place before the backward is refused."""
+    import torch
+
+    import paper_2506_20043_amd as pv
+    cfg = S.CONFIGS["tiny"]
+    rx, rt, bxs = S.make_receptor(cfg)
+    g = np.random.default_rng(31)
+    mols = [S.tree_ligand(g, n, t) for n, t in ((20, 4), (3, 0), (40, 9), (70, 12))]
+    grids, ligs = pv.build_grids(pv_ctx, rx, rt, bxs[:1]), pv.Ligands(pv_ctx, mols)
+    B = 203
+    lig = torch.tensor(g.integers(0, 4, B), dtype=torch.int32, device="cuda")
+    box = torch.zeros(B, dtype=torch.int32, device="cuda")
+    lig[5], lig[6], box[7] = -1, 4, 1
+    x = torch.tensor(S.poses(g, B, 6.0, 24.0, ligs.max_tors + 2), device="cuda")
+    if of_xyz:
+        x = pv.score_grad(pv_ctx, grids, ligs, lig, box, x, xyz=True)["xyz"].nan_to_num(5.0)
+    w = torch.tensor(g.normal(size=B), dtype=torch.float32, device="cuda")
+    w[:5] = torch.tensor([0.0, float("inf"), -float("inf"), float("nan"), 1.0])
+    score = pv.score_grad_xyz if of_xyz else pv.score_grad
+    ref = score(pv_ctx, grids, ligs, lig, box, x, grad_energy=w)
+    fn = pv.ScoreGradXYZ if of_xyz else pv.ScoreGrad
+    x.requires_grad_(True)
+    e = fn.apply(x, (pv_ctx, grids, ligs, lig, box))
+    (got,) = torch.autograd.grad(e, x, w, retain_graph=True)
+    want = ref["grad_xyz" if of_xyz else "grad_dof"]
+    assert np.array_equal(got.cpu().numpy(), want.cpu().numpy(), equal_nan=True)
+    assert np.array_equal(e.detach().cpu().numpy(), ref["energy"].cpu().numpy(), equal_nan=True)
+    with torch.no_grad():
+        alone = fn.apply(x, (pv_ctx, grids, ligs, lig, box))
+        assert np.array_equal(alone.cpu().numpy(), ref["energy"].cpu().numpy(), equal_nan=True)
+        x.add_(1.0)
+    with pytest.raises(RuntimeError):
+        torch.autograd.grad(e, x, w)
