@@ -166,9 +166,9 @@ def _stream(stream=None):
     then first waits for the current stream's work (the inputs were prepared
     there).  Results on `stream` are the caller's to wait for."""
     torch = _torch()
+    if stream is None:   # the raw handle: a Stream object costs a quarter of a small call
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     cur = torch.cuda.current_stream()
-    if stream is None:
-        return C.c_void_p(cur.cuda_stream)
     if stream.cuda_stream != cur.cuda_stream:
         stream.wait_stream(cur)
     return C.c_void_p(stream.cuda_stream)
@@ -193,6 +193,8 @@ def _used_on(stream, *tensors):
 def _dev_tensor(a, dtype, device):
     torch = _torch()
     if isinstance(a, torch.Tensor):
+        if a.dtype is dtype and a.device == device and a.is_contiguous():
+            return a
         t = a.to(device=device, dtype=dtype)
     else:
         t = torch.as_tensor(np.asarray(a), device=device).to(dtype)
@@ -206,10 +208,7 @@ class Context:
         _check(lib().pv_create(int(device), C.byref(h)), "pv_create")
         self.h = h
         self.device = int(device)
-
-    @property
-    def torch_device(self):
-        return _torch().device("cuda", self.device)
+        self.torch_device = _torch().device("cuda", self.device)
 
     def close(self):
         if self.h:
@@ -492,15 +491,11 @@ class Plan:
     """A dock plan: the job table on the device plus checked parameters."""
 
     def __init__(self, ctx: Context, grids: Grids, ligs: Ligands, jobs, params: DockParams):
-        jobs = np.ascontiguousarray(jobs, np.int32).reshape(-1, 2)
-        arr = (Job * max(len(jobs), 1))()
-        for i, (l, b) in enumerate(jobs):
-            arr[i].ligand, arr[i].box = int(l), int(b)
+        arr, n = _job_array(jobs)
         h = C.c_void_p()
-        _check(lib().pv_dock_plan(ctx.h, grids.h, ligs.h, arr, len(jobs), C.byref(params), C.byref(h)),
-               "pv_dock_plan")
+        _check(lib().pv_dock_plan(ctx.h, grids.h, ligs.h, arr, n, C.byref(params), C.byref(h)), "pv_dock_plan")
         self.ctx, self.grids, self.ligs, self.h = ctx, grids, ligs, h
-        self.n_jobs, self.params = len(jobs), params
+        self.n_jobs, self.params = n, params
         self._out = None
 
     def outputs(self):
@@ -592,8 +587,7 @@ NOALLOC_MAX_JOBS, NOALLOC_MAX_CHAINS = 65536, 1 << 20
 def _job_array(jobs):
     jobs = np.ascontiguousarray(jobs, np.int32).reshape(-1, 2)
     arr = (Job * max(len(jobs), 1))()
-    for i, (l, b) in enumerate(jobs):
-        arr[i].ligand, arr[i].box = int(l), int(b)
+    C.memmove(arr, jobs.ctypes.data, jobs.nbytes)   # a Job is two int32
     return arr, len(jobs)
 
 

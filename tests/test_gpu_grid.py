@@ -225,3 +225,42 @@ def test_tile_and_list_edges(oracle, pv_ctx, dims, n_rec, cube):
     d, org = grids.info(0)
     assert tuple(d) == dims
     _assert_maps_close(maps[0], oracle.build_maps(rx, rt, d, org, box.spacing), str(dims))
+
+
+def test_map_blocks_are_reused_safely(pv_ctx):
+    """A freed set of maps leaves its memory to the next build that fits it: builds of equal, smaller and larger sizes,
+    with other sets alive, frees while work on the set is still queued on another stream, and several threads at once
+    all give the maps of a first build."""
+    import threading
+
+    import torch
+
+    import paper_2506_20043_amd as pv
+    g = np.random.default_rng(3)
+    rx, rt = S.receptor(g, 900, 20.0)
+    boxes = {e: [S.Box(np.full(3, 10.0, np.float32), np.full(3, e, np.float32))] for e in (9.0, 12.0, 13.0, 19.0)}
+    ref = {e: _gpu_maps(pv_ctx, rx, rt, b)[1][0] for e, b in boxes.items()}
+    side = torch.cuda.Stream()
+
+    def work(order, bad):
+        for k, e in enumerate(order):
+            other = pv.build_grids(pv_ctx, rx[:100], rt[:100], boxes[order[k - 1]])
+            grids = pv.build_grids(pv_ctx, rx, rt, boxes[e])
+            if k % 2:
+                for _ in range(3):
+                    other.rebuild(stream=side)   # still queued when the set is freed
+            other.close()
+            again = pv.build_grids(pv_ctx, rx, rt, boxes[e])
+            for q in (grids, again):
+                if not np.array_equal(q.maps(0).cpu().numpy(), ref[e]):
+                    bad.append(e)
+            grids.close()
+
+    bad = []
+    work([12.0, 13.0, 12.0, 19.0, 9.0, 19.0], bad)
+    threads = [threading.Thread(target=work, args=(o, bad)) for o in ([12.0, 19.0, 13.0], [13.0, 9.0, 13.0], [19.0, 19.0])]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
