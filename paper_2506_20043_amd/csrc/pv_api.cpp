@@ -182,6 +182,7 @@ struct pv_ligands {
     uint32_t* ell;
     uint32_t* pslot;
     int32_t max_ell;
+    bool ragged;                                 // sizes differ: see launch_score
     std::vector<std::array<int32_t, 9>>* info;   // pv_ligands_info's 8 values, then the slot-table size
 };
 
@@ -609,6 +610,9 @@ pv_status pv_ligands_create(pv_ctx* ctx, int32_t n_lig, const int32_t* atom_off,
     L->max_pairs = max_pairs;
     L->max_tors = max_tors;
     L->max_ell = max_ell;
+    int64_t sum_pairs = 0;
+    for (const auto& in : *info) sum_pairs += in[3];
+    L->ragged = 4 * sum_pairs < 3 * (int64_t)max_pairs * n_lig;
     L->info = info;
     if ((st = upload(&L->ligs, H.data(), H.size(), "ligand upload")) != PV_OK ||
         (st = upload(&L->atoms, (const float4*)atoms.data(), atoms.size() / 4, "ligand upload")) != PV_OK ||
@@ -714,7 +718,7 @@ pv_status pv_score_grad(pv_ctx* ctx, const pv_grids* grids, const pv_ligands* li
     a.xyz_out = xyz_out;
     a.grad_xyz = grad_xyz;
     a.xyz_stride = xyz_stride;
-    hipError_t e = launch_score(a, ctx->n_cu, (hipStream_t)stream);
+    hipError_t e = launch_score(a, ligs->ragged, ctx->n_cu, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "score launch");
     return PV_OK;
 }
@@ -746,7 +750,7 @@ pv_status pv_score_grad_xyz(pv_ctx* ctx, const pv_grids* grids, const pv_ligands
     a.e_parts = e_parts;
     a.grad_xyz = grad_xyz;
     a.xyz_stride = xyz_stride;
-    hipError_t e = launch_score(a, ctx->n_cu, (hipStream_t)stream);
+    hipError_t e = launch_score(a, ligs->ragged, ctx->n_cu, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "score launch");
     return PV_OK;
 }

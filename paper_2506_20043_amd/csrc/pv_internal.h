@@ -221,7 +221,8 @@ hipError_t launch_shape(int kind, const LigDev& l, int64_t items, int n_cu, Laun
 // hipErrorInvalidConfiguration when no workgroup of it fits a CU.
 hipError_t launch_shape_variant(int kind, const LigDev& l, int variant, LaunchShape* out);
 
-hipError_t launch_score(const ScoreArgs& a, int n_cu, hipStream_t s);
+// ragged: the ligands' sizes differ widely
+hipError_t launch_score(const ScoreArgs& a, bool ragged, int n_cu, hipStream_t s);
 // out = grad with each row's own values times its pose's scale; n = poses x row
 hipError_t launch_scale_grad(const LigDev& l, int64_t n, int row, const int32_t* lig_of_pose, bool of_xyz,
                              const float* grad, const float* scale, float* out, hipStream_t s);

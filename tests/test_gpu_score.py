@@ -322,3 +322,24 @@ def test_autograd_scaling_matches_the_kernel(pv_ctx, of_xyz):
         x.add_(1.0)
     with pytest.raises(RuntimeError):
         torch.autograd.grad(e, x, w)
+
+
+@pytest.mark.parametrize("n", [1, 2049, 13000])
+def test_ragged_batches_equal_their_pieces(pv_ctx, n):
+    """Ligands of very different sizes run shorter runs of poses per wave: fewer poses than waves, one past them, and
+    more than six per slot give what pieces of 500 poses give, bit for bit."""
+    import torch
+
+    import paper_2506_20043_amd as pv
+    rx, rt, bxs = S.make_receptor(S.CONFIGS["tiny"])
+    g = np.random.default_rng(13)
+    mols = [S.tree_ligand(g, k, t) for k, t in ((70, 10), (8, 1), (20, 4), (12, 2), (33, 6))]
+    grids, ligs = pv.build_grids(pv_ctx, rx, rt, bxs[:1]), pv.Ligands(pv_ctx, mols)
+    lig = torch.tensor(g.integers(0, 5, n), dtype=torch.int32, device="cuda")
+    box = torch.zeros(n, dtype=torch.int32, device="cuda")
+    dof = torch.tensor(S.poses(g, n, 6.0, 24.0, ligs.max_tors), device="cuda")
+    whole = pv.score_grad(pv_ctx, grids, ligs, lig, box, dof, parts=True, xyz=True)
+    for a in range(0, n, 500):
+        part = pv.score_grad(pv_ctx, grids, ligs, lig[a:a + 500], box[a:a + 500], dof[a:a + 500], parts=True, xyz=True)
+        for k, v in part.items():
+            assert torch.equal(whole[k][a:a + 500], v), k
