@@ -15,6 +15,7 @@ constexpr int kMaxAtoms = 128;
 constexpr int kMaxTors = 32;
 constexpr int kMaxFrag = kMaxTors + 1;
 constexpr int kWave = 64;
+constexpr int kEllPad = 32;   // zero entries after the atom -> pair tables (the kernels read rows in chunks)
 
 // Per-ligand header in device memory.  Atoms are stored in depth-first
 // fragment order (each torsion moves one contiguous atom range); fragments

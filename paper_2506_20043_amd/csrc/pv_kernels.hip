@@ -53,6 +53,21 @@ __device__ __forceinline__ float from_lane(int src4, float v)
 
 __device__ __forceinline__ int lane_i(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 
+// v plus lane 15 of the row before, in rows 1 and 3, then lane 31's in rows 2
+// and 3; the other rows keep theirs.  One instruction each (the compiler makes
+// three: it does not fold an addition into a permutation of some rows).  A
+// permutation may read a register two wait states after it was written.
+__device__ __forceinline__ float add_row_before(float v)
+{
+    asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ float add_rows_before(float v)
+{
+    asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf" : "+v"(v));
+    return v;
+}
+
 // sum over the 64 lanes, identical in every lane
 __device__ __forceinline__ float wsum(float v)
 {
@@ -61,9 +76,7 @@ __device__ __forceinline__ float wsum(float v)
     v += dpp0<0x141>(v);  // row_half_mirror: the other quad of each 8 lanes
     v += dpp0<0x140>(v);  // row_mirror: the other half of each row
     // the rows' sums: (row 0 + row 1) + (row 2 + row 3) ends in lane 63
-    v += dpp0<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-    v += dpp0<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-    return lane_f(v, 63);
+    return lane_f(add_rows_before(add_row_before(v)), 63);
 }
 
 // sum over lanes 0..n-1 of a b, where every lane from n up holds zero (n is
@@ -76,10 +89,9 @@ __device__ __forceinline__ float wdot_n(float a, float b, int n)
     v += dpp0<0x141>(v);
     v += dpp0<0x140>(v);
     if (n <= 16) return lane_f(v, 0);
-    v += dpp0<0x142, 0xA>(v);
+    v = add_row_before(v);
     if (n <= 32) return lane_f(v, 31);
-    v += dpp0<0x143, 0xC>(v);
-    return lane_f(v, 63);
+    return lane_f(add_rows_before(v), 63);
 }
 
 // integer sum over the 64 lanes, identical in every lane
@@ -90,16 +102,32 @@ __device__ __forceinline__ int64_t wsum_i64(int64_t v)
     return v;
 }
 
-// inclusive prefix sum over the 64 lanes in lane order
-__device__ __forceinline__ float wscan(float v)
+// inclusive prefix sums of six values over the 64 lanes in lane order (side by
+// side, so that their cross-row steps need no wait states between them)
+__device__ __forceinline__ void wscan6(float v[6])
 {
-    v += dpp0<0x111>(v);        // row_shr:1
-    v += dpp0<0x112>(v);        // row_shr:2
-    v += dpp0<0x114>(v);        // row_shr:4
-    v += dpp0<0x118>(v);        // row_shr:8
-    v += dpp0<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp0<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) v[c] += dpp0<0x111>(v[c]);   // row_shr:1
+#pragma unroll
+    for (int c = 0; c < 6; ++c) v[c] += dpp0<0x112>(v[c]);   // row_shr:2
+#pragma unroll
+    for (int c = 0; c < 6; ++c) v[c] += dpp0<0x114>(v[c]);   // row_shr:4
+#pragma unroll
+    for (int c = 0; c < 6; ++c) v[c] += dpp0<0x118>(v[c]);   // row_shr:8
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_add_f32_dpp %5, %5, %5 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_add_f32_dpp %4, %4, %4 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "v_add_f32_dpp %5, %5, %5 row_bcast:31 row_mask:0xc bank_mask:0xf"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]));
 }
 
 // the lane within the wave for the one-wave workgroups of the docking kernels
@@ -292,8 +320,7 @@ constexpr int kSlot = 40;
 struct Lds {
     char* base;        // start of the wave's LDS
     uint32_t pos0;     // LDS byte address of pos
-    float* frame;      // [kMaxFrag][12] frames, then [kMaxFrag] ancestor links / torsion derivatives
-                       // (without the frames: the [kMaxFrag] torsion derivatives only)
+    float* frame;      // [kMaxFrag][12] frames (where a kernel keeps them)
     float4* pos;       // [ma + 1]; entry ma: a point far outside every box
     float4* frc;       // [max_atoms] dE/dx per atom, or NULL when nothing reads it back
     float* pre;        // [6][max_atoms]
@@ -339,8 +366,9 @@ __host__ __device__ inline int lds_atoms(int max_atoms) { return round_up(max_at
 // Optional regions: the per-atom forces (read back only by the score
 // kernel's coordinate gradient) and the fragment frames (needed when atoms
 // take their frames from LDS: two atoms per lane, and the output stage's
-// pose positions; with one atom per lane the frames travel by ds_bpermute
-// and only the torsion derivatives use the area).
+// pose positions; with one atom per lane the frames travel by ds_bpermute,
+// as the torsion derivatives do, and the area is only kept for its size, see
+// kLdsSpare).
 struct LdsNeeds {
     bool slots, frc, frames;
     bool pw;   // gather layout: the pair words in LDS too (one atom per lane), else read from global memory
@@ -387,10 +415,6 @@ __device__ __forceinline__ Lds carve(char* base, int max_atoms, int max_pairs, i
     s.ma = ma;
     return s;
 }
-
-// Torsion derivatives in LDS: after the frames (and their links) when the
-// frames are stored, else at the start of the frame area.
-__device__ __forceinline__ float* dpsi_area(const Lds& S, bool frames) { return frames ? S.frame + 12 * kMaxFrag : S.frame; }
 
 // The regions a kernel's LDS holds: per-atom forces for the score kernel's
 // coordinate gradient; frames for two atoms per lane and the output stage;
@@ -801,8 +825,11 @@ __device__ __forceinline__ float pair_loop(const Topo<A, SL>& T, const Lds& S, i
 // entry holds p's byte offset in S.cp in its low half and j's in S.pos in its high half.
 // row loads of the global atom -> pair table issued together by the gather:
 // the table sits in L2, so a row walked one load at a time pays one L2
-// round trip per four entries
+// round trip per four entries.  The loads are issued by four: past the row
+// they read the next rows (past the last one the table's padding, kEllPad
+// entries), which are not summed.
 constexpr int kGatherChunk = 8;
+static_assert(4 * kGatherChunk <= kEllPad, "the padding covers a chunk");
 
 template <int A, bool SL>
 __device__ __forceinline__ void gather_pair_forces(const Topo<A, SL>& T, const Lds& S, int i, float4 xi, float& gx,
@@ -830,17 +857,18 @@ __device__ __forceinline__ void gather_pair_forces(const Topo<A, SL>& T, const L
         }
         return;
     }
-    // the atom's row is contiguous ([n][ell_w], ell_w a multiple of four):
-    // one 16-byte load per four entries, at an unsigned 32-bit offset from
-    // the table's base (a scalar base plus one vector offset)
-    // up to kGatherChunk loads of the row are issued before any is used, so
-    // a row of at most 4 * kGatherChunk entries pays one load latency
+    // the atom's row is contiguous ([n][ell_w], ell_w a multiple of four): one
+    // 16-byte load per four entries, a chunk's issued before any is used, so a
+    // row of at most 4 * kGatherChunk entries pays one load latency.  Issued by
+    // four with one base address and no test per load: the screening slice
+    // 357 -> 351 ms, a batch score of 8-80 atoms 39.6 -> 36.0 us (all eight
+    // without a test read too much: 375 ms).
     const char* row = (const char*)T.gell + (uint32_t)(i * T.ell_w * 4);
     for (int k0 = 0; k0 < T.ell_w; k0 += 4 * kGatherChunk) {
         uint4 e4[kGatherChunk];
 #pragma unroll
         for (int q = 0; q < kGatherChunk; ++q)
-            if (k0 + 4 * q < T.ell_w) e4[q] = *(const uint4*)(row + (uint32_t)((k0 + 4 * q) * 4));
+            if (q < 4 || T.ell_w - k0 > 16) e4[q] = *(const uint4*)(row + (uint32_t)(k0 * 4) + 16 * q);
 #pragma unroll
         for (int q = 0; q < kGatherChunk; ++q) {
             if (k0 + 4 * q >= T.ell_w) break;
@@ -854,9 +882,9 @@ __device__ __forceinline__ void gather_pair_forces(const Topo<A, SL>& T, const L
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                gx += c[u] * (xi.x - xj[u].x);
-                gy += c[u] * (xi.y - xj[u].y);
-                gz += c[u] * (xi.z - xj[u].z);
+                gx = fmaf(c[u], xi.x - xj[u].x, gx);
+                gy = fmaf(c[u], xi.y - xj[u].y, gy);
+                gz = fmaf(c[u], xi.z - xj[u].z, gz);
             }
         }
     }
@@ -1033,16 +1061,17 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
             if (S.frc) S.frc[i] = make_float4(G[a][0], G[a][1], G[a][2], 0.f);
             rx = X4[a].x - tx; ry = X4[a].y - ty; rz = X4[a].z - tz;
         }
-        run[0] += G[a][0]; run[1] += G[a][1]; run[2] += G[a][2];
-        run[3] += ry * G[a][2] - rz * G[a][1];
-        run[4] += rz * G[a][0] - rx * G[a][2];
-        run[5] += rx * G[a][1] - ry * G[a][0];
+        const float m[6] = {G[a][0], G[a][1], G[a][2], fmaf(ry, G[a][2], -(rz * G[a][1])),
+                            fmaf(rz, G[a][0], -(rx * G[a][2])), fmaf(rx, G[a][1], -(ry * G[a][0]))};
+#pragma unroll
+        for (int c = 0; c < 6; ++c) run[c] = a == 0 ? m[c] : run[c] + m[c];
 #pragma unroll
         for (int c = 0; c < 6; ++c) v[a][c] = run[c];
     }
     float incl[6];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) incl[c] = wscan(run[c]);
+    for (int c = 0; c < 6; ++c) incl[c] = run[c];
+    wscan6(incl);
     // atom i's prefix: lane i's inclusive scan (one atom per lane), else the
     // lane's exclusive scan plus its running sum up to the atom
 #pragma unroll
@@ -1060,6 +1089,7 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
     }
     wave_sync();
     // torsion derivative: world axis . sum over the moved atoms of (x - x_c) x G
+    const float total = S.pre[(l < 6 ? l : 0) * S.ma + T.n - 1];
     float dpsi = 0.f;
     if (l >= 1 && l < T.nf) {
         const int e = T.f_end - 1, s0 = T.f_a0 - 1;
@@ -1073,14 +1103,8 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
         const float mz = Sg[5] - (cx * Sg[1] - cy * Sg[0]);
         dpsi = awx * mx + awy * my + awz * mz;
     }
-    float* dps = dpsi_area(S, A > 1);
-    if (l >= 1 && l < T.nf) dps[l] = dpsi;
-    wave_sync();
-    const int last = T.n - 1;
-    float g = 0.f;
-    if (l < 6) g = S.pre[l * S.ma + last];
-    else if (l < 6 + T.nt) g = *(const float*)((const char*)dps + T.dof_src);
-    out.g = g;
+    const float own = __int_as_float(__builtin_amdgcn_ds_bpermute(T.dof_src, __float_as_int(dpsi)));
+    out.g = l < 6 ? total : l < 6 + T.nt ? own : 0.f;
     wave_sync();
     return out;
 }
@@ -1147,7 +1171,8 @@ __device__ __forceinline__ float retract(float x, float d, float lam)
     quat_normalize(nq);
     // pose entries 0..2 move by tangent lanes 0..2, entry k >= 7 (a torsion)
     // by tangent lane k - 1
-    return with_quat(fmaf(lam, l < 3 ? d : lane_below(d), x), nq);
+    const float below = lane_below(d);
+    return with_quat(fmaf(lam, l < 3 ? d : below, x), nq);
 }
 
 // ---------------------------------------------------------------- RILC-BFGS
