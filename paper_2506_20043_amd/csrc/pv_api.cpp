@@ -1008,7 +1008,7 @@ static hipError_t enqueue_batched(pv_plan* P, const pv_dock_out* o, hipStream_t 
         a.job_begin = 0;
         a.n_items = (int64_t)G.n_jobs * P->sp.chains;
         a.persistent = 1;
-        const hipError_t el = launch_dock(a, G.shape, G.workgroups, two && k == 0 ? P->side_stream : s);
+        const hipError_t el = launch_dock(a, G.shape, G.workgroups, !two, P->ctx->n_cu, two && k == 0 ? P->side_stream : s);
         if (e == hipSuccess) e = el;
     }
     // joined also where a launch failed, so that nothing is left running
@@ -1079,7 +1079,7 @@ pv_status pv_dock_run_plain(pv_plan* P, const pv_dock_out* o, void* stream)
         a.job_begin = j;
         a.n_items = P->sp.chains;
         a.persistent = 0;
-        HIP_TRY(launch_dock(a, G.plain_shape, 0, s), "dock launch");
+        HIP_TRY(launch_dock(a, G.plain_shape, 0, false, P->ctx->n_cu, s), "dock launch");
     }
     if (o->job_best_e || o->job_best_chain || o->job_evals || o->job_status)
         HIP_TRY(launch_job_reduce(cbe, cev, cst, P->n_jobs, P->sp.chains, o->job_best_e, o->job_best_chain,
@@ -1267,7 +1267,7 @@ pv_status pv_dock_autotune(pv_plan* P, int32_t tune_steps, int32_t repeats, void
             for (int r = 0; r < repeats; ++r) {
                 e = launch_reset_queue(P->queue, s);
                 if (e == hipSuccess) e = hipEventRecord(t0, s);
-                if (e == hipSuccess) e = launch_dock(a, cand[k].first, cand[k].second, s);
+                if (e == hipSuccess) e = launch_dock(a, cand[k].first, cand[k].second, P->groups.size() == 1, P->ctx->n_cu, s);
                 if (e == hipSuccess) e = hipEventRecord(t1, s);
                 if (e == hipSuccess) e = hipEventSynchronize(t1);
                 float ms = 0.f;
@@ -1414,7 +1414,7 @@ pv_status pv_dock_noalloc(pv_ctx* ctx, const pv_grids* grids, const pv_ligands* 
         a.job_t_start = out->job_t_start;
         a.job_t_end = out->job_t_end;
         a.dof_stride = out->dof_stride;
-        HIP_TRY(launch_dock(a, sh[g], width[g], s), "dock launch");
+        HIP_TRY(launch_dock(a, sh[g], width[g], true, ctx->n_cu, s), "dock launch");
     }
     if (out->job_best_e || out->job_best_chain || out->job_evals || out->job_status)
         HIP_TRY(launch_job_reduce(cbe, cev, cst, n_jobs, params->chains, out->job_best_e, out->job_best_chain,

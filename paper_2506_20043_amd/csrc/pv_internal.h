@@ -227,7 +227,8 @@ hipError_t launch_score(const ScoreArgs& a, bool ragged, int n_cu, hipStream_t s
 // out = grad with each row's own values times its pose's scale; n = poses x row
 hipError_t launch_scale_grad(const LigDev& l, int64_t n, int row, const int32_t* lig_of_pose, bool of_xyz,
                              const float* grad, const float* scale, float* out, hipStream_t s);
-hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgroups, hipStream_t s);
+// alone: no other dock launch runs beside it
+hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgroups, bool alone, int n_cu, hipStream_t s);
 hipError_t launch_reset_queue(uint32_t* q, hipStream_t s);
 hipError_t launch_fma_peak(float* out, int n, int iters, hipStream_t s);
 hipError_t launch_job_reduce(const float* chain_best_e, const int64_t* chain_evals, const int32_t* chain_status,

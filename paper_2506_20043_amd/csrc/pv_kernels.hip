@@ -144,6 +144,15 @@ __device__ __forceinline__ void wave_sync()
 }
 
 
+// Orders LDS accesses between the waves of a workgroup; every wave that has not
+// ended takes part.
+__device__ __forceinline__ void team_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // ---------------------------------------------------------------- Philox4x64-10
 __device__ __forceinline__ void philox4x64_10(uint64_t c[4], uint64_t k0, uint64_t k1)
 {
@@ -324,6 +333,11 @@ struct Lds {
     float4* pos;       // [ma + 1]; entry ma: a point far outside every box
     float4* frc;       // [max_atoms] dE/dx per atom, or NULL when nothing reads it back
     float* pre;        // [6][max_atoms]
+    float4* map;       // with helper waves: [ma] map force per atom,
+    uint32_t* count;   //   [helpers][64] the lanes' pairs inside the cutoff | an atom outside << 31,
+    float* part;       //   [their chunks][64] the pairs' energies,
+    float* e_map;      //   [1] the map energy,
+    int* done;         //   [1] the chain has ended
     uint4* pairs;      // [max_pairs rounded up to kPairPass] pair records, slot layout (see stage_ligand)
     float* cp;         // [max_pairs rounded up to kWave] per-pair force coefficient, gather layout
     uint32_t* pw;      // [max_pairs rounded up to kWave] pair words, gather layout (see stage_ligand)
@@ -416,6 +430,46 @@ __device__ __forceinline__ Lds carve(char* base, int max_atoms, int max_pairs, i
     return s;
 }
 
+// A chain is one wave's serial work, and a launch of few chains leaves most SIMDs
+// idle while its longest runs on.  Such a launch gives every chain a team of W
+// waves: its own and W - 1 helpers, which wait at a barrier for an evaluation's
+// atom positions; the last one looks the maps up, and the chunks of 64 pairs are
+// shared out.  Energies cross per pair and are added in the order of the list,
+// so the searches stay the same bit for bit.  At most 168 VGPRs, so that a CU
+// holds three teams of four or six of two.
+//
+// First of the nc chunks of wave w of a team (of wave W: nc): the map lookup is
+// worth about three chunks (five pockets, 445 pairs, teams of two: own wave four
+// of seven chunks 152 ms, five 142, six 145; one wave 165 ms).
+template <int W>
+__host__ __device__ inline int team_chunk(int nc, int w)
+{
+    if constexpr (W == 1) return w * nc;
+    else {
+        const int last = nc > 3 * (W - 1) ? (nc - 3 * (W - 1)) / W : 0, rest = nc - last;
+        return w == W ? nc : (rest * w + W - 2) / (W - 1);
+    }
+}
+
+// The helpers' results in LDS, after the regions of carve.
+template <int W>
+__host__ __device__ inline int team_bytes(int max_atoms, int max_pairs)
+{
+    const int nc = (max_pairs + kWave - 1) / kWave;
+    return lds_atoms(max_atoms) * 16 + (W - 1) * kWave * 4 + 16 + (nc - team_chunk<W>(nc, 1)) * kWave * 4;
+}
+
+template <int W>
+__device__ __forceinline__ void carve_team(Lds& s, char* p, int max_atoms)
+{
+    s.map = (float4*)p; p += lds_atoms(max_atoms) * 16;
+    s.count = (uint32_t*)p; p += (W - 1) * kWave * 4;
+    s.done = (int*)p;
+    s.e_map = (float*)p + 1;
+    p += 16;
+    s.part = (float*)p;
+}
+
 // The regions a kernel's LDS holds: per-atom forces for the score kernel's
 // coordinate gradient; frames for two atoms per lane and the output stage;
 // the pair words for one atom per lane on the gather layout (with two atoms
@@ -456,7 +510,7 @@ struct Topo {
 };
 
 template <int A, bool SL>
-__device__ void stage_ligand(Topo<A, SL>& T, const LigDev& L, int lig, const Lds& S)
+__device__ void stage_ligand(Topo<A, SL>& T, const LigDev& L, int lig, const Lds& S, bool fill = true)
 {
     const int l = lane_id();
     const DevLig d = L.ligs[lig];
@@ -503,6 +557,7 @@ __device__ void stage_ligand(Topo<A, SL>& T, const LigDev& L, int lig, const Lds
     T.gpairs = L.pairs + d.pair_base;
     T.gell = L.ell + d.ell_base;
     T.np0 = d.n_plain; T.np1 = d.n_hyd; T.lb = d.intra_lb;
+    if (!fill) return;
     if (l == 0) S.pos[S.ma] = make_float4(1e18f, 1e18f, 1e18f, 0.f);
     if (SL) {
         // Pair record, everything the pair loop needs without decoding:
@@ -664,7 +719,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 // adds this lane's energy to e and its pairs inside the cutoff to cnt.
 template <int A, bool SL, int U>
 __device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, int c0, float& e, int& cnt,
-                                          const uint32_t* words = nullptr)
+                                          const uint32_t* words = nullptr, float* part = nullptr)
 {
     const int p0 = c0 + lane_id();
     // position addresses; slot addresses; radius sum bits (slots) or the
@@ -749,7 +804,8 @@ __device__ __forceinline__ void pair_pass(const Topo<A, SL>& T, const Lds& S, in
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        e += in[u] ? en[u] : 0.f;
+        if (part) part[u * kWave + lane_id()] = in[u] ? en[u] : 0.f;
+        else e += in[u] ? en[u] : 0.f;
         cnt += in[u] ? 1 : 0;
         const float c = in[u] ? de[u] * rinv[u] : 0.f;
         if (SL) {
@@ -823,6 +879,20 @@ __device__ __forceinline__ float pair_loop(const Topo<A, SL>& T, const Lds& S, i
 // forces (independent reads, rows padded to a multiple of four with zeros).
 // Global tables: sum over the pairs holding atom i of c_p (x_i - x_j); an
 // entry holds p's byte offset in S.cp in its low half and j's in S.pos in its high half.
+// The chunks [k, end) of 64 pairs; their energies go to part where it is given.
+template <int A, bool SL>
+__device__ __forceinline__ void pair_chunks(const Topo<A, SL>& T, const Lds& S, int k, int end, float& e, int& cnt, float* part)
+{
+    const int first = k;
+    auto to = [&] { return part ? part + (k - first) * kWave : nullptr; };
+    for (; k + kPairUnroll <= end; k += kPairUnroll) pair_pass<A, SL, kPairUnroll>(T, S, k * kWave, e, cnt, nullptr, to());
+    if (k + 2 <= end) {
+        pair_pass<A, SL, 2>(T, S, k * kWave, e, cnt, nullptr, to());
+        k += 2;
+    }
+    if (k < end) pair_pass<A, SL, 1>(T, S, k * kWave, e, cnt, nullptr, to());
+}
+
 // row loads of the global atom -> pair table issued together by the gather:
 // the table sits in L2, so a row walked one load at a time pays one L2
 // round trip per four entries.  The loads are issued by four: past the row
@@ -836,11 +906,19 @@ __device__ __forceinline__ void gather_pair_forces(const Topo<A, SL>& T, const L
                                                    float& gy, float& gz)
 {
     if (SL) {
-        // eight independent reads in flight per group (rows are padded to a
-        // multiple of four, so at most one group of four is left)
+        // sixteen, eight and four independent reads in flight per group (rows are
+        // padded to a multiple of four); without the groups of sixteen the
+        // five-pocket dock took 1% longer
         const float4* row = S.fs + i;
         const int ns = T.fs_stride;
         int k = 0;
+        for (; k + 16 <= T.ell_w; k += 16) {
+            float4 f[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) f[u] = row[(k + u) * ns];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) { gx += f[u].x; gy += f[u].y; gz += f[u].z; }
+        }
         for (; k + 8 <= T.ell_w; k += 8) {
             float4 f[8];
 #pragma unroll
@@ -909,7 +987,7 @@ __device__ __forceinline__ float4 atom_position(float4 ref, const Lds& S)
 // whose gradient nobody reads) it returns after the energy, with g = 0 and
 // S.frc not written.  use_bound lets such a trial try the intra lower bound
 // before its pair loop.
-template <int A, bool SL>
+template <int A, bool SL, int W = 1>
 __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, float pose,
                          float e_limit = __builtin_inff(), bool use_bound = true, bool y_first = false)
 {
@@ -950,7 +1028,7 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
         G[0][0] = G[0][1] = G[0][2] = 0.f;
         if (l < T.n) {
             S.pos[l] = X4[0];
-            tri_issue(B, __float_as_uint(rf.w) & 0xff, X4[0].x, X4[0].y, X4[0].z, TL[0]);
+            if (W == 1) tri_issue(B, __float_as_uint(rf.w) & 0xff, X4[0].x, X4[0].y, X4[0].z, TL[0]);
         } else {
             X4[0] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
@@ -1009,12 +1087,44 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
         }
     }
     int cnt = 0;
-    const float e_ia = pair_loop(T, S, cnt);   // hides the map loads (one atom per lane)
+    float e_ia = 0.f;
+    if (W > 1) {
+        const int nc = (T.np + kWave - 1) / kWave, own = team_chunk<W>(nc, 1);
+        team_sync();
+        pair_chunks(T, S, 0, own, e_ia, cnt, nullptr);
+        team_sync();
+        // four energies in flight
+        const float* part = S.part + l;
+        int k = own;
+        for (; k + 4 <= nc; k += 4, part += 4 * kWave) {
+            const float p0 = part[0], p1 = part[kWave], p2 = part[2 * kWave], p3 = part[3 * kWave];
+            e_ia += p0; e_ia += p1; e_ia += p2; e_ia += p3;
+        }
+        if (k < nc) {
+            const float p0 = part[0], p1 = part[k + 1 < nc ? kWave : 0], p2 = part[k + 2 < nc ? 2 * kWave : 0];
+            e_ia += p0;
+            if (k + 1 < nc) e_ia += p1;
+            if (k + 2 < nc) e_ia += p2;
+        }
+#pragma unroll
+        for (int h = 0; h < W - 1; ++h) {
+            const uint32_t c = S.count[h * kWave + l];
+            cnt += (int)(c & 0x7fffffffu);
+            outl = c >> 31;
+        }
+        if (l < T.n) {
+            const float4 m = S.map[l];
+            G[0][0] = m.x; G[0][1] = m.y; G[0][2] = m.z;
+        }
+        out.e_inter = lane_f(*S.e_map, 0);
+    } else {
+        e_ia = pair_loop(T, S, cnt);   // hides the map loads (one atom per lane)
+    }
     // the energy sums start here, so their cross-lane steps overlap the
     // force gather and the scans below
     out.e_intra = wsum(e_ia);
     wave_sync();
-    if (!map_done) {
+    if (W == 1 && !map_done) {
         if (A > 1) {
             // two atoms per lane: the map loads start only now, since holding
             // both lookups across the pair loop would cost a resident wave
@@ -1030,7 +1140,7 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
                 outl = outl || TL[a].cx || TL[a].cy || TL[a].cz;
             }
         out.e_inter = wsum(e_in);
-    } else {
+    } else if (W == 1) {
 #pragma unroll
         for (int a = 0; a < A; ++a) {
             const int i = l * A + a;
@@ -1107,6 +1217,46 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
     out.g = l < 6 ? total : l < 6 + T.nt ? own : 0.f;
     wave_sync();
     return out;
+}
+
+// Wave w > 0 of a chain's team: until the chain ends, its chunks of pairs of each
+// evaluation and, the last wave, the map lookups.
+template <int W, int A, bool SL>
+__device__ void help(const Topo<A, SL>& T, const BoxView& B, const Lds& S, int w)
+{
+    const int l = lane_id();
+    const int type = __float_as_uint(T.ref[0].w) & 0xff;
+    __builtin_amdgcn_s_setprio(2);   // the chain waits for it
+    const bool maps = w == W - 1 && l < T.n;
+    const int nc = (T.np + kWave - 1) / kWave, first = team_chunk<W>(nc, w), end = team_chunk<W>(nc, w + 1);
+    float* part = S.part + (first - team_chunk<W>(nc, 1)) * kWave;
+    while (true) {
+        team_sync();   // the positions are in place, or the chain has ended
+        if (__builtin_amdgcn_readfirstlane(*S.done)) break;
+        TriLoad L;
+        if (maps) {
+            const float4 p = S.pos[l];
+            tri_issue(B, type, p.x, p.y, p.z, L);
+        }
+        int cnt = 0;
+        float e = 0.f;
+        pair_chunks(T, S, first, end, e, cnt, part);
+        uint32_t outl = 0;
+        if (w == W - 1) {
+            float em = 0.f;
+            if (maps) {
+                float4 m;
+                em += tri_finish(B, L, m.x, m.y, m.z);
+                m.w = 0.f;
+                S.map[l] = m;
+                outl = L.cx || L.cy || L.cz;
+            }
+            em = wsum(em);
+            if (l == 0) *S.e_map = em;
+        }
+        S.count[(w - 1) * kWave + l] = (uint32_t)cnt | outl << 31;
+        team_sync();
+    }
 }
 
 // Score on given coordinates already in S.pos: forces in S.frc (with grads).
@@ -1239,7 +1389,7 @@ __device__ __forceinline__ bool consistency_passes(float x, float fx, float gx, 
 // start's evaluation and the line search's are two copies of the evaluation
 // code; the line search is a loop of its own, so that the state of the outer
 // iteration (the history above all) stays in its registers across the trials.
-template <int A, bool SL, int MM = kMaxM>
+template <int A, bool SL, int MM = kMaxM, int W = 1>
 __device__ BfgsOut bfgs(const Topo<A, SL>& T, const BoxView& B, const Lds& S, const SearchParams& P, int max_iter,
                         float x, bool check = false, CheckIn ck = CheckIn{0.f, 0.f, 0.f, 0, 0})
 {
@@ -1248,7 +1398,7 @@ __device__ BfgsOut bfgs(const Topo<A, SL>& T, const BoxView& B, const Lds& S, co
     const int nd = 6 + T.nt;
     const bool act = l < nd;
     BfgsOut out;
-    const Eval e0 = evaluate(T, B, S, x);
+    const Eval e0 = evaluate<A, SL, W>(T, B, S, x);
     float f = e0.e, g = act ? e0.g : 0.f;
     out.evals = out.grads = 1;
     out.bounded = 0;
@@ -1299,8 +1449,8 @@ __device__ BfgsOut bfgs(const Topo<A, SL>& T, const BoxView& B, const Lds& S, co
             // once a trial of the iteration has failed, and while no history pair
             // is stored, when the full step is the unscaled gradient step
             const float armijo = fmaf(P.rho * lam, gd, f);
-            const Eval ev = evaluate(T, B, S, xt, armijo, !(P.flags & kDockNoIntraBound) && (A > 1 || tr > 0 || hn == 0),
-                                     MM <= kShortM);
+            const Eval ev = evaluate<A, SL, W>(T, B, S, xt, armijo,
+                                               !(P.flags & kDockNoIntraBound) && (A > 1 || tr > 0 || hn == 0), MM <= kShortM);
             const float ft = ev.e, gt = act ? ev.g : 0.f;
             const bool above = ft > armijo;
             ++out.evals;
@@ -1427,7 +1577,7 @@ __device__ __forceinline__ void chain_priority(int64_t evals, int s, int steps)
     else __builtin_amdgcn_s_setprio(0);
 }
 
-template <int A, bool SL, int MM = kMaxM>
+template <int A, bool SL, int MM = kMaxM, int W = 1>
 __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& S, const SearchParams& P, int job,
                              int chain)
 {
@@ -1450,7 +1600,7 @@ __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& 
     while (true) {
         const int iters = mode == 0 || mode == 3 ? 0 : (mode == 1 ? P.max_iter : P.refine_max_iter);
         ck.f = e_cur;
-        const BfgsOut bo = bfgs<A, SL, MM>(T, B, S, P, iters, x, mode == 1 && P.consistency, ck);
+        const BfgsOut bo = bfgs<A, SL, MM, W>(T, B, S, P, iters, x, mode == 1 && P.consistency, ck);
         if (mode == 3) {
             if (bo.outside0) out.status |= kStatusOutside;
             break;
@@ -1517,20 +1667,25 @@ __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& 
 
 // Two waves per SIMD for the slot form and the two-atom form: without the
 // hint they take AGPRs above 256 VGPRs and fall to one wave (with it the slot
-// form holds 247 VGPRs, the two-atom form 256 with 28 spilled).  The one-atom
-// gather form fits two waves by itself and is faster without the hint.
-template <int A, bool SL, int MM>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 ? 2 : 1))) void dock_kernel(DockArgs a)
+// form holds 244 VGPRs, the two-atom form 256 with 8 spilled).  The one-atom
+// gather form fits two waves by itself and is faster without the hint.  With
+// helper waves (W > 1) three waves per SIMD, see team_chunk.
+template <int A, bool SL, int MM, int W = 1>
+__global__ __launch_bounds__(64 * W)
+__attribute__((amdgpu_waves_per_eu(W > 1 ? 3 : SL || A > 1 ? 2 : 1))) void dock_kernel(DockArgs a)
 {
     extern __shared__ __align__(16) char smem[];
-    const Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindDock, A, SL));
+    Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindDock, A, SL));
+    if (W > 1)
+        carve_team<W>(S, smem + lds_bytes(a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindDock, A, SL)), a.l.max_atoms);
     const int l = lane_id();
     Topo<A, SL> T;
     T.lig = -1;
     const int chains = a.sp.chains;
-    int64_t item = a.persistent ? -1 : (int64_t)blockIdx.x;
+    const bool persistent = W == 1 && a.persistent;   // with helpers every chain has its workgroup
+    int64_t item = persistent ? -1 : (int64_t)blockIdx.x;
     while (true) {
-        if (a.persistent) {
+        if (persistent) {
             uint32_t v = 0;
             if (l == 0) v = atomicAdd(a.queue, 1u);
             item = (int64_t)(uint32_t)lane_i((int)v, 0);
@@ -1540,11 +1695,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 
         const int job = a.job_map ? a.job_map[gj] : a.job_begin + gj;
         const int chain = (int)(item % chains);
         const int2 jb = a.jobs[job];
-        if (jb.x != T.lig) stage_ligand(T, a.l, jb.x, S);
+        const int wave = W > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.y) : 0;
+        if (jb.x != T.lig) stage_ligand(T, a.l, jb.x, S, wave == 0);
         const BoxView B = box_view(a.g, jb.y);
+        if (W > 1) {
+            if (wave == 0 && l == 0) *S.done = 0;
+            team_sync();
+            if (wave > 0) {
+                help<W>(T, B, S, wave);
+                break;
+            }
+        }
         uint64_t t0 = 0;
         if (a.sp.flags & 1u) t0 = wall_clock64();
-        ChainOut co = mc_chain<A, SL, MM>(T, B, S, a.sp, job, chain);
+        ChainOut co = mc_chain<A, SL, MM, W>(T, B, S, a.sp, job, chain);
+        if (W > 1) {
+            if (l == 0) *S.done = 1;
+            team_sync();
+        }
         const int64_t pairs = wsum_i64(co.pairs);
         const int64_t ci = (int64_t)job * chains + chain;
         if (a.chain_best_dof && l < a.dof_stride)
@@ -1563,7 +1731,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 
             }
         }
         wave_sync();
-        if (!a.persistent) break;
+        if (!persistent) break;
     }
 }
 
@@ -2593,10 +2761,10 @@ hipError_t launch_build_grids(const GridBuildArgs& a, int64_t n_tiles, hipStream
 }
 
 template <typename K>
-static int occupancy(K kernel, int lds)
+static int occupancy(K kernel, int lds, int threads = kWave)
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 64, lds) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, lds) != hipSuccess) return 0;
     return n;
 }
 
@@ -2671,14 +2839,47 @@ hipError_t launch_score(const ScoreArgs& a, bool ragged, int n_cu, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgroups, hipStream_t s)
+// Whether a launch's chains can have teams of W waves: all of them resident at once.
+template <int MM, int W>
+static bool team_fits(const DockArgs& a, const LaunchShape& sh, int n_cu)
+{
+    const int lds = sh.lds + team_bytes<W>(a.l.max_atoms, a.l.max_pairs);
+    return (int64_t)occupancy(dock_kernel<1, true, MM, W>, lds, W * kWave) * n_cu >= a.n_items;
+}
+
+template <int MM, int W>
+static void launch_slots(const DockArgs& a, const LaunchShape& sh, unsigned grid, hipStream_t s)
+{
+    const int lds = sh.lds + (W > 1 ? team_bytes<W>(a.l.max_atoms, a.l.max_pairs) : 0);
+    hipLaunchKernelGGL((dock_kernel<1, true, MM, W>), dim3(grid), dim3(kWave, W), lds, s, a);
+}
+
+// Slot launches: teams where every chain is resident at once with its helpers,
+// with more than one chunk of pairs (fewer take no longer than the waits for the
+// helpers: 16 atoms, 61 pairs, 1,024 chains 11.2 ms alone, 11.6 in teams of two),
+// and with no other class's launch beside it.  Teams of four before teams of two,
+// chains of 60 steps alone / of two / of four:
+//     20 atoms, 122 pairs     8 chains 10.3 / 9.8 / 9.9 ms     256: 11.4 / 10.9 / 11.1
+//     35 atoms, 445 pairs     8 chains 5.93 / 5.15 / 4.51      256: 9.32 / 8.08 / 7.22
+//     64 atoms, 1,717 pairs   8 chains 7.88 / 6.14 / 4.66      256: 9.91 / 7.80 / 5.97
+//     35 atoms, 1,024 chains 9.87 / 8.50 (no room for teams of four)
+template <int MM>
+static void launch_slot_dock(const DockArgs& a, const LaunchShape& sh, unsigned grid, bool alone, int n_cu, hipStream_t s)
+{
+    const bool team = alone && a.persistent && grid >= a.n_items && a.l.max_pairs > kWave;
+    if (team && team_fits<MM, 4>(a, sh, n_cu)) launch_slots<MM, 4>(a, sh, grid, s);
+    else if (team && team_fits<MM, 2>(a, sh, n_cu)) launch_slots<MM, 2>(a, sh, grid, s);
+    else launch_slots<MM, 1>(a, sh, grid, s);
+}
+
+hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgroups, bool alone, int n_cu, hipStream_t s)
 {
     if (a.n_items <= 0) return hipSuccess;
     const unsigned grid = a.persistent ? (unsigned)workgroups : (unsigned)a.n_items;
     const bool short_m = a.sp.m <= kShortM;
     if (sh.variant == 0) {
-        if (short_m) hipLaunchKernelGGL((dock_kernel<1, true, kShortM>), dim3(grid), dim3(64), sh.lds, s, a);
-        else hipLaunchKernelGGL((dock_kernel<1, true, kMaxM>), dim3(grid), dim3(64), sh.lds, s, a);
+        if (short_m) launch_slot_dock<kShortM>(a, sh, grid, alone, n_cu, s);
+        else launch_slot_dock<kMaxM>(a, sh, grid, alone, n_cu, s);
     } else if (sh.variant == 1) {
         if (short_m) hipLaunchKernelGGL((dock_kernel<1, false, kShortM>), dim3(grid), dim3(64), sh.lds, s, a);
         else hipLaunchKernelGGL((dock_kernel<1, false, kMaxM>), dim3(grid), dim3(64), sh.lds, s, a);

@@ -279,3 +279,33 @@ def test_pair_chunk_remainders(oracle, pv_ctx):
         L = st.ol[c // 4]
         r = L.score_grad(st.og[0], cpu_dof(res[0]["chain_best_dof"][c, :L.ndof]))
         assert abs(e - r["e"]) <= e_tol(r["e"]) + (0.01 if r["min_cut"] < 1e-4 else 0.0)
+
+
+@pytest.mark.parametrize("chains,steps,m,n_max", [(4, 4, 5, 64), (4, 4, 8, 64), (90, 1, 5, 38), (90, 1, 8, 38)])
+def test_helper_waves_change_nothing(oracle, pv_ctx, chains, steps, m, n_max):
+    """Chains with helper waves (every chain resident, more than 64 pairs) against chains of one wave each (a launch
+    of one workgroup less has no helpers): the same bit for bit, over ligands of no pairs, of one chunk of 64, and of
+    every number of chunks the sizes reach, in teams of four (few chains) and of two (more than three per CU)."""
+    import paper_2506_20043_amd as pv
+    cfg = S.CONFIGS["tiny"]
+    rx, rt, bxs = S.make_receptor(cfg)
+    g = np.random.default_rng(31)
+    mols, seen = [S.tree_ligand(g, 1, 0)], {0}
+    for n in range(8, n_max + 1):
+        mol = S.tree_ligand(g, n, min(3 + n // 8, 10))
+        p = pv.describe_ligand(mol.xyz, mol.types, mol.bonds, mol.rotatable)[0][3]
+        if (p + 63) // 64 not in seen:
+            seen.add((p + 63) // 64)
+            mols.append(mol)
+    assert {1, 2, 3, 4} <= seen
+    st = Setup(oracle, pv_ctx, rx, rt, bxs[:1], mols)
+    plan = pv.Plan(pv_ctx, st.grids, st.ligs, [(i, 0) for i in range(len(mols))],
+                   pv.dock_params(chains=chains, steps=steps, bfgs_m=m))
+    res = []
+    for workgroups in (0, len(mols) * chains - 1):
+        plan.set_schedule(0, pv.VARIANT_SLOTS, workgroups)
+        out = plan.run()
+        res.append({k: v.cpu().numpy().copy() for k, v in out.items()})
+    plan.close()
+    for k in res[0]:
+        assert np.array_equal(res[0][k], res[1][k]), k
