@@ -215,6 +215,8 @@ struct LaunchShape {
     int variant;
     int lds;
     int per_cu;
+    bool lean;     // variant 1: a launch of more than full_cu workgroups per CU runs the
+    int full_cu;   // kernels of three waves per SIMD (which need less than lds)
 };
 enum KernelKind { kKindDock = 0, kKindScore = 1, kKindOpt = 2 };
 hipError_t launch_shape(int kind, const LigDev& l, int64_t items, int n_cu, LaunchShape* out);

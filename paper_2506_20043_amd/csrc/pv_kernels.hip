@@ -229,6 +229,31 @@ __device__ __forceinline__ BoxView box_view(const GridDev& g, int box)
     return v;
 }
 
+// Values that are the same in every lane, moved to scalar registers: what a kernel
+// loads after it has stored anything comes by vector loads (the compiler cannot
+// tell that the tables did not change), so a box's and a ligand's numbers would
+// hold some thirty vector registers for a chain's whole life.
+__device__ __forceinline__ void to_scalar(int& v) { v = __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ void to_scalar(float& v) { v = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+template <typename P>
+__device__ __forceinline__ void to_scalar(const P*& p)
+{
+    const uint64_t v = (uint64_t)p;
+    int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
+    to_scalar(lo);
+    to_scalar(hi);
+    p = (const P*)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
+}
+
+__device__ __forceinline__ void to_scalar(BoxView& v)
+{
+    to_scalar(v.maps);
+    to_scalar(v.nx); to_scalar(v.ny); to_scalar(v.nz);
+    v.msz = (int64_t)v.nx * v.ny * v.nz;
+    to_scalar(v.ox); to_scalar(v.oy); to_scalar(v.oz); to_scalar(v.h); to_scalar(v.inv_h);
+    to_scalar(v.ex); to_scalar(v.ey); to_scalar(v.ez);
+}
+
 // One axis of the lookup: fractional coordinate clamped to [0, n-1], cell
 // i0 = min(floor f, n-2), the out-of-box penalty and whether the axis is
 // clamped (its interpolant gradient is then zero).
@@ -386,6 +411,7 @@ __host__ __device__ inline int lds_atoms(int max_atoms) { return round_up(max_at
 struct LdsNeeds {
     bool slots, frc, frames;
     bool pw;   // gather layout: the pair words in LDS too (one atom per lane), else read from global memory
+    bool lean; // nothing but what the kernel uses (three waves per SIMD, see kLean)
 };
 
 // Bytes that no region uses.  They keep the sizes, and with them the choice
@@ -397,8 +423,8 @@ constexpr int kLdsSpare = 5 * kSlot * 4;
 __host__ __device__ inline int lds_bytes(int max_atoms, int max_pairs, int max_ell, LdsNeeds nd)
 {
     const int ma = lds_atoms(max_atoms);
-    int b = kLdsSpare + (ma + 1) * 16 + 6 * ma * 4;
-    b += nd.frames ? kMaxFrag * 13 * 4 + 12 : round_up(kMaxFrag, 4) * 4;
+    int b = (nd.lean ? 0 : kLdsSpare) + (ma + 1) * 16 + 6 * ma * 4;
+    b += nd.frames ? kMaxFrag * 13 * 4 + 12 : nd.lean ? 0 : round_up(kMaxFrag, 4) * 4;
     if (nd.frc) b += ma * 16;
     if (nd.slots) b += round_up(max_pairs < 1 ? 1 : max_pairs, kPairPass) * 16 + (max_ell + 1) * 16;
     else b += (nd.pw ? 2 : 1) * round_up(max_pairs + 1, kWave) * 4;
@@ -416,7 +442,7 @@ __device__ __forceinline__ Lds carve(char* base, int max_atoms, int max_pairs, i
     s.pre = (float*)p; p += 6 * ma * 4;
     s.frc = nullptr;
     if (nd.frc) { s.frc = (float4*)p; p += ma * 16; }
-    s.frame = (float*)p; p += nd.frames ? kMaxFrag * 13 * 4 + 12 : round_up(kMaxFrag, 4) * 4;
+    s.frame = (float*)p; p += nd.frames ? kMaxFrag * 13 * 4 + 12 : nd.lean ? 0 : round_up(kMaxFrag, 4) * 4;
     s.pairs = nullptr; s.fs = nullptr; s.cp = nullptr; s.pw = nullptr;
     if (nd.slots) {
         s.pairs = (uint4*)p; p += round_up(max_pairs < 1 ? 1 : max_pairs, kPairPass) * 16;
@@ -444,7 +470,7 @@ __device__ __forceinline__ Lds carve(char* base, int max_atoms, int max_pairs, i
 template <int W>
 __host__ __device__ inline int team_chunk(int nc, int w)
 {
-    if constexpr (W == 1) return w * nc;
+    if constexpr (W <= 1) return w * nc;
     else {
         const int last = nc > 3 * (W - 1) ? (nc - 3 * (W - 1)) / W : 0, rest = nc - last;
         return w == W ? nc : (rest * w + W - 2) / (W - 1);
@@ -476,10 +502,22 @@ __device__ __forceinline__ void carve_team(Lds& s, char* p, int max_atoms)
 // per lane the pair lists are long and the words stay in global memory, so
 // that LDS does not cut the resident waves).
 constexpr int kKindOutput = 3;
-__host__ __device__ inline LdsNeeds kernel_needs(int kind, int A, bool slots)
+__host__ __device__ inline LdsNeeds kernel_needs(int kind, int A, bool slots, bool lean = false)
 {
-    return LdsNeeds{slots, kind == kKindScore, A > 1 || kind == kKindOutput, !slots && A == 1};
+    return LdsNeeds{slots, kind == kKindScore, A > 1 || kind == kKindOutput, !slots && A == 1, lean};
 }
+
+// Team size (template argument W) 0: one wave per chain, built for three waves per
+// SIMD.  The gather form with one atom per lane holds about 230 VGPRs, two waves,
+// and these keep the vector units 65% busy; with the map lookups ended before
+// the pair loop, the uniform numbers in scalar registers and the rest spilled (20
+// to 40 registers, in the code around the evaluations) it fits 168.  16,384 poses
+// of local optimisation 3.14 -> 2.59 ms; screens of 8-40 atoms 494 -> 406 ms, of
+// 30-50 atoms 392 -> 326 ms.  Used where a launch has more waves than two per
+// SIMD and the LDS holds twelve per CU: with nine (ligands of up to 64 atoms) a
+// screen took 5% longer, and with the pair words left in global memory to make
+// room for twelve 20% (the optimisation 2.80 ms).
+constexpr int kLean = 0;
 
 // Least value over all surface distances of a pair's energy, by class (the
 // Vina terms above: plain at d = 0.003, hydrophobic at d = 0.003, hydrogen
@@ -508,6 +546,15 @@ struct Topo {
     const uint32_t* gpairs;   // pair list and atom -> pair table in global
     const uint32_t* gell;     // memory (read from there when A > 1)
 };
+
+template <int A, bool SL>
+__device__ __forceinline__ void to_scalar(Topo<A, SL>& T)
+{
+    to_scalar(T.n); to_scalar(T.nf); to_scalar(T.nt); to_scalar(T.np); to_scalar(T.rounds); to_scalar(T.ell_w);
+    T.fs_stride = T.n | 1;
+    to_scalar(T.rot_scale); to_scalar(T.lb); to_scalar(T.np0); to_scalar(T.np1);
+    to_scalar(T.gpairs); to_scalar(T.gell);
+}
 
 template <int A, bool SL>
 __device__ void stage_ligand(Topo<A, SL>& T, const LigDev& L, int lig, const Lds& S, bool fill = true)
@@ -1053,8 +1100,8 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
     // always runs both.
     const bool bound = !SL && use_bound && e_limit < 3.0e38f;   // wave-uniform
     bool outl = false, map_done = false;
-    if (bound) {
-        if (A > 1) {
+    if (W == kLean || bound) {
+        if (A > 1 || W == kLean) {
 #pragma unroll
             for (int a = 0; a < A; ++a)
                 if (l * A + a < T.n)
@@ -1068,7 +1115,7 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
             }
         out.e_inter = wsum(e_in);
         map_done = true;
-        if (out.e_inter + T.lb > e_limit + 1e-3f + 1e-4f * (fabsf(out.e_inter) + fabsf(T.lb))) {
+        if (bound && out.e_inter + T.lb > e_limit + 1e-3f + 1e-4f * (fabsf(out.e_inter) + fabsf(T.lb))) {
             out.e_intra = T.lb;
             out.e = out.e_inter + T.lb;
             out.pairs_in = 0;
@@ -1124,7 +1171,7 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
     // force gather and the scans below
     out.e_intra = wsum(e_ia);
     wave_sync();
-    if (W == 1 && !map_done) {
+    if (W <= 1 && !map_done) {
         if (A > 1) {
             // two atoms per lane: the map loads start only now, since holding
             // both lookups across the pair loop would cost a resident wave
@@ -1140,7 +1187,7 @@ __device__ Eval evaluate(const Topo<A, SL>& T, const BoxView& B, const Lds& S, f
                 outl = outl || TL[a].cx || TL[a].cy || TL[a].cz;
             }
         out.e_inter = wsum(e_in);
-    } else if (W == 1) {
+    } else if (W <= 1) {
 #pragma unroll
         for (int a = 0; a < A; ++a) {
             const int i = l * A + a;
@@ -1671,18 +1718,18 @@ __device__ ChainOut mc_chain(const Topo<A, SL>& T, const BoxView& B, const Lds& 
 // gather form fits two waves by itself and is faster without the hint.  With
 // helper waves (W > 1) three waves per SIMD, see team_chunk.
 template <int A, bool SL, int MM, int W = 1>
-__global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(W > 1 ? 3 : SL || A > 1 ? 2 : 1))) void dock_kernel(DockArgs a)
+__global__ __launch_bounds__(64 * (W > 1 ? W : 1))
+__attribute__((amdgpu_waves_per_eu(W != 1 ? 3 : SL || A > 1 ? 2 : 1))) void dock_kernel(DockArgs a)
 {
     extern __shared__ __align__(16) char smem[];
-    Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindDock, A, SL));
+    Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindDock, A, SL, W == kLean));
     if (W > 1)
         carve_team<W>(S, smem + lds_bytes(a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindDock, A, SL)), a.l.max_atoms);
     const int l = lane_id();
     Topo<A, SL> T;
     T.lig = -1;
     const int chains = a.sp.chains;
-    const bool persistent = W == 1 && a.persistent;   // with helpers every chain has its workgroup
+    const bool persistent = W <= 1 && a.persistent;   // with helpers every chain has its workgroup
     int64_t item = persistent ? -1 : (int64_t)blockIdx.x;
     while (true) {
         if (persistent) {
@@ -1697,7 +1744,11 @@ __attribute__((amdgpu_waves_per_eu(W > 1 ? 3 : SL || A > 1 ? 2 : 1))) void dock_
         const int2 jb = a.jobs[job];
         const int wave = W > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.y) : 0;
         if (jb.x != T.lig) stage_ligand(T, a.l, jb.x, S, wave == 0);
-        const BoxView B = box_view(a.g, jb.y);
+        BoxView B = box_view(a.g, jb.y);
+        if (W == kLean) {
+            to_scalar(T);
+            to_scalar(B);
+        }
         if (W > 1) {
             if (wave == 0 && l == 0) *S.done = 0;
             team_sync();
@@ -1918,11 +1969,12 @@ hipError_t launch_scale_grad(const LigDev& l, int64_t n, int row, const int32_t*
     return hipGetLastError();
 }
 
-template <int A, bool SL>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 ? 2 : 1))) void local_opt_kernel(OptArgs a)
+template <int A, bool SL, int W = 1>
+__global__ __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(W == kLean ? 3 : SL || A > 1 ? 2 : 1))) void local_opt_kernel(OptArgs a)
 {
     extern __shared__ __align__(16) char smem[];
-    const Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOpt, A, SL));
+    const Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindOpt, A, SL, W == kLean));
     const int l = lane_id();
     Topo<A, SL> T;
     T.lig = -1;
@@ -1933,13 +1985,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(SL || A > 1 
             continue;
         }
         if (lig != T.lig) stage_ligand(T, a.l, lig, S);
-        const BoxView B = box_view(a.g, box);
+        BoxView B = box_view(a.g, box);
+        if (W == kLean) {
+            to_scalar(T);
+            to_scalar(B);
+        }
         float v = l < 7 + T.nt ? a.dof_in[(int64_t)pose * a.dof_stride + l] : 0.f;
         // normalise the quaternion once so the run starts from a unit q
         float q0 = lane_f(v, 3), q1 = lane_f(v, 4), q2 = lane_f(v, 5), q3 = lane_f(v, 6);
         const float qn = rsqrtf(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
         if (l >= 3 && l < 7) v *= qn;
-        const BfgsOut bo = bfgs(T, B, S, a.sp, a.sp.max_iter, v);
+        const BfgsOut bo = bfgs<A, SL, kMaxM, W>(T, B, S, a.sp, a.sp.max_iter, v);
         if (l < a.dof_stride) a.dof_out[(int64_t)pose * a.dof_stride + l] = l < 7 + T.nt ? bo.x : 0.f;
         if (l == 0) {
             if (a.energy) a.energy[pose] = bo.f;
@@ -2778,16 +2834,35 @@ static int kind_occupancy(int kind, int lds)
     return occupancy(local_opt_kernel<A, SL>, lds);
 }
 
+static int lean_lds(int kind, const LigDev& l)
+{
+    return lds_bytes(l.max_atoms, l.max_pairs, l.max_ell, kernel_needs(kind, 1, false, true));
+}
+
+// The gather form's shape: of the lean kernels where three of their waves fit a SIMD.
+static LaunchShape gather_shape(int kind, const LigDev& l, int lds, int occ)
+{
+    LaunchShape s = {1, lds, occ, false, occ};
+    if (kind == kKindScore) return s;
+    const int ll = lean_lds(kind, l);
+    const int lean = kind == kKindOpt ? occupancy(local_opt_kernel<1, false, kLean>, ll)
+                                      : std::min(occupancy(dock_kernel<1, false, kShortM, kLean>, ll),
+                                                 occupancy(dock_kernel<1, false, kMaxM, kLean>, ll));
+    s.lean = lean >= 12;
+    if (s.lean) s.per_cu = lean;
+    return s;
+}
+
 // Slots are faster per evaluation but take 16 B per pair end in LDS; they
 // are used while the CUs can still hold as many of the launch's waves as the
-// gather layout would (a persistent launch over few chains, or small
+// gather layout would at two waves per SIMD (a persistent launch over few chains, or small
 // ligands), else the gather layout keeps the occupancy.
 hipError_t launch_shape(int kind, const LigDev& l, int64_t items, int n_cu, LaunchShape* out)
 {
     const int64_t cus = n_cu > 0 ? n_cu : 1;
     if (l.max_atoms > 64) {
         const int lds = lds_bytes(l.max_atoms, l.max_pairs, l.max_ell, kernel_needs(kind, 2, false));
-        *out = {2, lds, kind_occupancy<2, false>(kind, lds)};
+        *out = {2, lds, kind_occupancy<2, false>(kind, lds), false, 0};
         return out->per_cu > 0 ? hipSuccess : hipErrorInvalidConfiguration;
     }
     const int lds_s = lds_bytes(l.max_atoms, l.max_pairs, l.max_ell, kernel_needs(kind, 1, true));
@@ -2796,22 +2871,23 @@ hipError_t launch_shape(int kind, const LigDev& l, int64_t items, int n_cu, Laun
     const int occ_g = kind_occupancy<1, false>(kind, lds_g);
     const int64_t need = std::min<int64_t>(items > 0 ? items : 1, (int64_t)occ_g * cus);
     if (occ_s > 0 && (int64_t)occ_s * cus >= need)
-        *out = {0, lds_s, occ_s};
+        *out = {0, lds_s, occ_s, false, 0};
     else
-        *out = {1, lds_g, occ_g};
+        *out = gather_shape(kind, l, lds_g, occ_g);
     return out->per_cu > 0 ? hipSuccess : hipErrorInvalidConfiguration;
 }
 
 hipError_t launch_shape_variant(int kind, const LigDev& l, int variant, LaunchShape* out)
 {
-    *out = {variant, 0, 0};
+    *out = {variant, 0, 0, false, 0};
     if (variant < 0 || variant > 2 || (variant < 2 && l.max_atoms > 64)) return hipErrorInvalidValue;
     const int lds = lds_bytes(l.max_atoms, l.max_pairs, l.max_ell, kernel_needs(kind, variant == 2 ? 2 : 1, variant == 0));
     int occ;
     if (variant == 0) occ = kind_occupancy<1, true>(kind, lds);
     else if (variant == 1) occ = kind_occupancy<1, false>(kind, lds);
     else occ = kind_occupancy<2, false>(kind, lds);
-    *out = {variant, lds, occ};
+    *out = {variant, lds, occ, false, 0};
+    if (variant == 1 && occ > 0) *out = gather_shape(kind, l, lds, occ);
     return occ > 0 ? hipSuccess : hipErrorInvalidConfiguration;
 }
 
@@ -2880,6 +2956,10 @@ hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgro
     if (sh.variant == 0) {
         if (short_m) launch_slot_dock<kShortM>(a, sh, grid, alone, n_cu, s);
         else launch_slot_dock<kMaxM>(a, sh, grid, alone, n_cu, s);
+    } else if (sh.variant == 1 && sh.lean && grid > (int64_t)sh.full_cu * n_cu) {
+        const int lds = lean_lds(kKindDock, a.l);
+        if (short_m) hipLaunchKernelGGL((dock_kernel<1, false, kShortM, kLean>), dim3(grid), dim3(64), lds, s, a);
+        else hipLaunchKernelGGL((dock_kernel<1, false, kMaxM, kLean>), dim3(grid), dim3(64), lds, s, a);
     } else if (sh.variant == 1) {
         if (short_m) hipLaunchKernelGGL((dock_kernel<1, false, kShortM>), dim3(grid), dim3(64), sh.lds, s, a);
         else hipLaunchKernelGGL((dock_kernel<1, false, kMaxM>), dim3(grid), dim3(64), sh.lds, s, a);
@@ -2927,6 +3007,8 @@ hipError_t launch_local_opt(const OptArgs& a, int n_cu, hipStream_t s)
     const int grid = a.n_poses < 65536 ? a.n_poses : 65536;
     if (sh.variant == 0)
         hipLaunchKernelGGL((local_opt_kernel<1, true>), dim3(grid), dim3(64), sh.lds, s, a);
+    else if (sh.variant == 1 && sh.lean && a.n_poses > (int64_t)sh.full_cu * n_cu)
+        hipLaunchKernelGGL((local_opt_kernel<1, false, kLean>), dim3(grid), dim3(64), lean_lds(kKindOpt, a.l), s, a);
     else if (sh.variant == 1)
         hipLaunchKernelGGL((local_opt_kernel<1, false>), dim3(grid), dim3(64), sh.lds, s, a);
     else

@@ -309,3 +309,45 @@ def test_helper_waves_change_nothing(oracle, pv_ctx, chains, steps, m, n_max):
     plan.close()
     for k in res[0]:
         assert np.array_equal(res[0][k], res[1][k]), k
+
+
+@pytest.mark.parametrize("m", [5, 8])
+def test_three_waves_per_simd_change_nothing(oracle, pv_ctx, m):
+    """Launches of more than eight one-wave workgroups per CU run the gather form built for twelve: docks against the
+    same plan at eight per CU, a local optimisation against its first poses alone; bit for bit, over ligands of no
+    pairs, of one chunk of 64, and of every number of chunks the sizes reach."""
+    import torch
+    import paper_2506_20043_amd as pv
+    n8 = 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    cfg = S.CONFIGS["tiny"]
+    rx, rt, bxs = S.make_receptor(cfg)
+    g = np.random.default_rng(37)
+    mols, seen = [S.tree_ligand(g, 1, 0)], {0}
+    for n in range(8, 45):
+        mol = S.tree_ligand(g, n, min(3 + n // 8, 10))
+        p = pv.describe_ligand(mol.xyz, mol.types, mol.bonds, mol.rotatable)[0][3]
+        if (p + 63) // 64 not in seen:
+            seen.add((p + 63) // 64)
+            mols.append(mol)
+    assert {1, 2, 3, 4, 5} <= seen
+    st = Setup(oracle, pv_ctx, rx, rt, bxs[:1], mols)
+    chains = n8 // len(mols) + 40
+    assert pv.launch_info(pv_ctx, st.ligs, pv.KIND_DOCK, len(mols) * chains)[::2] == (pv.VARIANT_GATHER, 12)
+    plan = pv.Plan(pv_ctx, st.grids, st.ligs, [(i, 0) for i in range(len(mols))],
+                   pv.dock_params(chains=chains, steps=1, bfgs_m=m))
+    res = []
+    for workgroups in (0, n8):
+        plan.set_schedule(0, pv.VARIANT_GATHER, workgroups)
+        res.append({k: v.cpu().numpy().copy() for k, v in plan.run().items()})
+    plan.close()
+    for k in res[0]:
+        assert np.array_equal(res[0][k], res[1][k]), k
+    n = n8 + 77
+    assert pv.launch_info(pv_ctx, st.ligs, pv.KIND_LOCAL_OPT, n8)[::2] == (pv.VARIANT_GATHER, 12)
+    dims, org = st.grids.info(0)
+    dof = S.poses(g, n, org + 3.0, org + 0.375 * (dims - 1) - 3.0, 32).astype(np.float32)
+    lig, box = np.arange(n, dtype=np.int32) % len(mols), np.zeros(n, np.int32)
+    many = pv.local_opt(pv_ctx, st.grids, st.ligs, lig, box, dof, pv.dock_params(bfgs_m=m))
+    few = pv.local_opt(pv_ctx, st.grids, st.ligs, lig[:n8], box[:n8], dof[:n8], pv.dock_params(bfgs_m=m))
+    for a, b in zip(many, few):
+        assert np.array_equal(a[:n8].cpu().numpy(), b.cpu().numpy())
