@@ -234,7 +234,10 @@ __device__ __forceinline__ BoxView box_view(const GridDev& g, int box)
 // tell that the tables did not change), so a box's and a ligand's numbers would
 // hold some thirty vector registers for a chain's whole life.
 __device__ __forceinline__ void to_scalar(int& v) { v = __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ void to_scalar(float& v) { v = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+__device__ __forceinline__ void to_scalar(float& v)
+{
+    v = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
 template <typename P>
 __device__ __forceinline__ void to_scalar(const P*& p)
 {
@@ -928,7 +931,8 @@ __device__ __forceinline__ float pair_loop(const Topo<A, SL>& T, const Lds& S, i
 // entry holds p's byte offset in S.cp in its low half and j's in S.pos in its high half.
 // The chunks [k, end) of 64 pairs; their energies go to part where it is given.
 template <int A, bool SL>
-__device__ __forceinline__ void pair_chunks(const Topo<A, SL>& T, const Lds& S, int k, int end, float& e, int& cnt, float* part)
+__device__ __forceinline__ void pair_chunks(const Topo<A, SL>& T, const Lds& S, int k, int end, float& e, int& cnt,
+                                            float* part)
 {
     const int first = k;
     auto to = [&] { return part ? part + (k - first) * kWave : nullptr; };
@@ -1722,9 +1726,9 @@ __global__ __launch_bounds__(64 * (W > 1 ? W : 1))
 __attribute__((amdgpu_waves_per_eu(W != 1 ? 3 : SL || A > 1 ? 2 : 1))) void dock_kernel(DockArgs a)
 {
     extern __shared__ __align__(16) char smem[];
-    Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindDock, A, SL, W == kLean));
-    if (W > 1)
-        carve_team<W>(S, smem + lds_bytes(a.l.max_atoms, a.l.max_pairs, a.l.max_ell, kernel_needs(kKindDock, A, SL)), a.l.max_atoms);
+    const LdsNeeds nd = kernel_needs(kKindDock, A, SL, W == kLean);
+    Lds S = carve(smem, a.l.max_atoms, a.l.max_pairs, a.l.max_ell, nd);
+    if (W > 1) carve_team<W>(S, smem + lds_bytes(a.l.max_atoms, a.l.max_pairs, a.l.max_ell, nd), a.l.max_atoms);
     const int l = lane_id();
     Topo<A, SL> T;
     T.lig = -1;
