@@ -321,9 +321,12 @@ void pv_plan_free(pv_plan* plan);
 /* Schedules.  A plan splits its jobs into size classes (ligands of at most
  * 64 atoms first, larger ones second; classes without jobs are left out),
  * and each class runs one persistent launch of pv_dock_run.  Its schedule:
- * the kernel variant (PV_VARIANT_*, below), the launch width in one-wave
- * workgroups and, reported only, the dynamic LDS bytes per workgroup, the
- * workgroups one CU holds and the class's job count.  The plan starts from
+ * the kernel variant (PV_VARIANT_*, below), the launch width in
+ * workgroups (one wave each; where the width covers every chain and no other
+ * class runs beside it, a chain's workgroup may have helper waves) and, reported only,
+ * the dynamic LDS bytes per workgroup, the workgroups one CU holds and the
+ * class's job count.  A launch of the gather variant wider than eight
+ * workgroups per CU may take less LDS than reported.  The plan starts from
  * the occupancy model of pv_launch_info; pv_dock_run_plain always uses that
  * model for its per-job launches. */
 typedef struct {

@@ -1079,7 +1079,7 @@ pv_status pv_dock_run_plain(pv_plan* P, const pv_dock_out* o, void* stream)
         a.job_begin = j;
         a.n_items = P->sp.chains;
         a.persistent = 0;
-        HIP_TRY(launch_dock(a, G.plain_shape, 0, false, P->ctx->n_cu, s), "dock launch");
+        HIP_TRY(launch_dock(a, G.plain_shape, 0, true, P->ctx->n_cu, s), "dock launch");
     }
     if (o->job_best_e || o->job_best_chain || o->job_evals || o->job_status)
         HIP_TRY(launch_job_reduce(cbe, cev, cst, P->n_jobs, P->sp.chains, o->job_best_e, o->job_best_chain,

@@ -2946,7 +2946,7 @@ static void launch_slots(const DockArgs& a, const LaunchShape& sh, unsigned grid
 template <int MM>
 static void launch_slot_dock(const DockArgs& a, const LaunchShape& sh, unsigned grid, bool alone, int n_cu, hipStream_t s)
 {
-    const bool team = alone && a.persistent && grid >= a.n_items && a.l.max_pairs > kWave;
+    const bool team = alone && grid >= a.n_items && a.l.max_pairs > kWave;
     if (team && team_fits<MM, 4>(a, sh, n_cu)) launch_slots<MM, 4>(a, sh, grid, s);
     else if (team && team_fits<MM, 2>(a, sh, n_cu)) launch_slots<MM, 2>(a, sh, grid, s);
     else launch_slots<MM, 1>(a, sh, grid, s);

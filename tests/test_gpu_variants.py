@@ -284,7 +284,7 @@ def test_pair_chunk_remainders(oracle, pv_ctx):
 @pytest.mark.parametrize("chains,steps,m,n_max", [(4, 4, 5, 64), (4, 4, 8, 64), (90, 1, 5, 38), (90, 1, 8, 38)])
 def test_helper_waves_change_nothing(oracle, pv_ctx, chains, steps, m, n_max):
     """Chains with helper waves (every chain resident, more than 64 pairs) against chains of one wave each (a launch
-    of one workgroup less has no helpers): the same bit for bit, over ligands of no pairs, of one chunk of 64, and of
+    of one workgroup less has no helpers), and against one launch per job: the same bit for bit, over ligands of no pairs, of one chunk of 64, and of
     every number of chunks the sizes reach, in teams of four (few chains) and of two (more than three per CU)."""
     import paper_2506_20043_amd as pv
     cfg = S.CONFIGS["tiny"]
@@ -306,9 +306,11 @@ def test_helper_waves_change_nothing(oracle, pv_ctx, chains, steps, m, n_max):
         plan.set_schedule(0, pv.VARIANT_SLOTS, workgroups)
         out = plan.run()
         res.append({k: v.cpu().numpy().copy() for k, v in out.items()})
+    out = plan.run(plain=True)
+    res.append({k: v.cpu().numpy().copy() for k, v in out.items()})
     plan.close()
     for k in res[0]:
-        assert np.array_equal(res[0][k], res[1][k]), k
+        assert np.array_equal(res[0][k], res[1][k]) and np.array_equal(res[0][k], res[2][k]), k
 
 
 @pytest.mark.parametrize("m", [5, 8])
