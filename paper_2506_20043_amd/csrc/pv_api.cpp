@@ -26,8 +26,12 @@ pv_status fail(pv_status s, const std::string& msg)
     return s;
 }
 
+// Reports a HIP error.  The runtime keeps a failed call's error until it is asked
+// for, and every launch asks: it is taken here, so that the next launch does not
+// report it once more.
 pv_status hip_fail(hipError_t e, const char* what)
 {
+    (void)hipGetLastError();
     g_err = std::string(what) + ": " + hipGetErrorString(e);
     return e == hipErrorOutOfMemory ? PV_E_NOMEM : PV_E_DEVICE;
 }
@@ -116,7 +120,10 @@ pv_status upload(T** dst, const T* src, size_t n, const char* what)
     *dst = nullptr;
     if (n == 0) n = 1;  // keep a valid pointer for empty tables
     hipError_t e = hipMalloc((void**)dst, n * sizeof(T));
-    if (e == hipErrorOutOfMemory && drop_spare()) e = hipMalloc((void**)dst, n * sizeof(T));
+    if (e == hipErrorOutOfMemory && drop_spare()) {
+        (void)hipGetLastError();   // of the first attempt: see hip_fail
+        e = hipMalloc((void**)dst, n * sizeof(T));
+    }
     if (e != hipSuccess) return hip_fail(e, what);
     if (src) {
         e = hipMemcpy(*dst, src, n * sizeof(T), hipMemcpyHostToDevice);

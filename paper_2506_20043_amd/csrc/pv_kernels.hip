@@ -2824,7 +2824,10 @@ template <typename K>
 static int occupancy(K kernel, int lds, int threads = kWave)
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, lds) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, lds) != hipSuccess) {
+        (void)hipGetLastError();   // answered by 0: the launch that follows must not report it
+        return 0;
+    }
     return n;
 }
 

@@ -1,0 +1,49 @@
+"""CPU tests of the library's host code on a HIP runtime without a device
+(fake_hip.cpp): allocations that fail, launches' sizes, what is called while a
+stream captures."""
+import ctypes as C
+
+import pytest
+
+import fake_hip
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = fake_hip.build(tmp_path_factory.mktemp("fake_hip"))
+    return lambda scenario: fake_hip.run(so, "test_host_path", scenario.__name__)
+
+
+# ---------------------------------------------------------------- memory
+def recovered_allocation(f):
+    """An allocation that succeeds once the kept map block is freed leaves no error
+    behind: the launch after it does not report one."""
+    ctx = f.context()
+    f.grids(ctx).close()
+    kept = f.rt.fake_used()
+    assert kept >= 21 ** 3 * 32
+    # room for the tables of two atoms' worth of boxes only when the block goes
+    from paper_2506_20043_amd import synth as S
+    import numpy as np
+    f.rt.fake_memory(kept + 64)
+    ligs = f.pv.Ligands(ctx, [S.tree_ligand(np.random.default_rng(0), 12, 2)])
+    assert f.rt.fake_used() < kept
+    f.rt.fake_memory(1 << 40)
+    assert f.lib.pv_fma_peak(ctx.h, 1, 1 << 20, 256, None) == 0, f.lib.pv_last_error()
+    ligs.close()
+
+
+def failed_allocation(f):
+    """Nor does one that fails: once there is room the same call succeeds."""
+    ctx = f.context()
+    f.rt.fake_memory(1000)
+    assert f.grids(ctx) == -3
+    f.rt.fake_memory(1 << 40)
+    g = f.grids(ctx)
+    assert g != -4, f.lib.pv_last_error()
+    g.close()
+
+
+@pytest.mark.parametrize("scenario", [recovered_allocation, failed_allocation], ids=lambda s: s.__name__)
+def test_allocation_errors_are_not_left_behind(fake, scenario):
+    fake(scenario)
