@@ -42,9 +42,12 @@ pv_status hip_fail(hipError_t e, const char* what)
         if (_e != hipSuccess) return hip_fail(_e, what);    \
     } while (0)
 
-void dfree(void* p)
+// whether the block is freed (hipFree may be refused while a stream captures)
+bool dfree(void* p)
 {
-    if (p) (void)hipFree(p);
+    if (!p || hipFree(p) == hipSuccess) return true;
+    (void)hipGetLastError();   // see hip_fail
+    return false;
 }
 
 // The maps of a pocket set take 5 to 700 MB, and giving such a block back to the
@@ -52,8 +55,10 @@ void dfree(void* p)
 // tenth of a screening receptor's build.  The last block freed on a device is
 // kept for the next build that fits it: one block of at most kSpareMax bytes per
 // device, freed with the device's last context, when a build needs another size
-// or when an allocation fails.  A block enters the cache only after everything
-// on the device has completed, as hipFree ensures by itself.
+// or when an allocation fails.  A block is kept only after everything on the
+// device has completed: the grids' other block is freed first, and hipFree waits
+// for the device.  Where that is refused (a stream is capturing) the maps are
+// freed like it; a wait of its own would be one more call that a capture forbids.
 constexpr size_t kSpareMax = (size_t)1 << 30;
 constexpr int kMaxDevices = 64;
 
@@ -100,11 +105,12 @@ bool drop_spare()
     return had;
 }
 
-// keeps a block (of the current device) as the spare one, or frees it
-void give_spare(int device, void* p, size_t n)
+// keeps a block as the device's spare one, or frees it; idle: the device has
+// completed everything that may use it
+void give_spare(int device, void* p, size_t n, bool idle)
 {
     SpareBlock* s = p ? spare_of(device) : nullptr;
-    if (s && n <= kSpareMax && hipDeviceSynchronize() == hipSuccess) {
+    if (s && n <= kSpareMax && idle) {
         std::lock_guard<std::mutex> lock(s->mu);
         if (s->contexts > 0) {
             std::swap(p, s->p);
@@ -537,8 +543,8 @@ void pv_grids_free(pv_grids* g)
 {
     if (!g) return;
     (void)hipSetDevice(g->device);
-    give_spare(g->device, g->maps, g->maps_bytes);
-    dfree(g->tables);
+    const bool idle = g->tables && dfree(g->tables);
+    give_spare(g->device, g->maps, g->maps_bytes, idle);
     delete g;
 }
 

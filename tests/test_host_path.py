@@ -47,3 +47,25 @@ def failed_allocation(f):
 @pytest.mark.parametrize("scenario", [recovered_allocation, failed_allocation], ids=lambda s: s.__name__)
 def test_allocation_errors_are_not_left_behind(fake, scenario):
     fake(scenario)
+
+
+# ---------------------------------------------------------------- captures
+def free_during_capture(f):
+    """Freeing grids while a stream captures makes no call that waits for the device, keeps no block that the device
+    may still use, and leaves no error behind."""
+    ctx = f.context()
+    a, b = f.grids(ctx), f.grids(ctx)
+    f.rt.fake_capture(1)
+    a.close()
+    assert f.rt.fake_device_syncs() == 0
+    assert f.lib.pv_fma_peak(ctx.h, 1, 1 << 20, 256, None) == 0, f.lib.pv_last_error()
+    f.rt.fake_capture(0)
+    used = f.rt.fake_used()
+    c = f.grids(ctx)   # the block of `a` was not kept: this build allocates
+    assert f.rt.fake_used() > used + 21 ** 3 * 32
+    b.close()
+    c.close()
+
+
+def test_grids_freed_during_a_capture(fake):
+    fake(free_during_capture)
