@@ -1948,28 +1948,32 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(A == 1 && !S
 }
 
 // The backward of a score whose gradient the forward computed: each row times
-// its pose's upstream factor, one thread per value.  Values past the ligand's
+// its pose's upstream factor, a value per thread and round.  Values past the ligand's
 // own (7 + torsions of a pose vector, 3 per atom of coordinates) are 0, or NaN
 // where the pose's ligand or box does not exist, and stay so whatever the
 // factor.  16,384 poses of 17 values take 3 us; evaluating them again took 63.
 __global__ __launch_bounds__(256) void scale_grad_kernel(LigDev L, int64_t n, int row, const int32_t* lig_of_pose,
                                                          bool of_xyz, const float* grad, const float* scale, float* out)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int pose = (int)(i / row), k = (int)(i % row), lig = lig_of_pose[pose];
-    const float v = grad[i];
-    int own = 0;
-    if (lig >= 0 && lig < L.n_lig) own = of_xyz ? 3 * L.ligs[lig].n_atoms : 7 + L.ligs[lig].n_tors;
-    out[i] = k < own ? v * scale[pose] : v;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const int pose = (int)(i / row), k = (int)(i % row), lig = lig_of_pose[pose];
+        const float v = grad[i];
+        int own = 0;
+        if (lig >= 0 && lig < L.n_lig) own = of_xyz ? 3 * L.ligs[lig].n_atoms : 7 + L.ligs[lig].n_tors;
+        out[i] = k < own ? v * scale[pose] : v;
+    }
 }
+
+// a launch may not have 2^32 threads in a dimension: from 2^31 values on a thread takes several
+constexpr int64_t kScaleBlocks = (int64_t)1 << 23;
 
 hipError_t launch_scale_grad(const LigDev& l, int64_t n, int row, const int32_t* lig_of_pose, bool of_xyz,
                              const float* grad, const float* scale, float* out, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(scale_grad_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, l, n, row, lig_of_pose,
-                       of_xyz, grad, scale, out);
+    const int64_t blocks = std::min<int64_t>((n + 255) / 256, kScaleBlocks);
+    hipLaunchKernelGGL(scale_grad_kernel, dim3((unsigned)blocks), dim3(256), 0, s, l, n, row, lig_of_pose, of_xyz, grad,
+                       scale, out);
     return hipGetLastError();
 }
 

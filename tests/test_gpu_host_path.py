@@ -81,3 +81,20 @@ def test_freed_maps_are_not_reused_while_a_stream_reads_them(ctx):
     got = dock(free_and_build)
     for k in want:
         assert torch.equal(got[k], want[k]), k
+
+
+def test_gradient_scaling_of_more_values_than_a_launch_has_threads(ctx):
+    """2^32 + 2^20 values (17 GB, in place): rows at both ends and where a thread's second and third round begin."""
+    g = np.random.default_rng(7)
+    ligs = pv.Ligands(ctx, [S.tree_ligand(g, 12, 2)])
+    row, B = 1 << 20, 4097
+    grad = torch.ones((B, row), device="cuda")
+    lig = torch.zeros(B, dtype=torch.int32, device="cuda")
+    scale = torch.arange(2, B + 2, dtype=torch.float32, device="cuda")
+    st = pv.lib().pv_scale_grad(ctx.h, ligs.h, B, lig.data_ptr(), grad.data_ptr(), row, 0, scale.data_ptr(), grad.data_ptr(),
+                                torch.cuda.current_stream().cuda_stream)
+    assert st == 0, pv.lib().pv_last_error()
+    own = 7 + ligs.max_tors
+    assert torch.equal(grad[:, :own], scale[:, None].expand(B, own))
+    for b in (0, 1, 2047, 2048, 2049, 4095, 4096):
+        assert bool((grad[b, own:] == 1).all()), b

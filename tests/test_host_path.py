@@ -69,3 +69,22 @@ def free_during_capture(f):
 
 def test_grids_freed_during_a_capture(fake):
     fake(free_during_capture)
+
+
+# ---------------------------------------------------------------- launch sizes
+def scale_launches(f):
+    """Every number of values is launched with fewer than 2^32 threads (the runtime takes no more in a dimension)."""
+    import numpy as np
+    from paper_2506_20043_amd import synth as S
+    ctx = f.context()
+    ligs = f.pv.Ligands(ctx, [S.tree_ligand(np.random.default_rng(0), 12, 2)])
+    p = 1 << 20
+    for poses, row, xyz in ((1, 9, 0), (16384, 17, 0), (1 << 27, 16, 0), ((1 << 28) + 1, 16, 0), (11200000, 384, 1)):
+        st = f.lib.pv_scale_grad(ctx.h, ligs.h, poses, p, p, row, xyz, p, p, None)
+        assert st == 0, (poses, row, f.lib.pv_last_error())
+        (k,) = f.launches("scale_grad")
+        assert k[1][0] * k[2][0] >= min(poses * row, 1 << 31) and k[1][1] == k[1][2] == 1
+
+
+def test_gradient_scaling_launches(fake):
+    fake(scale_launches)
