@@ -88,3 +88,25 @@ def scale_launches(f):
 
 def test_gradient_scaling_launches(fake):
     fake(scale_launches)
+
+
+def grid_launches(f):
+    """Map builds of up to 2^24 tiles (137 GB of maps), and around a row of workgroups: every tile has a workgroup, in
+    whole runs of 32."""
+    ctx = f.context()
+
+    def box(nx, ny, nz):
+        return [0.0, 0, 0], [nx - 1.0, ny - 1.0, nz - 1.0], 1.0
+
+    big = (240, 252, 276)                  # 15 x 63 x 69 tiles
+    for sizes, tiles in (([(5, 4, 4)], 1), ([big] * 16 + [(240, 80, 28)], 16 * 65205 + 2100), ([big] * 17, 17 * 65205),
+                         ([big] * 257 + [(240, 80, 260)], (1 << 24) - 31)):
+        g = f.grids(ctx, boxes=[box(*s) for s in sizes])
+        assert not isinstance(g, int), (tiles, f.lib.pv_last_error())
+        (k,) = f.launches("gridmap")
+        assert k[1][0] % 32 == 0 and tiles <= k[1][0] * k[1][1] < tiles + k[1][0] and k[1][2] == 1
+        g.close()
+
+
+def test_grid_map_launches(fake):
+    fake(grid_launches)
