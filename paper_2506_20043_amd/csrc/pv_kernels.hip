@@ -2079,9 +2079,8 @@ __device__ __forceinline__ float sq_dev(const Topo<A, SL>& T, const Lds& S, cons
 // batch is decided in order from the recorded conflicts), the refinements and
 // the rows of the final filter's conflict table.  Every comparison and every
 // refinement is the one a single wave makes, so the results do not depend on
-// the number of waves.  One wave -> this: 5 jobs x 256 chains, 20 modes 718 ->
-// 141 us; 1,024 jobs x 32 chains 1,275 -> 1,128 us; 256 jobs of 65-80 atoms x
-// 16 chains 1,294 -> 359 us.
+// the number of waves (output_waves).  One wave -> this: 5 jobs x 256 chains, 20 modes 718 ->
+// 141 us; 256 jobs of 65-80 atoms x 16 chains 1,294 -> 359 us.
 constexpr int kOutWaves = 8;
 
 template <int A>
@@ -3030,15 +3029,36 @@ hipError_t launch_local_opt(const OptArgs& a, int n_cu, hipStream_t s)
     return hipGetLastError();
 }
 
+// Waves per job: the fewest rounds of refinements, times the rounds of workgroups
+// that the CUs take to get through the jobs (a CU holds eight waves, two per SIMD,
+// or as many workgroups as its LDS), each workgroup's serial parts counted as 0.3
+// of a round of refinements; of equals the most waves.  Few jobs so get all eight
+// waves for the latency, and many jobs as many as keep every wave at work: jobs of
+// 64-atom ligands x 32 chains, one / two / four / eight waves each:
+//     120 x 20 modes 10.8 / 5.8 / 3.0 / 2.2 ms      1,000 x 20 modes 22.2 / 12.7 / 12.0 / 8.4 ms
+//     1,500 x 5 modes 3.5 / 3.8 / 6.6 / 4.2 ms      6,000 x 3 modes 7.9 / 9.4 / 8.1 / 14.6 ms
+// Four for every job count above the CUs, as before, took up to 1.9 times as long
+// as one wave (1,500 and 6,000 jobs x 5 modes); by this rule no set of 8 to
+// 128 atoms x 120 to 6,000 jobs x 3 to 20 modes takes above 3% longer than with
+// one wave, and all of them on average 1 to 4% longer than with their best number.
+static int output_waves(const OutputArgs& a, int n_cu, int lds_per_block)
+{
+    int best = 1;
+    int64_t least = INT64_MAX;
+    for (int w = 1; w <= kOutWaves; ++w) {
+        const int lds = output_lds_bytes(a.l, a.chains, a.modes, w);
+        if (w > 1 && lds > lds_per_block) break;
+        const int64_t held = (int64_t)std::max(1, std::min(kOutWaves / w, lds_per_block / lds)) * (n_cu > 0 ? n_cu : 1);
+        const int64_t cost = (a.n_jobs + held - 1) / held * (10 * ((std::min(a.modes, a.chains) + w - 1) / w) + 3);
+        if (cost <= least) { least = cost; best = w; }
+    }
+    return best;
+}
+
 hipError_t launch_output(const OutputArgs& a, int n_cu, int lds_per_block, hipStream_t s)
 {
     if (a.n_jobs <= 0) return hipSuccess;
-    // Few jobs: all the waves a workgroup may have (8 fill a CU at 2 per SIMD),
-    // for the latency.  More jobs than CUs: 4, two workgroups a CU, whose
-    // serial parts overlap and which divide the usual 20 modes evenly.  Fewer
-    // where LDS has no room for their tables.
-    int waves = a.n_jobs <= n_cu ? kOutWaves : kOutWaves / 2;
-    while (waves > 1 && output_lds_bytes(a.l, a.chains, a.modes, waves) > lds_per_block) --waves;
+    const int waves = output_waves(a, n_cu, lds_per_block);
     const int lds = output_lds_bytes(a.l, a.chains, a.modes, waves);
     if (a.l.max_atoms <= 64)
         hipLaunchKernelGGL((output_kernel<1>), dim3(a.n_jobs), dim3(kWave, waves), lds, s, a);

@@ -110,3 +110,28 @@ def grid_launches(f):
 
 def test_grid_map_launches(fake):
     fake(grid_launches)
+
+
+# ---------------------------------------------------------------- output stage
+def output_waves(f):
+    """Waves per job of the output stage: eight, or as many as the LDS holds, for few jobs; for many jobs as many as keep
+    every wave at work (four whatever the modes took up to 1.9 times as long as one)."""
+    import numpy as np
+    from paper_2506_20043_amd import synth as S
+    pv, ctx = f.pv, f.context()
+    grids = f.grids(ctx)
+    p = 1 << 20
+    for atoms, tors, jobs, modes, want in ((64, 20, 120, 20, 7), (64, 20, 1500, 5, 1), (64, 20, 6000, 3, 1), (64, 20, 1000, 20, 7),
+                                           (20, 4, 5, 3, 8), (20, 4, 1000, 20, 2), (20, 4, 2000, 9, 1), (100, 20, 2000, 3, 3),
+                                           (100, 20, 120, 20, 5)):
+        ligs = pv.Ligands(ctx, [S.tree_ligand(np.random.default_rng(atoms * 31 + tors), atoms, tors)])
+        plan = pv.Plan(ctx, grids, ligs, [(0, 0)] * jobs, pv.dock_params(chains=32))
+        o, op = pv.ModesOut(p, p, p, p, p, 7 + tors), pv.output_params(modes=modes)
+        f.launches()
+        assert f.lib.pv_output_stage(plan.h, p, p, 7 + tors, C.byref(op), C.byref(o), None) == 0, f.lib.pv_last_error()
+        (k,) = f.launches("output_kernel")
+        assert k[1][0] == jobs and k[2] == (64, want, 1), (atoms, jobs, modes, k[2])
+
+
+def test_output_stage_waves(fake):
+    fake(output_waves)
