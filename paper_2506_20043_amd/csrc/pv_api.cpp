@@ -1567,7 +1567,9 @@ pv_status pv_sas_build(pv_ctx* ctx, int32_t n_rec, const float* rec_xyz, const u
     const float um = (float)(umax * 1.00001), slack = (float)(0.01 + 1e-6 * (cmax + (2.0 + probe) * umax));
     // one temporary block: the directions, the masks, the counts
     const size_t words = (size_t)n_rec * ((n_dirs + 63) / 64);
-    const size_t off_count = (words + 1) * 8, off_dirs = off_count + 4 * ((size_t)n_rec + 2);
+    const int pieces = sas_pieces(n_rec, n_dirs, ctx->n_cu);
+    const size_t counts = (size_t)n_rec * pieces;
+    const size_t off_count = (words + 1) * 8, off_dirs = off_count + 4 * (counts + 2);
     char* tmp = nullptr;
     if ((st = upload(&h->atoms, ha.data(), ha.size(), "receptor")) != PV_OK ||
         (st = upload(&tmp, (const char*)nullptr, off_dirs + 12 * (size_t)n_dirs, "surface workspace")) != PV_OK) {
@@ -1579,8 +1581,8 @@ pv_status pv_sas_build(pv_ctx* ctx, int32_t n_rec, const float* rec_xyz, const u
     float* ddirs = (float*)(tmp + off_dirs);
     int32_t total = 0;
     hipError_t e = hipMemcpyAsync(ddirs, dirs, 12 * (size_t)n_dirs, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_sas_keep(h->atoms, n_rec, ddirs, n_dirs, probe, um, slack, keep, count, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&total, count + n_rec, sizeof(total), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = launch_sas_keep(h->atoms, n_rec, ddirs, n_dirs, probe, um, slack, pieces, keep, count, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&total, count + counts, sizeof(total), hipMemcpyDeviceToHost, s);
     // also where a call failed: the caller's arrays and `total` are free again
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess) e = es;
@@ -1591,7 +1593,7 @@ pv_status pv_sas_build(pv_ctx* ctx, int32_t n_rec, const float* rec_xyz, const u
         pv_sas_free(h);
         return st;
     }
-    e = launch_sas_scatter(h->atoms, n_rec, ddirs, n_dirs, probe, keep, count, h->pts, s);
+    e = launch_sas_scatter(h->atoms, n_rec, ddirs, n_dirs, probe, pieces, keep, count, h->pts, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     dfree(tmp);
     if (e != hipSuccess) { pv_sas_free(h); return hip_fail(e, "surface points"); }

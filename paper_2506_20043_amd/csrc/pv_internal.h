@@ -239,11 +239,13 @@ hipError_t launch_job_reduce(const float* chain_best_e, const int64_t* chain_eva
 hipError_t launch_local_opt(const OptArgs& a, int n_cu, hipStream_t s);
 hipError_t launch_output(const OutputArgs& a, int n_cu, int lds_per_block, hipStream_t s);
 // Surface points: kept directions of every atom as bit masks (ceil(n_dirs / 64)
-// words per atom) and the exclusive sums of their numbers (count [n_rec + 1],
-// the total last); umax >= |u| of every direction, slack: see sas_keep_kernel.
+// words per atom) and the exclusive sums of their numbers by atom and piece (count
+// [n_rec * pieces + 1], the total last); umax >= |u| of every direction, slack: see
+// sas_keep_kernel; pieces: sas_pieces.
+int sas_pieces(int n_rec, int n_dirs, int n_cu);
 hipError_t launch_sas_keep(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe, float umax,
-                           float slack, uint64_t* keep, int32_t* count, hipStream_t s);
-hipError_t launch_sas_scatter(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe,
+                           float slack, int pieces, uint64_t* keep, int32_t* count, hipStream_t s);
+hipError_t launch_sas_scatter(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe, int pieces,
                               const uint64_t* keep, const int32_t* offset, float4* pts, hipStream_t s);
 hipError_t launch_sas_split(const float4* pts, int n_pts, float* xyz, int32_t* atom, hipStream_t s);
 hipError_t launch_sas_features(const float4* atoms, int n_rec, const float4* pts, int n_pts, float* feat,

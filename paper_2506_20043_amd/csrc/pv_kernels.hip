@@ -2515,13 +2515,16 @@ __device__ __forceinline__ float3 sas_candidate(const float4& xa, float ra, cons
 // n_rec^2 n_dirs.  8,000 atoms x 30 directions: 807 us when every candidate
 // met every atom, 56 us now (36 us of them VALU issue); with the receptor
 // staged in LDS tiles, one atom per wave, 85-102 us.
-// Writes the kept directions as bit masks (ceil(n_dirs / 64) words per atom)
-// and their number.
+// Few atoms with many directions fill the chip with pieces of `per` chunks of 64
+// directions (blockIdx.y), each of which collects the neighbours again: a wave
+// that takes all of an atom's chunks is a serial chain of up to 128 tests of the
+// list.  Writes the kept directions as bit masks (ceil(n_dirs / 64) words per
+// atom) and their number by atom and piece.
 constexpr int kSasAtoms = 2;
 
 __global__ __launch_bounds__(kSasThreads) void sas_keep_kernel(const float4* atoms, int n_rec, const float* dirs,
                                                                int n_dirs, float probe, float umax, float slack,
-                                                               uint64_t* keep, int32_t* count)
+                                                               int per, uint64_t* keep, int32_t* count)
 {
     __shared__ float4 lists[kSasWaves][kSasAtoms][kSasList];
     const int l = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -2548,10 +2551,11 @@ __global__ __launch_bounds__(kSasThreads) void sas_keep_kernel(const float4* ato
     }
     const bool packed = n_dirs <= kWave / 2;
     const int chunks = (n_dirs + kWave - 1) / kWave;   // at most 64 (PV_MAX_SAS_DIRS)
+    const int c0 = (int)blockIdx.y * per, nc = min(per, chunks - c0);   // this piece's, at least one
     auto test = [&]() {
         wave_sync();
-        for (int pass = 0; pass < (packed ? 1 : kSasAtoms * chunks); ++pass) {
-            const int p = packed ? l / (kWave / 2) : pass / chunks, c = packed ? 0 : pass % chunks;
+        for (int pass = 0; pass < (packed ? 1 : kSasAtoms * nc); ++pass) {
+            const int p = packed ? l / (kWave / 2) : pass / nc, c = packed ? 0 : c0 + pass % nc;
             const int k = packed ? l % (kWave / 2) : c * kWave + l;
             const float4 xp = p ? xa[1] : xa[0];
             const float3 x = sas_candidate(xp, p ? ra[1] : ra[0], dirs + 3 * min(k, n_dirs - 1));
@@ -2601,7 +2605,7 @@ __global__ __launch_bounds__(kSasThreads) void sas_keep_kernel(const float4* ato
     for (int p = 0; p < kSasAtoms; ++p) {
         if (a0 + p >= n_rec) break;
         int total = 0;
-        for (int c = 0; c < chunks; ++c) {
+        for (int c = c0; c < c0 + nc; ++c) {
             uint64_t m;
             if (packed)
                 m = (__ballot(!(buried[p] & 1)) >> (p * (kWave / 2))) & ((1ull << n_dirs) - 1);
@@ -2610,17 +2614,17 @@ __global__ __launch_bounds__(kSasThreads) void sas_keep_kernel(const float4* ato
             if (l == 0) keep[(int64_t)(a0 + p) * chunks + c] = m;
             total += __popcll(m);
         }
-        if (l == 0) count[a0 + p] = total;
+        if (l == 0) count[(int64_t)(a0 + p) * gridDim.y + blockIdx.y] = total;
     }
 }
 
-// Exclusive sum of the atoms' counts in place; the total goes to count[n_rec].
-// One workgroup, a run of consecutive atoms per thread.
-__global__ __launch_bounds__(1024) void sas_scan_kernel(int32_t* count, int n_rec)
+// Exclusive sum of the n counts in place; the total goes to count[n].
+// One workgroup, a run of consecutive counts per thread.
+__global__ __launch_bounds__(1024) void sas_scan_kernel(int32_t* count, int n)
 {
     __shared__ int wave_n[1024 / kWave];
-    const int t = threadIdx.x, per = (n_rec + 1023) / 1024;
-    const int b = min(t * per, n_rec), e = min(b + per, n_rec);
+    const int t = threadIdx.x, per = (n + 1023) / 1024;
+    const int b = min(t * per, n), e = min(b + per, n);
     int sum = 0;
 #pragma unroll 8
     for (int i = b; i < e; ++i) sum += count[i];
@@ -2643,21 +2647,23 @@ __global__ __launch_bounds__(1024) void sas_scan_kernel(int32_t* count, int n_re
         count[i] = off;
         off += c;
     }
-    if (t == 0) count[n_rec] = all;
+    if (t == 0) count[n] = all;
 }
 
-// The kept candidates in (atom, direction) order, one wave per atom.
+// The kept candidates in (atom, direction) order, one wave per atom and piece.
 __global__ __launch_bounds__(kSasThreads) void sas_scatter_kernel(const float4* atoms, int n_rec, const float* dirs,
-                                                                  int n_dirs, float probe, const uint64_t* keep,
-                                                                  const int32_t* offset, float4* pts)
+                                                                  int n_dirs, float probe, int pieces, int per,
+                                                                  const uint64_t* keep, const int32_t* offset,
+                                                                  float4* pts)
 {
-    const int l = threadIdx.x & (kWave - 1), a = blockIdx.x * kSasWaves + threadIdx.x / kWave;
-    if (a >= n_rec) return;
+    const int l = threadIdx.x & (kWave - 1), w = blockIdx.x * kSasWaves + threadIdx.x / kWave;
+    if (w >= n_rec * pieces) return;
+    const int a = w / pieces, c0 = w % pieces * per;
     const float4 xa = atoms[a];
     const float ra = sas_radius(__float_as_uint(xa.w) & 0xff, probe);
     const int chunks = (n_dirs + kWave - 1) / kWave;
-    int off = offset[a];
-    for (int c = 0; c < chunks; ++c) {
+    int off = offset[w];
+    for (int c = c0; c < min(c0 + per, chunks); ++c) {
         const uint64_t m = keep[(int64_t)a * chunks + c];
         if ((m >> l) & 1) {
             const float3 x = sas_candidate(xa, ra, dirs + 3 * (c * kWave + l));
@@ -3074,25 +3080,41 @@ int output_lds_bytes(const LigDev& l, int chains, int modes, int waves)
            round_up(chains, 4) * 4 + modes * ma * 16 + modes * kSlot * 4 + 5 * round_up(modes, 4) * 4;
 }
 
+// Pieces of a whole number of chunks until the keep kernel has eight waves per CU:
+// 20 atoms x 4,096 directions 286 -> 103 us for the call, 500 x 4,096 606 -> 171.
+int sas_pieces(int n_rec, int n_dirs, int n_cu)
+{
+    const int chunks = (n_dirs + kWave - 1) / kWave, waves = n_rec / kSasAtoms + 1;
+    const int want = std::min(chunks, (8 * std::max(n_cu, 1) + waves - 1) / waves);
+    const int per = (chunks + want - 1) / want;
+    return (chunks + per - 1) / per;   // none of them empty
+}
+
+static int sas_per(int n_dirs, int pieces)
+{
+    return ((n_dirs + kWave - 1) / kWave + pieces - 1) / pieces;
+}
+
 hipError_t launch_sas_keep(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe, float umax,
-                           float slack, uint64_t* keep, int32_t* count, hipStream_t s)
+                           float slack, int pieces, uint64_t* keep, int32_t* count, hipStream_t s)
 {
     if (n_rec > 0) {
-        hipLaunchKernelGGL(sas_keep_kernel, dim3((n_rec + kSasWaves * kSasAtoms - 1) / (kSasWaves * kSasAtoms)),
-                           dim3(kSasThreads), 0, s, atoms, n_rec, dirs, n_dirs, probe, umax, slack, keep, count);
+        hipLaunchKernelGGL(sas_keep_kernel, dim3((n_rec + kSasWaves * kSasAtoms - 1) / (kSasWaves * kSasAtoms), pieces),
+                           dim3(kSasThreads), 0, s, atoms, n_rec, dirs, n_dirs, probe, umax, slack,
+                           sas_per(n_dirs, pieces), keep, count);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(sas_scan_kernel, dim3(1), dim3(1024), 0, s, count, n_rec);
+    hipLaunchKernelGGL(sas_scan_kernel, dim3(1), dim3(1024), 0, s, count, n_rec * pieces);
     return hipGetLastError();
 }
 
-hipError_t launch_sas_scatter(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe,
+hipError_t launch_sas_scatter(const float4* atoms, int n_rec, const float* dirs, int n_dirs, float probe, int pieces,
                               const uint64_t* keep, const int32_t* offset, float4* pts, hipStream_t s)
 {
     if (n_rec <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sas_scatter_kernel, dim3((n_rec + kSasWaves - 1) / kSasWaves), dim3(kSasThreads), 0, s, atoms,
-                       n_rec, dirs, n_dirs, probe, keep, offset, pts);
+    hipLaunchKernelGGL(sas_scatter_kernel, dim3((n_rec * pieces + kSasWaves - 1) / kSasWaves), dim3(kSasThreads), 0, s,
+                       atoms, n_rec, dirs, n_dirs, probe, pieces, sas_per(n_dirs, pieces), keep, offset, pts);
     return hipGetLastError();
 }
 

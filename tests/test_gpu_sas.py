@@ -63,6 +63,19 @@ def test_neighbour_lists(oracle, pv_ctx, n_rec, cube, n_dirs, scale):
     _check(oracle, pv_ctx, rx, rt, S.sphere_directions(n_dirs) * np.float32(scale))
 
 
+@pytest.mark.parametrize("n_rec, cube, n_dirs", [
+    (3, 4.0, 129),       # a piece per chunk, the last of one direction
+    (20, 7.0, 4096),     # a piece per chunk, the most directions
+    (300, 16.0, 4033),   # 13 pieces of five chunks, the last of four
+    (1400, 26.0, 200),   # two pieces of two chunks
+])
+def test_directions_in_pieces(oracle, pv_ctx, n_rec, cube, n_dirs):
+    """Few atoms with many directions: the chunks of an atom's directions are spread over several waves."""
+    g = np.random.default_rng(n_rec)
+    rx, rt = S.receptor(g, n_rec, cube)
+    _check(oracle, pv_ctx, rx, rt, S.sphere_directions(n_dirs))
+
+
 def test_degenerate_receptors(oracle, pv_ctx):
     import paper_2506_20043_amd as pv
     one = np.array([[1.0, 2.0, 3.0]], np.float32)

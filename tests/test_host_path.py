@@ -135,3 +135,24 @@ def output_waves(f):
 
 def test_output_stage_waves(fake):
     fake(output_waves)
+
+
+# ---------------------------------------------------------------- surface points
+def surface_launches(f):
+    """Few atoms with many directions fill the chip, or take a wave per 64 directions of two atoms; many atoms take a wave
+    per two."""
+    import numpy as np
+    ctx = f.context()
+    for atoms, dirs, waves in ((20, 4096, 640), (500, 4096, 2000), (500, 1000, 2000), (1, 33, 1), (2000, 30, 1000), (8000, 4096, 4000)):
+        x, t, d = np.zeros((atoms, 3), np.float32), np.zeros(atoms, np.uint8), np.ones((dirs, 3), np.float32)
+        h = C.c_void_p()
+        f.launches()
+        assert f.lib.pv_sas_build(ctx.h, atoms, x.ctypes.data, t.ctypes.data, dirs, d.ctypes.data, 1.6, None, C.byref(h)) == 0
+        (k,) = f.launches("sas_keep")
+        got = (atoms + 1) // 2 * k[1][1]
+        assert waves <= got <= 2 * waves, (atoms, dirs, got)
+        f.lib.pv_sas_free(h)
+
+
+def test_surface_launches(fake):
+    fake(surface_launches)
