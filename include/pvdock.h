@@ -338,6 +338,9 @@ typedef struct {
 } pv_schedule;
 pv_status pv_plan_groups(const pv_plan* plan, int32_t* n_groups);
 pv_status pv_plan_schedule(const pv_plan* plan, int32_t group, pv_schedule* out);
+/* Waves per workgroup of a class's launch under its schedule: 1, or 2 or 4
+ * where its chains have helper waves. */
+pv_status pv_plan_waves(const pv_plan* plan, int32_t group, int32_t* waves);
 /* Sets a class's variant and width.  PV_VARIANT_SLOTS and PV_VARIANT_GATHER
  * need ligands of at most 64 atoms; PV_VARIANT_GATHER2 takes any.  A
  * workgroup of the variant must fit a CU (PV_E_RANGE otherwise); workgroups

@@ -1148,6 +1148,18 @@ pv_status pv_plan_schedule(const pv_plan* P, int32_t group, pv_schedule* out)
     return PV_OK;
 }
 
+pv_status pv_plan_waves(const pv_plan* P, int32_t group, int32_t* waves)
+{
+    if (!P || !waves) return fail(PV_E_INVALID, "plan or output is NULL");
+    if (group < 0 || group >= (int32_t)P->groups.size()) return fail(PV_E_RANGE, "no such size class");
+    pv_status st = set_device(P->ctx);
+    if (st != PV_OK) return st;
+    const DockGroup& G = P->groups[group];
+    *waves = dock_waves(G.lv, P->sp.m, (int64_t)G.n_jobs * P->sp.chains, G.shape, G.workgroups, P->groups.size() == 1,
+                        P->ctx->n_cu);
+    return PV_OK;
+}
+
 // Shape and width of `variant` for a size class; workgroups 0 = all the CUs
 // hold, capped by the class's work.  The device must be current.
 static pv_status group_shape(const pv_plan* P, int32_t group, int32_t variant, int32_t workgroups, LaunchShape* sh,

@@ -2936,10 +2936,10 @@ hipError_t launch_score(const ScoreArgs& a, bool ragged, int n_cu, hipStream_t s
 
 // Whether a launch's chains can have teams of W waves: all of them resident at once.
 template <int MM, int W>
-static bool team_fits(const DockArgs& a, const LaunchShape& sh, int n_cu)
+static bool team_fits(const LigDev& l, int64_t items, const LaunchShape& sh, int n_cu)
 {
-    const int lds = sh.lds + team_bytes<W>(a.l.max_atoms, a.l.max_pairs);
-    return (int64_t)occupancy(dock_kernel<1, true, MM, W>, lds, W * kWave) * n_cu >= a.n_items;
+    const int lds = sh.lds + team_bytes<W>(l.max_atoms, l.max_pairs);
+    return (int64_t)occupancy(dock_kernel<1, true, MM, W>, lds, W * kWave) * n_cu >= items;
 }
 
 template <int MM, int W>
@@ -2959,11 +2959,25 @@ static void launch_slots(const DockArgs& a, const LaunchShape& sh, unsigned grid
 //     64 atoms, 1,717 pairs   8 chains 7.88 / 6.14 / 4.66      256: 9.91 / 7.80 / 5.97
 //     35 atoms, 1,024 chains 9.87 / 8.50 (no room for teams of four)
 template <int MM>
+static int team_waves(const LigDev& l, int64_t items, const LaunchShape& sh, unsigned grid, bool alone, int n_cu)
+{
+    if (!alone || grid < items || l.max_pairs <= kWave) return 1;
+    return team_fits<MM, 4>(l, items, sh, n_cu) ? 4 : team_fits<MM, 2>(l, items, sh, n_cu) ? 2 : 1;
+}
+
+int dock_waves(const LigDev& l, int m, int64_t items, const LaunchShape& sh, int32_t workgroups, bool alone, int n_cu)
+{
+    if (sh.variant != 0) return 1;
+    return m <= kShortM ? team_waves<kShortM>(l, items, sh, (unsigned)workgroups, alone, n_cu)
+                        : team_waves<kMaxM>(l, items, sh, (unsigned)workgroups, alone, n_cu);
+}
+
+template <int MM>
 static void launch_slot_dock(const DockArgs& a, const LaunchShape& sh, unsigned grid, bool alone, int n_cu, hipStream_t s)
 {
-    const bool team = alone && grid >= a.n_items && a.l.max_pairs > kWave;
-    if (team && team_fits<MM, 4>(a, sh, n_cu)) launch_slots<MM, 4>(a, sh, grid, s);
-    else if (team && team_fits<MM, 2>(a, sh, n_cu)) launch_slots<MM, 2>(a, sh, grid, s);
+    const int waves = team_waves<MM>(a.l, a.n_items, sh, grid, alone, n_cu);
+    if (waves == 4) launch_slots<MM, 4>(a, sh, grid, s);
+    else if (waves == 2) launch_slots<MM, 2>(a, sh, grid, s);
     else launch_slots<MM, 1>(a, sh, grid, s);
 }
 

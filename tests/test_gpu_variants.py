@@ -353,3 +353,36 @@ def test_three_waves_per_simd_change_nothing(oracle, pv_ctx, m):
     few = pv.local_opt(pv_ctx, st.grids, st.ligs, lig[:n8], box[:n8], dof[:n8], pv.dock_params(bfgs_m=m))
     for a, b in zip(many, few):
         assert np.array_equal(a[:n8].cpu().numpy(), b.cpu().numpy())
+
+
+@pytest.mark.parametrize("chains,m,n_max,waves", [(4, 5, 64, 4), (4, 8, 64, 4), (90, 5, 38, 2), (90, 8, 38, 2)])
+def test_helper_waves_are_there(oracle, pv_ctx, chains, m, n_max, waves):
+    """The launches of test_helper_waves_change_nothing: teams of four and of two with a workgroup for every chain, one
+    wave each with one workgroup less; and no helpers beside another size class, on the gather form, or for at most 64 pairs."""
+    import paper_2506_20043_amd as pv
+    cfg = S.CONFIGS["tiny"]
+    rx, rt, bxs = S.make_receptor(cfg)
+    g = np.random.default_rng(31)
+    mols, seen = [S.tree_ligand(g, 1, 0)], {0}
+    for n in range(8, n_max + 1):
+        mol = S.tree_ligand(g, n, min(3 + n // 8, 10))
+        p = pv.describe_ligand(mol.xyz, mol.types, mol.bonds, mol.rotatable)[0][3]
+        if (p + 63) // 64 not in seen:
+            seen.add((p + 63) // 64)
+            mols.append(mol)
+    n = len(mols)
+    st = Setup(oracle, pv_ctx, rx, rt, bxs[:1], mols + [S.tree_ligand(g, 70, 5)])
+    params = pv.dock_params(chains=chains, steps=1, bfgs_m=m)
+    plan = pv.Plan(pv_ctx, st.grids, st.ligs, [(i, 0) for i in range(n)], params)
+    for variant, workgroups, want in ((pv.VARIANT_SLOTS, 0, waves), (pv.VARIANT_SLOTS, n * chains - 1, 1), (pv.VARIANT_GATHER, 0, 1)):
+        plan.set_schedule(0, variant, workgroups)
+        assert plan.waves() == want, (variant, workgroups)
+    plan.close()
+    plan = pv.Plan(pv_ctx, st.grids, st.ligs, [(i, 0) for i in range(n + 1)], params)
+    plan.set_schedule(0, pv.VARIANT_SLOTS)
+    assert plan.groups() == 2 and plan.waves(0) == plan.waves(1) == 1
+    plan.close()
+    plan = pv.Plan(pv_ctx, st.grids, st.ligs, [(0, 0), (1, 0)], params)   # no pairs, and one chunk of 64
+    plan.set_schedule(0, pv.VARIANT_SLOTS)
+    assert plan.waves() == 1
+    plan.close()
