@@ -2934,10 +2934,21 @@ hipError_t launch_score(const ScoreArgs& a, bool ragged, int n_cu, hipStream_t s
     return hipGetLastError();
 }
 
-// Whether a launch's chains can have teams of W waves: all of them resident at once.
+// Whether a launch's chains can have teams of W waves: all of them resident at
+// once, and beside them as many equal launches of other streams as without teams,
+// up to the four that a process's hardware queues run side by side.  Launches that
+// no longer fit together run one after the other (chains of 60 steps, teams where
+// one launch fits / one wave each / this rule):
+//     20 atoms, 320 chains, three streams 16.0 / 12.4 / 10.9 ms; 500, two 15.7 / 12.2 / 10.9
+//     20 atoms, 750 chains, two streams 19.7 / 12.8 / 10.6 ms; 35 atoms, 240, four 14.4 / - / 10.5
+// One launch alone pays where the smaller team is slower: 35 atoms, 320 chains 8.9
+// / 11.8 / 9.7 ms.
+constexpr int kSideBySide = 4;
+
 template <int MM, int W>
 static bool team_fits(const LigDev& l, int64_t items, const LaunchShape& sh, int n_cu)
 {
+    items *= std::min<int64_t>(kSideBySide, std::max<int64_t>(1, (int64_t)sh.per_cu * n_cu / items));
     const int lds = sh.lds + team_bytes<W>(l.max_atoms, l.max_pairs);
     return (int64_t)occupancy(dock_kernel<1, true, MM, W>, lds, W * kWave) * n_cu >= items;
 }
@@ -2949,7 +2960,7 @@ static void launch_slots(const DockArgs& a, const LaunchShape& sh, unsigned grid
     hipLaunchKernelGGL((dock_kernel<1, true, MM, W>), dim3(grid), dim3(kWave, W), lds, s, a);
 }
 
-// Slot launches: teams where every chain is resident at once with its helpers,
+// Slot launches: teams where every chain is resident at once with its helpers (team_fits),
 // with more than one chunk of pairs (fewer take no longer than the waits for the
 // helpers: 16 atoms, 61 pairs, 1,024 chains 11.2 ms alone, 11.6 in teams of two),
 // and with no other class's launch beside it.  Teams of four before teams of two,
