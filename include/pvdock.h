@@ -358,8 +358,8 @@ pv_status pv_plan_set_schedule(pv_plan* plan, int32_t group, int32_t variant, in
  * the best of `repeats` >= 1 timings (HIP events on `stream`) and sets the candidate
  * with the most evaluations per second; on a tie the earlier candidate (the
  * model's schedule comes first) wins.  The choice is remembered by the
- * context, keyed by the class's ligand limits, work items, tune_steps and
- * search settings, and a later call on a plan of the same key takes it
+ * context, keyed by the class's ligand limits and work items, those of the
+ * plan's other class, tune_steps and search settings, and a later call on a plan of the same key takes it
  * without timing (reported with cached = 1); it keeps the latest 256 such
  * choices.  results: host, up to
  * max_results entries (may be NULL); n_results: how many were written (may

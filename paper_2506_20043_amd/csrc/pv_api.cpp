@@ -141,9 +141,18 @@ pv_status upload(T** dst, const T* src, size_t n, const char* what)
 }  // namespace
 
 // One autotuner choice: the key of a size class's launch, and its schedule.
-struct TuneEntry {
+struct TuneClass {
     int32_t max_atoms, max_pairs, max_ell, max_tors;
     int64_t items;
+    bool operator==(const TuneClass& o) const
+    {
+        return max_atoms == o.max_atoms && max_pairs == o.max_pairs && max_ell == o.max_ell && max_tors == o.max_tors &&
+               items == o.items;
+    }
+};
+struct TuneEntry {
+    TuneClass cls, beside;   // the class, and the one whose launch runs beside it (all 0: none, so that
+                             // its chains may have helper waves)
     int32_t steps, max_iter, refine_max_iter, m, ls_max, consistency;
     int32_t variant, workgroups;
 };
@@ -1194,8 +1203,7 @@ pv_status pv_plan_set_schedule(pv_plan* P, int32_t group, int32_t variant, int32
 
 static bool same_key(const TuneEntry& a, const TuneEntry& b)
 {
-    return a.max_atoms == b.max_atoms && a.max_pairs == b.max_pairs && a.max_ell == b.max_ell &&
-           a.max_tors == b.max_tors && a.items == b.items && a.steps == b.steps && a.max_iter == b.max_iter &&
+    return a.cls == b.cls && a.beside == b.beside && a.steps == b.steps && a.max_iter == b.max_iter &&
            a.refine_max_iter == b.refine_max_iter && a.m == b.m && a.ls_max == b.ls_max &&
            a.consistency == b.consistency;
 }
@@ -1235,7 +1243,10 @@ pv_status pv_dock_autotune(pv_plan* P, int32_t tune_steps, int32_t repeats, void
     for (size_t g = 0; g < P->groups.size(); ++g) {
         DockGroup& G = P->groups[g];
         const int64_t items = (int64_t)G.n_jobs * chains;
-        TuneEntry key = {G.lv.max_atoms, G.lv.max_pairs, G.lv.max_ell, G.lv.max_tors, items, tune_steps,
+        auto tune_class = [&](const DockGroup& c) {
+            return TuneClass{c.lv.max_atoms, c.lv.max_pairs, c.lv.max_ell, c.lv.max_tors, (int64_t)c.n_jobs * chains};
+        };
+        TuneEntry key = {tune_class(G), P->groups.size() == 2 ? tune_class(P->groups[1 - g]) : TuneClass{}, tune_steps,
                          P->sp.max_iter, P->sp.refine_max_iter, P->sp.m, P->sp.ls_max, P->sp.consistency, 0, 0};
         bool cached = false;
         {

@@ -183,3 +183,40 @@ def team_sizes(f):
 
 def test_teams_leave_room_for_other_streams(fake):
     fake(team_sizes)
+
+
+# ---------------------------------------------------------------- autotuner
+def _tune(f, plan, repeats=1):
+    """(group, variant, workgroups, cached) of every candidate, and the dock launches."""
+    pv = f.pv
+    res, n = (pv.TuneResult * 64)(), C.c_int32()
+    f.launches()
+    assert f.lib.pv_dock_autotune(plan.h, 2, repeats, None, res, 64, C.byref(n)) == 0, f.lib.pv_last_error()
+    return [(r.group, r.variant, r.workgroups, r.cached) for r in res[:n.value]], f.launches("dock_kernel")
+
+
+def _tune_plans(f):
+    """A plan of one size class, and one with the same class and a larger one."""
+    import numpy as np
+    from paper_2506_20043_amd import synth as S
+    g, ctx = np.random.default_rng(3), f.context()
+    grids = f.grids(ctx)
+    ligs = f.pv.Ligands(ctx, [S.tree_ligand(g, 30, 5), S.tree_ligand(g, 90, 8)])
+    p = f.pv.dock_params(chains=16)
+    return [f.pv.Plan(ctx, grids, ligs, jobs, p) for jobs in ([(0, 0)] * 4, [(0, 0)] * 4, [(0, 0)] * 4 + [(1, 0)] * 3)]
+
+
+def tuned_choices(f):
+    """A class's remembered schedule is not taken where another class runs beside it, which decides about its helper
+    waves; one of an equal plan is."""
+    one, same, two = _tune_plans(f)
+    assert all(r[3] == 0 for r in _tune(f, one)[0])
+    assert [r[3] for r in _tune(f, same)[0]] == [1]
+    res, _ = _tune(f, two)
+    assert {r[0] for r in res} == {0, 1} and all(r[3] == 0 for r in res), res
+    assert [r[3] for r in _tune(f, two)[0]] == [1, 1]
+
+
+@pytest.mark.parametrize("scenario", [tuned_choices], ids=lambda s: s.__name__)
+def test_autotuner(fake, scenario):
+    fake(scenario)
