@@ -354,10 +354,12 @@ pv_status pv_plan_set_schedule(pv_plan* plan, int32_t group, int32_t variant, in
  * on a short run of the class's launch (tune_steps >= 1 Monte Carlo steps per
  * chain, outputs to the plan's own scratch, no timestamps) over the class's
  * first jobs in the order the launch hands them out (enough chains to fill
- * the widest candidate 8 times, or the whole class when it has fewer), keeps
- * the best of `repeats` >= 1 timings (HIP events on `stream`) and sets the candidate
- * with the most evaluations per second; on a tie the earlier candidate (the
- * model's schedule comes first) wins.  The choice is remembered by the
+ * the widest candidate 8 times, or the whole class when it has fewer), the
+ * plan's other class, if any, beside it as in pv_dock_run (with its schedule
+ * so far, on the same share of its jobs, bounded likewise).  It keeps the best
+ * of `repeats` >= 1 timings (HIP events on `stream`) and sets the candidate
+ * with the most evaluations per second, both classes' counted; on a tie the
+ * earlier candidate (the model's schedule comes first) wins.  The choice is remembered by the
  * context, keyed by the class's ligand limits and work items, those of the
  * plan's other class, tune_steps and search settings, and a later call on a plan of the same key takes it
  * without timing (reported with cached = 1); it keeps the latest 256 such

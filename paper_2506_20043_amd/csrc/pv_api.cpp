@@ -992,6 +992,18 @@ static DockArgs dock_args(pv_plan* P, const pv_dock_out* o, float* cbe, int64_t*
     return a;
 }
 
+// the persistent launch of class k over its first `items` chains
+static DockArgs class_args(pv_plan* P, const pv_dock_out* o, float* cbe, int64_t* cev, int32_t* cst, size_t k, int64_t items)
+{
+    DockArgs a = dock_args(P, o, cbe, cev, cst);
+    a.l = P->groups[k].lv;
+    a.job_map = P->groups[k].job_map;
+    a.queue = P->queue + k;
+    a.n_items = items;
+    a.persistent = 1;
+    return a;
+}
+
 static pv_status check_out(const pv_plan* P, const pv_dock_out* o)
 {
     if (!o) return fail(PV_E_INVALID, "out is NULL");
@@ -1000,6 +1012,33 @@ static pv_status check_out(const pv_plan* P, const pv_dock_out* o)
     if ((P->sp.flags & PV_DOCK_TIMESTAMPS) && (!o->job_t_start || !o->job_t_end))
         return fail(PV_E_INVALID, "timestamps requested without job_t_start / job_t_end");
     return PV_OK;
+}
+
+// The launches of every class (a[g]: class g's arguments, sh[g] and wg[g] its
+// schedule) on s, the queue counters reset before them.
+// Two size classes run side by side: their chains are long (tens of ms), so
+// one class after the other leaves most of the chip idle while the first
+// one's last chains end.  The larger ligands' launch goes first, on s.
+// 1,024 jobs of a screen (736 small), 16 chains x 300 steps: 402 -> 361 ms.
+static hipError_t launch_classes(const pv_plan* P, const DockArgs* a, const LaunchShape* sh, const int32_t* wg, hipStream_t s)
+{
+    const bool two = P->groups.size() == 2;
+    hipError_t e = launch_reset_queue(P->queue, s);
+    if (e == hipSuccess && two) e = hipEventRecord(P->fork, s);
+    if (e == hipSuccess && two) e = hipStreamWaitEvent(P->side_stream, P->fork, 0);
+    if (e != hipSuccess) return e;
+    for (size_t k = P->groups.size(); k-- > 0;) {
+        const hipError_t el = launch_dock(a[k], sh[k], wg[k], !two, P->ctx->n_cu, two && k == 0 ? P->side_stream : s);
+        if (e == hipSuccess) e = el;
+    }
+    // joined also where a launch failed, so that nothing is left running
+    // beside s (nor a capture left forked)
+    if (two) {
+        hipError_t ej = hipEventRecord(P->join, P->side_stream);
+        if (ej == hipSuccess) ej = hipStreamWaitEvent(s, P->join, 0);
+        if (e == hipSuccess) e = ej;
+    }
+    return e;
 }
 
 static hipError_t enqueue_batched(pv_plan* P, const pv_dock_out* o, hipStream_t s)
@@ -1012,34 +1051,16 @@ static hipError_t enqueue_batched(pv_plan* P, const pv_dock_out* o, hipStream_t 
         e = launch_reset_times(o->job_t_start, o->job_t_end, P->n_jobs, s);
         if (e != hipSuccess) return e;
     }
-    // Two size classes run side by side: their chains are long (tens of ms), so
-    // one class after the other leaves most of the chip idle while the first
-    // one's last chains end.  The larger ligands' launch goes first, on s.
-    // 1,024 jobs of a screen (736 small), 16 chains x 300 steps: 402 -> 361 ms.
-    const bool two = P->groups.size() == 2;
-    e = launch_reset_queue(P->queue, s);
-    if (e == hipSuccess && two) e = hipEventRecord(P->fork, s);
-    if (e == hipSuccess && two) e = hipStreamWaitEvent(P->side_stream, P->fork, 0);
-    if (e != hipSuccess) return e;
-    for (size_t k = P->groups.size(); k-- > 0;) {
+    DockArgs a[2];
+    LaunchShape sh[2];
+    int32_t wg[2];
+    for (size_t k = 0; k < P->groups.size(); ++k) {
         const DockGroup& G = P->groups[k];
-        DockArgs a = dock_args(P, o, cbe, cev, cst);
-        a.l = G.lv;
-        a.job_map = G.job_map;
-        a.queue = P->queue + k;
-        a.job_begin = 0;
-        a.n_items = (int64_t)G.n_jobs * P->sp.chains;
-        a.persistent = 1;
-        const hipError_t el = launch_dock(a, G.shape, G.workgroups, !two, P->ctx->n_cu, two && k == 0 ? P->side_stream : s);
-        if (e == hipSuccess) e = el;
+        a[k] = class_args(P, o, cbe, cev, cst, k, (int64_t)G.n_jobs * P->sp.chains);
+        sh[k] = G.shape;
+        wg[k] = G.workgroups;
     }
-    // joined also where a launch failed, so that nothing is left running
-    // beside s (nor a capture left forked)
-    if (two) {
-        hipError_t ej = hipEventRecord(P->join, P->side_stream);
-        if (ej == hipSuccess) ej = hipStreamWaitEvent(s, P->join, 0);
-        if (e == hipSuccess) e = ej;
-    }
+    e = launch_classes(P, a, sh, wg, s);
     if (e != hipSuccess) return e;
     if (o->job_best_e || o->job_best_chain || o->job_evals || o->job_status)
         e = launch_job_reduce(cbe, cev, cst, P->n_jobs, P->sp.chains, o->job_best_e, o->job_best_chain, o->job_evals,
@@ -1281,29 +1302,40 @@ pv_status pv_dock_autotune(pv_plan* P, int32_t tune_steps, int32_t repeats, void
         // every candidate runs on the class's first jobs in job-map order:
         // enough chains to fill the widest candidate kTuneFill times (all of
         // the class when it is smaller), so the tuning cost does not grow
-        // with the batch
+        // with the batch; the plan's other class runs beside it as pv_dock_run's
+        // launches do, with its schedule of the moment and the same share of its
+        // jobs (bounded likewise)
         int64_t widest = 1;
         for (const auto& c : cand) widest = std::max<int64_t>(widest, c.second);
-        const int64_t t_items = std::min<int64_t>(items, (kTuneFill * widest + chains - 1) / chains * chains);
-        const int32_t t_jobs = (int32_t)(t_items / chains);
+        auto whole_jobs = [&](int64_t n) { return (n + chains - 1) / chains * chains; };
+        int64_t run_items[2];
+        run_items[g] = std::min<int64_t>(items, whole_jobs(kTuneFill * widest));
+        for (size_t k = 0; k < P->groups.size(); ++k) {
+            if (k == g) continue;
+            const DockGroup& O = P->groups[k];
+            const int64_t all = (int64_t)O.n_jobs * chains;
+            const double share = (double)run_items[g] / (double)items;
+            run_items[k] = std::min<int64_t>({all, whole_jobs(kTuneFill * (int64_t)O.workgroups),
+                                              whole_jobs(std::max<int64_t>(1, (int64_t)(share * (double)all)))});
+        }
         size_t best = 0;
         double best_rate = -1.0;
         std::vector<int32_t> slot(cand.size(), -1);
         for (size_t k = 0; k < cand.size(); ++k) {
-            DockArgs a = dock_args(P, &none, P->scratch_best, P->scratch_evals, P->scratch_status);
-            a.sp.steps = tune_steps;
-            a.sp.flags &= ~PV_DOCK_TIMESTAMPS;
-            a.l = G.lv;
-            a.job_map = G.job_map;
-            a.queue = P->queue + g;
-            a.job_begin = 0;
-            a.n_items = t_items;
-            a.persistent = 1;
+            DockArgs a[2];
+            LaunchShape sh[2];
+            int32_t wg[2];
+            for (size_t q = 0; q < P->groups.size(); ++q) {
+                a[q] = class_args(P, &none, P->scratch_best, P->scratch_evals, P->scratch_status, q, run_items[q]);
+                a[q].sp.steps = tune_steps;
+                a[q].sp.flags &= ~PV_DOCK_TIMESTAMPS;
+                sh[q] = q == g ? cand[k].first : P->groups[q].shape;
+                wg[q] = q == g ? cand[k].second : P->groups[q].workgroups;
+            }
             float best_ms = 0.f;
             for (int r = 0; r < repeats; ++r) {
-                e = launch_reset_queue(P->queue, s);
-                if (e == hipSuccess) e = hipEventRecord(t0, s);
-                if (e == hipSuccess) e = launch_dock(a, cand[k].first, cand[k].second, P->groups.size() == 1, P->ctx->n_cu, s);
+                e = hipEventRecord(t0, s);
+                if (e == hipSuccess) e = launch_classes(P, a, sh, wg, s);
                 if (e == hipSuccess) e = hipEventRecord(t1, s);
                 if (e == hipSuccess) e = hipEventSynchronize(t1);
                 float ms = 0.f;
@@ -1314,10 +1346,11 @@ pv_status pv_dock_autotune(pv_plan* P, int32_t tune_steps, int32_t repeats, void
             e = hipMemcpy(hev.data(), P->scratch_evals, hev.size() * sizeof(int64_t), hipMemcpyDeviceToHost);
             if (e != hipSuccess) return done(hip_fail(e, "autotune evaluation counts"));
             int64_t ev = 0;
-            for (int32_t q = 0; q < t_jobs; ++q) {
-                const int32_t j = P->group_jobs[g][q];
-                for (int32_t c = 0; c < chains; ++c) ev += hev[(size_t)j * chains + c];
-            }
+            for (size_t q = 0; q < P->groups.size(); ++q)
+                for (int64_t n = 0; n < run_items[q] / chains; ++n) {
+                    const int32_t j = P->group_jobs[q][n];
+                    for (int32_t c = 0; c < chains; ++c) ev += hev[(size_t)j * chains + c];
+                }
             const double rate = best_ms > 0.f ? (double)ev / (best_ms * 1e-3) : 0.0;
             slot[k] = put(pv_tune_result{(int32_t)g, cand[k].first.variant, cand[k].second, 0, 0, best_ms, rate});
             if (rate > best_rate) { best_rate = rate; best = k; }

@@ -217,6 +217,16 @@ def tuned_choices(f):
     assert [r[3] for r in _tune(f, two)[0]] == [1, 1]
 
 
-@pytest.mark.parametrize("scenario", [tuned_choices], ids=lambda s: s.__name__)
+def tuned_side_by_side(f):
+    """Every candidate of a plan of two classes is timed as the plan runs: both classes' launches, on two streams."""
+    one, _, two = _tune_plans(f)
+    for plan, classes in ((one, 1), (two, 2)):
+        res, launches = _tune(f, plan, repeats=3)
+        assert len(launches) == 3 * classes * len(res)
+        for k in range(0, len(launches), classes):
+            assert len({x[4] for x in launches[k:k + classes]}) == classes
+
+
+@pytest.mark.parametrize("scenario", [tuned_choices, tuned_side_by_side], ids=lambda s: s.__name__)
 def test_autotuner(fake, scenario):
     fake(scenario)
