@@ -55,6 +55,10 @@ typedef struct pv_ctx pv_ctx;
  * makes that device current. */
 pv_status pv_create(int32_t device, pv_ctx** out);
 void pv_destroy(pv_ctx* ctx);
+/* Gives the device memory that the library keeps for later calls back to the
+ * driver: the block of the last maps freed on the context's device (see
+ * pv_grids_free).  Waits for the device, as hipFree does. */
+pv_status pv_trim(pv_ctx* ctx);
 
 /* ---------------------------------------------------------------- grid maps
  * Grid cache of the paper's "Kernel 1" (Methods, Accelerated Docking;
@@ -104,6 +108,11 @@ pv_status pv_grids_rebuild(pv_grids* g, void* stream);
 /* copies the 8 maps of one box ([8][nz][ny][nx] binary32) into the caller's
  * device buffer `dst`, ordered on `stream` */
 pv_status pv_grids_copy(const pv_grids* g, int32_t box, float* dst, void* stream);
+/* Waits for the device, as hipFree does.  The maps' block, if of at most 1 GiB,
+ * is kept for the next pv_build_grids on that device whose maps take half of it
+ * or more: one block per device, which other allocators in the process do not
+ * see.  It is freed by pv_trim, by a build of other sizes, when an allocation of
+ * the library fails, and with the device's last context. */
 void pv_grids_free(pv_grids* g);
 
 /* ------------------------------------------------------------------ ligands

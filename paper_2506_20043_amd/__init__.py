@@ -93,6 +93,7 @@ SIGNATURES = {
     "pv_version": (C.c_int32, []),
     "pv_create": (C.c_int, [_i32, C.POINTER(_vp)]),
     "pv_destroy": (None, [_vp]),
+    "pv_trim": (C.c_int, [_vp]),
     "pv_box_lattice": (C.c_int, [C.POINTER(Box), _ip, C.POINTER(C.c_float)]),
     "pv_build_grids": (C.c_int, [_vp, _i32, _vp, _vp, C.POINTER(Box), _i32, C.c_float, _vp, C.POINTER(_vp)]),
     "pv_grids_info": (C.c_int, [_vp, _i32, _ip, C.POINTER(C.c_float), C.POINTER(_vp)]),
@@ -210,6 +211,10 @@ class Context:
         self.h = h
         self.device = int(device)
         self.torch_device = _torch().device("cuda", self.device)
+
+    def trim(self):
+        """Gives the device memory kept for later grid builds back to the driver."""
+        _check(lib().pv_trim(self.h), "pv_trim")
 
     def close(self):
         if self.h:

@@ -54,8 +54,8 @@ bool dfree(void* p)
 // driver takes 230-260 us (measured at 167 to 660 MB; hipMalloc 31-41 us), a
 // tenth of a screening receptor's build.  The last block freed on a device is
 // kept for the next build that fits it: one block of at most kSpareMax bytes per
-// device, freed with the device's last context, when a build needs another size
-// or when an allocation fails.  A block is kept only after everything on the
+// device, freed by pv_trim, with the device's last context, when a build needs
+// another size or when an allocation fails.  A block is kept only after everything on the
 // device has completed: the grids' other block is freed first, and hipFree waits
 // for the device.  Where that is refused (a stream is capturing) the maps are
 // freed like it; a wait of its own would be one more call that a capture forbids.
@@ -338,6 +338,15 @@ void pv_destroy(pv_ctx* c)
         }
     }
     delete c;
+}
+
+pv_status pv_trim(pv_ctx* ctx)
+{
+    if (!ctx_ok(ctx)) return fail(PV_E_STATE, "invalid context");
+    pv_status st = set_device(ctx);
+    if (st != PV_OK) return st;
+    (void)drop_spare();
+    return PV_OK;
 }
 
 // ------------------------------------------------------------------ grids

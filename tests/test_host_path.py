@@ -49,6 +49,30 @@ def test_allocation_errors_are_not_left_behind(fake, scenario):
     fake(scenario)
 
 
+def kept_block(f):
+    """Freed maps up to 1 GiB are kept until pv_trim, a build of other sizes or the last context's end; larger ones never."""
+    a, b = f.context(), f.context()
+    f.grids(a).close()
+    assert f.rt.fake_used() == 21 ** 3 * 32
+    assert f.lib.pv_trim(a.h) == 0 and f.rt.fake_used() == 0
+    assert f.lib.pv_trim(a.h) == 0                       # nothing kept
+    assert f.lib.pv_trim(None) == -6
+    f.grids(a).close()
+    f.grids(a, boxes=[([0., 0, 0], 300.0, 1.5)]).close()   # 201^3 points, 260 MB: the smaller block goes
+    assert 201 ** 3 * 32 <= f.rt.fake_used() < 201 ** 3 * 32 + 1000
+    f.grids(a, boxes=[([0., 0, 0], 300.0, 1.5)] * 5).close()   # 1.3 GB
+    assert f.rt.fake_used() == 0
+    f.grids(a).close()
+    f.lib.pv_destroy(a.h)
+    assert f.rt.fake_used() > 0
+    f.lib.pv_destroy(b.h)
+    assert f.rt.fake_used() == 0
+
+
+def test_kept_map_block(fake):
+    fake(kept_block)
+
+
 # ---------------------------------------------------------------- captures
 def free_during_capture(f):
     """Freeing grids while a stream captures makes no call that waits for the device, keeps no block that the device
