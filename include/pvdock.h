@@ -184,7 +184,8 @@ pv_status pv_score_grad_xyz(pv_ctx* ctx, const pv_grids* grids, const pv_ligands
                             int32_t xyz_stride, const float* grad_energy, float* energy, float* e_parts,
                             float* grad_xyz, void* stream);
 
-/* The backward pass of a score whose gradient was taken along: out = grad,
+/* The backward pass of a score whose gradient was taken along (the caller keeps
+ * it from the forward to the backward pass, B x row values): out = grad,
  * each row's own values (7 + T of a pose vector, 3 per atom of coordinates)
  * times its pose's upstream factor scale [B], as pv_score_grad's grad_energy
  * gives them; values past them, and rows of out-of-range poses, as they are.

@@ -437,12 +437,18 @@ def _autograd_classes():
 
         apply(dof [B, stride], handles) -> energy [B]; the gradient reaches
         dof as dE/d(t, raw q, psi).  One launch computes the energy and, where
-        dof needs it, the gradient, which the backward scales."""
+        dof needs it and gradients are recorded, the gradient, which is kept
+        ([B, stride]) for the backward to scale."""
+
+        @classmethod
+        def apply(cls, dof, handles):
+            # the forward runs with gradients off: whether they are recorded is known here
+            return super().apply(dof, handles, torch.is_grad_enabled())
 
         @staticmethod
-        def forward(fctx, dof, handles):
+        def forward(fctx, dof, handles, recorded):
             ctx, grids, ligs, lp, bp = handles
-            r = score_grad(ctx, grids, ligs, lp, bp, dof.detach(), grad=fctx.needs_input_grad[0])
+            r = score_grad(ctx, grids, ligs, lp, bp, dof.detach(), grad=recorded and fctx.needs_input_grad[0])
             # dof too: a change of it in place before the backward stays an error
             fctx.save_for_backward(dof, r.get("grad_dof"))
             fctx.handles = (ctx, ligs, lp)
@@ -452,10 +458,11 @@ def _autograd_classes():
         def backward(fctx, g):
             grad = fctx.saved_tensors[1]
             ctx, ligs, lp = fctx.handles
-            return _scale_grad(ctx, ligs, lp, grad, False, g), None
+            return _scale_grad(ctx, ligs, lp, grad, False, g), None, None
 
     class ScoreGradXYZ(torch.autograd.Function):
-        """E(xyz) with dE/dxyz from the same kernel."""
+        """E(xyz) with dE/dxyz from the same kernel, kept ([B, atoms, 3]) for the
+        backward to scale."""
 
         @staticmethod
         def forward(fctx, xyz, handles):
