@@ -331,8 +331,11 @@ void pv_destroy(pv_ctx* c)
     if (SpareBlock* s = spare_of(c->device)) {
         std::lock_guard<std::mutex> lock(s->mu);
         if (--s->contexts == 0 && s->p) {
+            int current = -1;
+            const bool known = hipGetDevice(&current) == hipSuccess;
             (void)hipSetDevice(c->device);
             dfree(s->p);
+            if (known) (void)hipSetDevice(current);
             s->p = nullptr;
             s->n = 0;
         }
@@ -560,7 +563,7 @@ pv_status pv_grids_copy(const pv_grids* g, int32_t box, float* dst, void* stream
 void pv_grids_free(pv_grids* g)
 {
     if (!g) return;
-    (void)hipSetDevice(g->device);
+    (void)hipSetDevice(g->device);   // hipFree waits for the current device
     const bool idle = g->tables && dfree(g->tables);
     give_spare(g->device, g->maps, g->maps_bytes, idle);
     delete g;

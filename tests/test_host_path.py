@@ -73,6 +73,20 @@ def test_kept_map_block(fake):
     fake(kept_block)
 
 
+def current_device(f):
+    """Destroying a device's last context frees its kept block and leaves the thread's current device as it is."""
+    a, b = f.context(0), f.context(1)
+    f.grids(b).close()
+    f.lib.pv_trim(a.h)
+    assert f.rt.fake_current_device() == 0 and f.rt.fake_used() > 0
+    f.lib.pv_destroy(b.h)
+    assert f.rt.fake_current_device() == 0 and f.rt.fake_used() == 0
+
+
+def test_current_device_after_a_context_ends(fake):
+    fake(current_device)
+
+
 # ---------------------------------------------------------------- captures
 def free_during_capture(f):
     """Freeing grids while a stream captures makes no call that waits for the device, keeps no block that the device
