@@ -18,6 +18,8 @@
 // Every workgroup is one wave of 64 lanes; all arithmetic is binary32.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "pv_internal.h"
@@ -3062,28 +3064,33 @@ hipError_t launch_local_opt(const OptArgs& a, int n_cu, hipStream_t s)
 
 // Waves per job: the fewest rounds of refinements, times the rounds of workgroups
 // that the CUs take to get through the jobs (a CU holds eight waves, two per SIMD,
-// or as many workgroups as its LDS), each workgroup's serial parts counted as 0.3
-// of a round of refinements; of equals the most waves.  Few jobs so get all eight
-// waves for the latency, and many jobs as many as keep every wave at work: jobs of
-// 64-atom ligands x 32 chains, one / two / four / eight waves each:
+// or as many workgroups as its LDS; a started round counts as three quarters of a
+// whole one at least, since the jobs' lengths differ), each workgroup's serial
+// parts counted as 0.3 of a round of refinements; of those within 3% the most
+// waves.  Few jobs so get all eight waves for the latency, and many jobs as many as
+// keep every wave at work: jobs of 64-atom ligands x 32 chains of random poses,
+// one / two / four / eight waves each:
 //     120 x 20 modes 10.8 / 5.8 / 3.0 / 2.2 ms      1,000 x 20 modes 22.2 / 12.7 / 12.0 / 8.4 ms
 //     1,500 x 5 modes 3.5 / 3.8 / 6.6 / 4.2 ms      6,000 x 3 modes 7.9 / 9.4 / 8.1 / 14.6 ms
-// Four for every job count above the CUs, as before, took up to 1.9 times as long
-// as one wave (1,500 and 6,000 jobs x 5 modes); by this rule no set of 8 to
-// 128 atoms x 120 to 6,000 jobs x 3 to 20 modes takes above 3% longer than with
-// one wave, and all of them on average 1 to 4% longer than with their best number.
+// Four for every job count above the CUs took up to 1.9 times as long as one wave;
+// by this rule no set of 8 to 128 atoms x 120 to 6,000 jobs x 3 to 20 modes, on
+// random and on docked poses, takes above 3% longer than with one wave, and all of
+// them on average 2% longer than with their best number.
 static int output_waves(const OutputArgs& a, int n_cu, int lds_per_block)
 {
-    int best = 1;
-    int64_t least = INT64_MAX;
+    double cost[kOutWaves + 1], least = 0.0;
+    int top = 0;
     for (int w = 1; w <= kOutWaves; ++w) {
         const int lds = output_lds_bytes(a.l, a.chains, a.modes, w);
         if (w > 1 && lds > lds_per_block) break;
-        const int64_t held = (int64_t)std::max(1, std::min(kOutWaves / w, lds_per_block / lds)) * (n_cu > 0 ? n_cu : 1);
-        const int64_t cost = (a.n_jobs + held - 1) / held * (10 * ((std::min(a.modes, a.chains) + w - 1) / w) + 3);
-        if (cost <= least) { least = cost; best = w; }
+        const int held = std::max(1, std::min(kOutWaves / w, lds_per_block / lds)) * std::max(n_cu, 1);
+        const double rounds = (double)a.n_jobs / held;
+        cost[w] = (0.75 * std::ceil(rounds) + 0.25 * std::max(1.0, rounds)) * ((std::min(a.modes, a.chains) + w - 1) / w + 0.3);
+        if (w == 1 || cost[w] < least) least = cost[w];
+        top = w;
     }
-    return best;
+    while (cost[top] > 1.03 * least) --top;
+    return top;
 }
 
 hipError_t launch_output(const OutputArgs& a, int n_cu, int lds_per_block, hipStream_t s)

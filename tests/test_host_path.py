@@ -160,7 +160,7 @@ def output_waves(f):
     grids = f.grids(ctx)
     p = 1 << 20
     for atoms, tors, jobs, modes, want in ((64, 20, 120, 20, 7), (64, 20, 1500, 5, 1), (64, 20, 6000, 3, 1), (64, 20, 1000, 20, 7),
-                                           (20, 4, 5, 3, 8), (20, 4, 1000, 20, 2), (20, 4, 2000, 9, 1), (100, 20, 2000, 3, 3),
+                                           (20, 4, 5, 3, 8), (20, 4, 1000, 20, 4), (20, 4, 2000, 9, 1), (100, 20, 2000, 3, 3),
                                            (100, 20, 120, 20, 5)):
         ligs = pv.Ligands(ctx, [S.tree_ligand(np.random.default_rng(atoms * 31 + tors), atoms, tors)])
         plan = pv.Plan(ctx, grids, ligs, [(0, 0)] * jobs, pv.dock_params(chains=32))
