@@ -319,9 +319,10 @@ typedef struct {
 typedef struct pv_plan pv_plan;
 pv_status pv_dock_plan(pv_ctx* ctx, const pv_grids* grids, const pv_ligands* ligs, const pv_job* jobs,
                        int32_t n_jobs, const pv_dock_params* params, pv_plan** out);
-/* Batched form: every (job, chain) of the plan in one persistent launch
+/* Batched form: every (job, chain) of a size class in one persistent launch
  * whose waves pull work from a device queue (plus a reset and a per-job
- * reduction).  Captured in a hipGraph when the plan's flags ask for it. */
+ * reduction); two classes' launches run side by side, the second on a stream of
+ * the plan, forked from and joined to `stream`.  Captured in a hipGraph when the plan's flags ask for it. */
 pv_status pv_dock_run(pv_plan* plan, const pv_dock_out* out, void* stream);
 /* Plain form: one launch per job, in job order, on `stream`
  * (the per-ligand loop of Supplementary Algorithm 2). */
@@ -333,9 +334,10 @@ void pv_plan_free(pv_plan* plan);
  * and each class runs one persistent launch of pv_dock_run.  Its schedule:
  * the kernel variant (PV_VARIANT_*, below), the launch width in
  * workgroups (one wave each; where the width covers every chain and no other
- * class runs beside it, a chain's workgroup may have helper waves) and, reported only,
- * the dynamic LDS bytes per workgroup, the workgroups one CU holds and the
- * class's job count.  A launch of the gather variant wider than eight
+ * class runs beside it, a chain's workgroup may have helper waves, as long as
+ * they leave room for the equal launches, up to four, that fit the GPU without)
+ * and, reported only, the dynamic LDS bytes per workgroup, the workgroups one CU
+ * holds and the class's job count.  A launch of the gather variant wider than eight
  * workgroups per CU may take less LDS than reported.  The plan starts from
  * the occupancy model of pv_launch_info; pv_dock_run_plain always uses that
  * model for its per-job launches. */
@@ -397,7 +399,8 @@ pv_status pv_dock(pv_ctx* ctx, const pv_grids* grids, const pv_ligands* ligs, co
  * hipMalloc).  Same arguments, checks and outputs as pv_dock (host jobs,
  * device outputs), and the same outputs bit for bit: the jobs are split
  * into the same size classes, each run by one persistent launch with the
- * variant and width pv_dock_plan would choose.  It calls no hipMalloc,
+ * variant and width pv_dock_plan would choose, one class after the other (a
+ * plan runs them side by side and so takes less time for the same jobs).  It calls no hipMalloc,
  * hipFree or other allocating routine: the job table, the per-class job
  * maps, the queue counters and, when chain_best_e or chain_evals is NULL,
  * those per-chain arrays live in one file-scope device array per GPU

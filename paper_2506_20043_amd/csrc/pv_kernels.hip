@@ -15,7 +15,10 @@
 //    persistent launch whose waves pull (job, chain) items from a device
 //    queue, with Philox4x64-10 draws.
 //
-// Every workgroup is one wave of 64 lanes; all arithmetic is binary32.
+// A chain, a pose and a minimisation are one wave of 64 lanes (a chain may have
+// helper waves); the output stage, the maps and the surface points use workgroups
+// of several.  Arithmetic is binary32, but for the maps' cutoff where binary32
+// rounding could decide it (within_cutoff_f64).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -752,18 +755,6 @@ __device__ __forceinline__ void frames(const Topo<A, SL>& T, float pose, bool y_
     }
 }
 
-// Intra pairs, lanes over pairs, kPairUnroll pairs per lane and pass: every
-// load of a pass (pair records, then both positions) is issued before any of
-// its arithmetic, so the LDS latency is paid once per pass.  Per pair, with d
-// the surface distance and inside 8 A: the gauss, repulsion, hydrophobic and
-// hydrogen-bond terms of the Vina form and the force coefficient
-// c = (dphi/dr) / r.  Pairs are grouped by interaction class, so a whole
-// 64-pair chunk usually has no hydrophobic or hydrogen-bond weight and skips
-// those terms on a wave-uniform branch.  With the tables in LDS each pair
-// writes +f / -f into its slots of the two atoms' rows (the padded records
-// make every pass full, with no per-lane guard); otherwise it stores c for
-// the table gather.  No atomics either way.  Returns this lane's energy; adds
-// this lane's pairs inside the cutoff to cnt.
 typedef float f3v __attribute__((ext_vector_type(3)));
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -927,10 +918,6 @@ __device__ __forceinline__ float pair_loop(const Topo<A, SL>& T, const Lds& S, i
     return e;
 }
 
-// dE/dx_i of the intra term.  LDS tables: the sum of atom i's row of pair
-// forces (independent reads, rows padded to a multiple of four with zeros).
-// Global tables: sum over the pairs holding atom i of c_p (x_i - x_j); an
-// entry holds p's byte offset in S.cp in its low half and j's in S.pos in its high half.
 // The chunks [k, end) of 64 pairs; their energies go to part where it is given.
 template <int A, bool SL>
 __device__ __forceinline__ void pair_chunks(const Topo<A, SL>& T, const Lds& S, int k, int end, float& e, int& cnt,
@@ -954,6 +941,10 @@ __device__ __forceinline__ void pair_chunks(const Topo<A, SL>& T, const Lds& S, 
 constexpr int kGatherChunk = 8;
 static_assert(4 * kGatherChunk <= kEllPad, "the padding covers a chunk");
 
+// dE/dx_i of the intra term.  LDS tables: the sum of atom i's row of pair
+// forces (independent reads, rows padded to a multiple of four with zeros).
+// Global tables: sum over the pairs holding atom i of c_p (x_i - x_j); an
+// entry holds p's byte offset in S.cp in its low half and j's in S.pos in its high half.
 template <int A, bool SL>
 __device__ __forceinline__ void gather_pair_forces(const Topo<A, SL>& T, const Lds& S, int i, float4 xi, float& gx,
                                                    float& gy, float& gz)
@@ -2292,7 +2283,7 @@ struct MapSums {
 // O and S.
 // From d = 2.25 A on (kGridFar) a term is its second gaussian alone, bit for
 // bit: the first one's share, 0.0356 exp(-4 d^2), is below a quarter of a unit
-// in the last place of 0.00516 exp(-(d-3)^2/4) there (4 d^2 - (d-3)^2/4 > 19.3),
+// in the last place of 0.00516 exp(-(d-3)^2/4) there (4 d^2 - (d-3)^2/4 > 20.1),
 // and the other terms are zero.
 constexpr float kGridFar = 2.25f;
 
