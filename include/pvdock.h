@@ -322,7 +322,9 @@ pv_status pv_dock_plan(pv_ctx* ctx, const pv_grids* grids, const pv_ligands* lig
 /* Batched form: every (job, chain) of a size class in one persistent launch
  * whose waves pull work from a device queue (plus a reset and a per-job
  * reduction); two classes' launches run side by side, the second on a stream of
- * the plan, forked from and joined to `stream`.  Captured in a hipGraph when the plan's flags ask for it. */
+ * the plan, forked from and joined to `stream`, where they fill the GPU or
+ * `stream` is NULL (other streams may belong to callers who run several plans at
+ * once: smaller launches then run one after the other).  Captured in a hipGraph when the plan's flags ask for it. */
 pv_status pv_dock_run(pv_plan* plan, const pv_dock_out* out, void* stream);
 /* Plain form: one launch per job, in job order, on `stream`
  * (the per-ligand loop of Supplementary Algorithm 2). */
@@ -367,7 +369,7 @@ pv_status pv_plan_set_schedule(pv_plan* plan, int32_t group, int32_t variant, in
  * chain, outputs to the plan's own scratch, no timestamps) over the class's
  * first jobs in the order the launch hands them out (enough chains to fill
  * the widest candidate 8 times, or the whole class when it has fewer), the
- * plan's other class, if any, beside it as in pv_dock_run (with its schedule
+ * plan's other class, if any, beside or after it as in pv_dock_run (with its schedule
  * so far, on the same share of its jobs, bounded likewise).  It keeps the best
  * of `repeats` >= 1 timings (HIP events on `stream`) and sets the candidate
  * with the most evaluations per second, both classes' counted; on a tie the
@@ -400,7 +402,7 @@ pv_status pv_dock(pv_ctx* ctx, const pv_grids* grids, const pv_ligands* ligs, co
  * device outputs), and the same outputs bit for bit: the jobs are split
  * into the same size classes, each run by one persistent launch with the
  * variant and width pv_dock_plan would choose, one class after the other (a
- * plan runs them side by side and so takes less time for the same jobs).  It calls no hipMalloc,
+ * plan may run them side by side and so take less time for the same jobs).  It calls no hipMalloc,
  * hipFree or other allocating routine: the job table, the per-class job
  * maps, the queue counters and, when chain_best_e or chain_evals is NULL,
  * those per-chain arrays live in one file-scope device array per GPU

@@ -1032,20 +1032,32 @@ static pv_status check_out(const pv_plan* P, const pv_dock_out* o)
 // one class after the other leaves most of the chip idle while the first
 // one's last chains end.  The larger ligands' launch goes first, on s.
 // 1,024 jobs of a screen (736 small), 16 chains x 300 steps: 402 -> 361 ms.
-static hipError_t launch_classes(const pv_plan* P, const DockArgs* a, const LaunchShape* sh, const int32_t* wg, hipStream_t s)
+// The second stream takes one of the process's few hardware queues, and where the
+// caller docks on several streams their launches then wait for one another: three
+// streams of 2 x 40 chains 25.8 -> 32.9 ms, of 2 x 500 chains 31.0 -> 38.3 (one
+// stream 25.3 -> 12.5, 29.5 -> 17.0).  Launches that fill three quarters of the GPU
+// lose nothing by it (three streams of 2 x 800 chains 25.8 -> 25.7 ms; of 2 x 650,
+// just below, 24.1 -> 26.0); smaller ones run side by side on the null stream, which callers of one
+// stream use, and one after the other on others.  caller: the stream of the call
+// (s is another one while a graph is captured).
+static hipError_t launch_classes(const pv_plan* P, const DockArgs* a, const LaunchShape* sh, const int32_t* wg, hipStream_t s,
+                                 hipStream_t caller)
 {
     const bool two = P->groups.size() == 2;
+    double fill = 0.0;
+    for (size_t k = 0; k < P->groups.size(); ++k) fill += (double)wg[k] / ((double)sh[k].per_cu * P->ctx->n_cu);
+    const bool beside = two && (!caller || fill >= 0.75);
     hipError_t e = launch_reset_queue(P->queue, s);
-    if (e == hipSuccess && two) e = hipEventRecord(P->fork, s);
-    if (e == hipSuccess && two) e = hipStreamWaitEvent(P->side_stream, P->fork, 0);
+    if (e == hipSuccess && beside) e = hipEventRecord(P->fork, s);
+    if (e == hipSuccess && beside) e = hipStreamWaitEvent(P->side_stream, P->fork, 0);
     if (e != hipSuccess) return e;
     for (size_t k = P->groups.size(); k-- > 0;) {
-        const hipError_t el = launch_dock(a[k], sh[k], wg[k], !two, P->ctx->n_cu, two && k == 0 ? P->side_stream : s);
+        const hipError_t el = launch_dock(a[k], sh[k], wg[k], !two, P->ctx->n_cu, beside && k == 0 ? P->side_stream : s);
         if (e == hipSuccess) e = el;
     }
     // joined also where a launch failed, so that nothing is left running
     // beside s (nor a capture left forked)
-    if (two) {
+    if (beside) {
         hipError_t ej = hipEventRecord(P->join, P->side_stream);
         if (ej == hipSuccess) ej = hipStreamWaitEvent(s, P->join, 0);
         if (e == hipSuccess) e = ej;
@@ -1053,7 +1065,7 @@ static hipError_t launch_classes(const pv_plan* P, const DockArgs* a, const Laun
     return e;
 }
 
-static hipError_t enqueue_batched(pv_plan* P, const pv_dock_out* o, hipStream_t s)
+static hipError_t enqueue_batched(pv_plan* P, const pv_dock_out* o, hipStream_t s, hipStream_t caller)
 {
     float* cbe = o->chain_best_e ? o->chain_best_e : P->scratch_best;
     int64_t* cev = o->chain_evals ? o->chain_evals : P->scratch_evals;
@@ -1072,7 +1084,7 @@ static hipError_t enqueue_batched(pv_plan* P, const pv_dock_out* o, hipStream_t 
         sh[k] = G.shape;
         wg[k] = G.workgroups;
     }
-    e = launch_classes(P, a, sh, wg, s);
+    e = launch_classes(P, a, sh, wg, s, caller);
     if (e != hipSuccess) return e;
     if (o->job_best_e || o->job_best_chain || o->job_evals || o->job_status)
         e = launch_job_reduce(cbe, cev, cst, P->n_jobs, P->sp.chains, o->job_best_e, o->job_best_chain, o->job_evals,
@@ -1088,7 +1100,7 @@ pv_status pv_dock_run(pv_plan* P, const pv_dock_out* o, void* stream)
     if ((st = set_device(P->ctx)) != PV_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     if (!(P->sp.flags & PV_DOCK_GRAPH)) {
-        hipError_t e = enqueue_batched(P, o, s);
+        hipError_t e = enqueue_batched(P, o, s, s);
         if (e != hipSuccess) return hip_fail(e, "dock launch");
         return PV_OK;
     }
@@ -1099,7 +1111,7 @@ pv_status pv_dock_run(pv_plan* P, const pv_dock_out* o, void* stream)
             P->have_graph = false;
         }
         HIP_TRY(hipStreamBeginCapture(P->cap_stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-        hipError_t e = enqueue_batched(P, o, P->cap_stream);
+        hipError_t e = enqueue_batched(P, o, P->cap_stream, s);
         hipGraph_t g = nullptr;
         hipError_t e2 = hipStreamEndCapture(P->cap_stream, &g);
         if (e != hipSuccess) { if (g) (void)hipGraphDestroy(g); return hip_fail(e, "dock launch (capture)"); }
@@ -1347,7 +1359,7 @@ pv_status pv_dock_autotune(pv_plan* P, int32_t tune_steps, int32_t repeats, void
             float best_ms = 0.f;
             for (int r = 0; r < repeats; ++r) {
                 e = hipEventRecord(t0, s);
-                if (e == hipSuccess) e = launch_classes(P, a, sh, wg, s);
+                if (e == hipSuccess) e = launch_classes(P, a, sh, wg, s, s);
                 if (e == hipSuccess) e = hipEventRecord(t1, s);
                 if (e == hipSuccess) e = hipEventSynchronize(t1);
                 float ms = 0.f;

@@ -223,6 +223,32 @@ def test_teams_leave_room_for_other_streams(fake):
     fake(team_sizes)
 
 
+# ---------------------------------------------------------------- size classes
+def classes_on_streams(f):
+    """Two size classes run side by side on the null stream and where they fill the GPU; smaller launches on a stream of
+    the caller's run one after the other on it (its hardware queue is not the only one that others may wait for)."""
+    import numpy as np
+    from paper_2506_20043_amd import synth as S
+    pv, ctx, g = f.pv, f.context(), np.random.default_rng(3)
+    grids = f.grids(ctx)
+    ligs = pv.Ligands(ctx, [S.tree_ligand(g, 30, 5), S.tree_ligand(g, 90, 8)])
+    o = pv.DockOut()
+    for flags in (0, pv.PV_DOCK_GRAPH):
+        for jobs, stream, beside in ((3, None, True), (3, 0x77770, False), (200, None, True), (200, 0x77770, True)):
+            plan = pv.Plan(ctx, grids, ligs, [(0, 0), (1, 0)] * jobs, pv.dock_params(chains=16, flags=flags))
+            f.launches()
+            assert f.lib.pv_dock_run(plan.h, C.byref(o), stream) == 0, f.lib.pv_last_error()
+            streams = [k[4] for k in f.launches("dock_kernel")]
+            assert len(streams) == 2 and (streams[0] != streams[1]) == beside, (flags, jobs, stream, streams)
+            if not flags:
+                assert streams[0] == (stream or 0)
+            plan.close()
+
+
+def test_size_classes_beside_other_streams(fake):
+    fake(classes_on_streams)
+
+
 # ---------------------------------------------------------------- autotuner
 def _tune(f, plan, repeats=1):
     """(group, variant, workgroups, cached) of every candidate, and the dock launches."""
