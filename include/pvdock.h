@@ -336,8 +336,9 @@ void pv_plan_free(pv_plan* plan);
  * and each class runs one persistent launch of pv_dock_run.  Its schedule:
  * the kernel variant (PV_VARIANT_*, below), the launch width in
  * workgroups (one wave each; where the width covers every chain and no other
- * class runs beside it, a chain's workgroup may have helper waves, as long as
- * they leave room for the equal launches, up to four, that fit the GPU without)
+ * class runs beside it, a chain's workgroup may have helper waves; on a stream
+ * other than NULL they leave room for the equal launches, up to four, that fit
+ * the GPU without helpers)
  * and, reported only, the dynamic LDS bytes per workgroup, the workgroups one CU
  * holds and the class's job count.  A launch of the gather variant wider than eight
  * workgroups per CU may take less LDS than reported.  The plan starts from
@@ -352,9 +353,9 @@ typedef struct {
 } pv_schedule;
 pv_status pv_plan_groups(const pv_plan* plan, int32_t* n_groups);
 pv_status pv_plan_schedule(const pv_plan* plan, int32_t group, pv_schedule* out);
-/* Waves per workgroup of a class's launch under its schedule: 1, or 2 or 4
- * where its chains have helper waves. */
-pv_status pv_plan_waves(const pv_plan* plan, int32_t group, int32_t* waves);
+/* Waves per workgroup of a class's launch on `stream` under its schedule: 1, or
+ * 2 or 4 where its chains have helper waves. */
+pv_status pv_plan_waves(const pv_plan* plan, int32_t group, void* stream, int32_t* waves);
 /* Sets a class's variant and width.  PV_VARIANT_SLOTS and PV_VARIANT_GATHER
  * need ligands of at most 64 atoms; PV_VARIANT_GATHER2 takes any.  A
  * workgroup of the variant must fit a CU (PV_E_RANGE otherwise); workgroups
@@ -375,7 +376,8 @@ pv_status pv_plan_set_schedule(pv_plan* plan, int32_t group, int32_t variant, in
  * with the most evaluations per second, both classes' counted; on a tie the
  * earlier candidate (the model's schedule comes first) wins.  The choice is remembered by the
  * context, keyed by the class's ligand limits and work items, those of the
- * plan's other class, tune_steps and search settings, and a later call on a plan of the same key takes it
+ * plan's other class, tune_steps, search settings and whether `stream` is NULL,
+ * and a later call on a plan of the same key takes it
  * without timing (reported with cached = 1); it keeps the latest 256 such
  * choices.  results: host, up to
  * max_results entries (may be NULL); n_results: how many were written (may

@@ -114,7 +114,7 @@ SIGNATURES = {
     "pv_plan_free": (None, [_vp]),
     "pv_plan_groups": (C.c_int, [_vp, _ip]),
     "pv_plan_schedule": (C.c_int, [_vp, _i32, C.POINTER(Schedule)]),
-    "pv_plan_waves": (C.c_int, [_vp, _i32, _ip]),
+    "pv_plan_waves": (C.c_int, [_vp, _i32, _vp, _ip]),
     "pv_plan_set_schedule": (C.c_int, [_vp, _i32, _i32, _i32]),
     "pv_dock_autotune": (C.c_int, [_vp, _i32, _i32, _vp, C.POINTER(TuneResult), _i32, _ip]),
     "pv_dock": (C.c_int, [_vp, _vp, _vp, C.POINTER(Job), _i32, C.POINTER(DockParams), C.POINTER(DockOut), _vp]),
@@ -559,10 +559,11 @@ class Plan:
         _check(lib().pv_plan_schedule(self.h, group, C.byref(sc)), "pv_plan_schedule")
         return {k: getattr(sc, k) for k, _ in Schedule._fields_}
 
-    def waves(self, group: int = 0) -> int:
-        """Waves per workgroup of a size class's launch (above 1: helper waves)."""
+    def waves(self, group: int = 0, stream=None) -> int:
+        """Waves per workgroup of a size class's launch on a stream (above 1: helper waves)."""
         n = C.c_int32()
-        _check(lib().pv_plan_waves(self.h, group, C.byref(n)), "pv_plan_waves")
+        on = _stream() if stream is None else C.c_void_p(stream.cuda_stream)
+        _check(lib().pv_plan_waves(self.h, group, on, C.byref(n)), "pv_plan_waves")
         return n.value
 
     def set_schedule(self, group: int, variant: int, workgroups: int = 0):

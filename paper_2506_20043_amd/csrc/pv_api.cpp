@@ -151,8 +151,8 @@ struct TuneClass {
     }
 };
 struct TuneEntry {
-    TuneClass cls, beside;   // the class, and the one whose launch runs beside it (all 0: none, so that
-                             // its chains may have helper waves)
+    TuneClass cls, beside;   // the class, and the one whose launch runs beside it (all 0: none)
+    int32_t side;            // what decides about helper waves (see launch_dock) and the classes' launches
     int32_t steps, max_iter, refine_max_iter, m, ls_max, consistency;
     int32_t variant, workgroups;
 };
@@ -1052,7 +1052,7 @@ static hipError_t launch_classes(const pv_plan* P, const DockArgs* a, const Laun
     if (e == hipSuccess && beside) e = hipStreamWaitEvent(P->side_stream, P->fork, 0);
     if (e != hipSuccess) return e;
     for (size_t k = P->groups.size(); k-- > 0;) {
-        const hipError_t el = launch_dock(a[k], sh[k], wg[k], !two, P->ctx->n_cu, beside && k == 0 ? P->side_stream : s);
+        const hipError_t el = launch_dock(a[k], sh[k], wg[k], two ? 0 : side_of(caller), P->ctx->n_cu, beside && k == 0 ? P->side_stream : s);
         if (e == hipSuccess) e = el;
     }
     // joined also where a launch failed, so that nothing is left running
@@ -1146,7 +1146,7 @@ pv_status pv_dock_run_plain(pv_plan* P, const pv_dock_out* o, void* stream)
         a.job_begin = j;
         a.n_items = P->sp.chains;
         a.persistent = 0;
-        HIP_TRY(launch_dock(a, G.plain_shape, 0, true, P->ctx->n_cu, s), "dock launch");
+        HIP_TRY(launch_dock(a, G.plain_shape, 0, side_of(s), P->ctx->n_cu, s), "dock launch");
     }
     if (o->job_best_e || o->job_best_chain || o->job_evals || o->job_status)
         HIP_TRY(launch_job_reduce(cbe, cev, cst, P->n_jobs, P->sp.chains, o->job_best_e, o->job_best_chain,
@@ -1202,15 +1202,15 @@ pv_status pv_plan_schedule(const pv_plan* P, int32_t group, pv_schedule* out)
     return PV_OK;
 }
 
-pv_status pv_plan_waves(const pv_plan* P, int32_t group, int32_t* waves)
+pv_status pv_plan_waves(const pv_plan* P, int32_t group, void* stream, int32_t* waves)
 {
     if (!P || !waves) return fail(PV_E_INVALID, "plan or output is NULL");
     if (group < 0 || group >= (int32_t)P->groups.size()) return fail(PV_E_RANGE, "no such size class");
     pv_status st = set_device(P->ctx);
     if (st != PV_OK) return st;
     const DockGroup& G = P->groups[group];
-    *waves = dock_waves(G.lv, P->sp.m, (int64_t)G.n_jobs * P->sp.chains, G.shape, G.workgroups, P->groups.size() == 1,
-                        P->ctx->n_cu);
+    *waves = dock_waves(G.lv, P->sp.m, (int64_t)G.n_jobs * P->sp.chains, G.shape, G.workgroups,
+                        P->groups.size() == 2 ? 0 : side_of((hipStream_t)stream), P->ctx->n_cu);
     return PV_OK;
 }
 
@@ -1248,7 +1248,7 @@ pv_status pv_plan_set_schedule(pv_plan* P, int32_t group, int32_t variant, int32
 
 static bool same_key(const TuneEntry& a, const TuneEntry& b)
 {
-    return a.cls == b.cls && a.beside == b.beside && a.steps == b.steps && a.max_iter == b.max_iter &&
+    return a.cls == b.cls && a.beside == b.beside && a.side == b.side && a.steps == b.steps && a.max_iter == b.max_iter &&
            a.refine_max_iter == b.refine_max_iter && a.m == b.m && a.ls_max == b.ls_max &&
            a.consistency == b.consistency;
 }
@@ -1291,7 +1291,7 @@ pv_status pv_dock_autotune(pv_plan* P, int32_t tune_steps, int32_t repeats, void
         auto tune_class = [&](const DockGroup& c) {
             return TuneClass{c.lv.max_atoms, c.lv.max_pairs, c.lv.max_ell, c.lv.max_tors, (int64_t)c.n_jobs * chains};
         };
-        TuneEntry key = {tune_class(G), P->groups.size() == 2 ? tune_class(P->groups[1 - g]) : TuneClass{}, tune_steps,
+        TuneEntry key = {tune_class(G), P->groups.size() == 2 ? tune_class(P->groups[1 - g]) : TuneClass{}, side_of(s), tune_steps,
                          P->sp.max_iter, P->sp.refine_max_iter, P->sp.m, P->sp.ls_max, P->sp.consistency, 0, 0};
         bool cached = false;
         {
@@ -1507,7 +1507,7 @@ pv_status pv_dock_noalloc(pv_ctx* ctx, const pv_grids* grids, const pv_ligands* 
         a.job_t_start = out->job_t_start;
         a.job_t_end = out->job_t_end;
         a.dof_stride = out->dof_stride;
-        HIP_TRY(launch_dock(a, sh[g], width[g], true, ctx->n_cu, s), "dock launch");
+        HIP_TRY(launch_dock(a, sh[g], width[g], side_of(s), ctx->n_cu, s), "dock launch");
     }
     if (out->job_best_e || out->job_best_chain || out->job_evals || out->job_status)
         HIP_TRY(launch_job_reduce(cbe, cev, cst, n_jobs, params->chains, out->job_best_e, out->job_best_chain,

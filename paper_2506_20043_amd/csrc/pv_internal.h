@@ -229,10 +229,15 @@ hipError_t launch_score(const ScoreArgs& a, bool ragged, int n_cu, hipStream_t s
 // out = grad with each row's own values times its pose's scale; n = poses x row
 hipError_t launch_scale_grad(const LigDev& l, int64_t n, int row, const int32_t* lig_of_pose, bool of_xyz,
                              const float* grad, const float* scale, float* out, hipStream_t s);
-// alone: no other dock launch runs beside it
-hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgroups, bool alone, int n_cu, hipStream_t s);
+// side: the equal launches, itself included, that its helper waves must leave room
+// for (0: another class's launch runs beside it, no helpers): itself on the null
+// stream, which callers of one stream use, as many as a process has hardware queues
+// on another stream
+constexpr int kSideBySide = 4;
+inline int side_of(hipStream_t caller) { return caller ? kSideBySide : 1; }
+hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgroups, int side, int n_cu, hipStream_t s);
 // waves per workgroup of a persistent launch_dock of these (m: the history pairs)
-int dock_waves(const LigDev& l, int m, int64_t items, const LaunchShape& sh, int32_t workgroups, bool alone, int n_cu);
+int dock_waves(const LigDev& l, int m, int64_t items, const LaunchShape& sh, int32_t workgroups, int side, int n_cu);
 hipError_t launch_reset_queue(uint32_t* q, hipStream_t s);
 hipError_t launch_fma_peak(float* out, int n, int iters, hipStream_t s);
 hipError_t launch_job_reduce(const float* chain_best_e, const int64_t* chain_evals, const int32_t* chain_status,

@@ -2929,19 +2929,18 @@ hipError_t launch_score(const ScoreArgs& a, bool ragged, int n_cu, hipStream_t s
 
 // Whether a launch's chains can have teams of W waves: all of them resident at
 // once, and beside them as many equal launches of other streams as without teams,
-// up to the four that a process's hardware queues run side by side.  Launches that
+// up to `side`, the four that a process's hardware queues run side by side (on the
+// null stream, which callers of one stream use, itself alone).  Launches that
 // no longer fit together run one after the other (chains of 60 steps, teams where
 // one launch fits / one wave each / this rule):
 //     20 atoms, 320 chains, three streams 16.0 / 12.4 / 10.9 ms; 500, two 15.7 / 12.2 / 10.9
 //     20 atoms, 750 chains, two streams 19.7 / 12.8 / 10.6 ms; 35 atoms, 240, four 14.4 / - / 10.5
-// One launch alone pays where the smaller team is slower: 35 atoms, 320 chains 8.9
-// / 11.8 / 9.7 ms.
-constexpr int kSideBySide = 4;
-
+// One launch alone on such a stream pays where the smaller team is slower: 35 atoms,
+// 320 chains 8.9 / 11.8 / 9.7 ms.
 template <int MM, int W>
-static bool team_fits(const LigDev& l, int64_t items, const LaunchShape& sh, int n_cu)
+static bool team_fits(const LigDev& l, int64_t items, const LaunchShape& sh, int side, int n_cu)
 {
-    items *= std::min<int64_t>(kSideBySide, std::max<int64_t>(1, (int64_t)sh.per_cu * n_cu / items));
+    items *= std::min<int64_t>(side, std::max<int64_t>(1, (int64_t)sh.per_cu * n_cu / items));
     const int lds = sh.lds + team_bytes<W>(l.max_atoms, l.max_pairs);
     return (int64_t)occupancy(dock_kernel<1, true, MM, W>, lds, W * kWave) * n_cu >= items;
 }
@@ -2963,36 +2962,36 @@ static void launch_slots(const DockArgs& a, const LaunchShape& sh, unsigned grid
 //     64 atoms, 1,717 pairs   8 chains 7.88 / 6.14 / 4.66      256: 9.91 / 7.80 / 5.97
 //     35 atoms, 1,024 chains 9.87 / 8.50 (no room for teams of four)
 template <int MM>
-static int team_waves(const LigDev& l, int64_t items, const LaunchShape& sh, unsigned grid, bool alone, int n_cu)
+static int team_waves(const LigDev& l, int64_t items, const LaunchShape& sh, unsigned grid, int side, int n_cu)
 {
-    if (!alone || grid < items || l.max_pairs <= kWave) return 1;
-    return team_fits<MM, 4>(l, items, sh, n_cu) ? 4 : team_fits<MM, 2>(l, items, sh, n_cu) ? 2 : 1;
+    if (!side || grid < items || l.max_pairs <= kWave) return 1;
+    return team_fits<MM, 4>(l, items, sh, side, n_cu) ? 4 : team_fits<MM, 2>(l, items, sh, side, n_cu) ? 2 : 1;
 }
 
-int dock_waves(const LigDev& l, int m, int64_t items, const LaunchShape& sh, int32_t workgroups, bool alone, int n_cu)
+int dock_waves(const LigDev& l, int m, int64_t items, const LaunchShape& sh, int32_t workgroups, int side, int n_cu)
 {
     if (sh.variant != 0) return 1;
-    return m <= kShortM ? team_waves<kShortM>(l, items, sh, (unsigned)workgroups, alone, n_cu)
-                        : team_waves<kMaxM>(l, items, sh, (unsigned)workgroups, alone, n_cu);
+    return m <= kShortM ? team_waves<kShortM>(l, items, sh, (unsigned)workgroups, side, n_cu)
+                        : team_waves<kMaxM>(l, items, sh, (unsigned)workgroups, side, n_cu);
 }
 
 template <int MM>
-static void launch_slot_dock(const DockArgs& a, const LaunchShape& sh, unsigned grid, bool alone, int n_cu, hipStream_t s)
+static void launch_slot_dock(const DockArgs& a, const LaunchShape& sh, unsigned grid, int side, int n_cu, hipStream_t s)
 {
-    const int waves = team_waves<MM>(a.l, a.n_items, sh, grid, alone, n_cu);
+    const int waves = team_waves<MM>(a.l, a.n_items, sh, grid, side, n_cu);
     if (waves == 4) launch_slots<MM, 4>(a, sh, grid, s);
     else if (waves == 2) launch_slots<MM, 2>(a, sh, grid, s);
     else launch_slots<MM, 1>(a, sh, grid, s);
 }
 
-hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgroups, bool alone, int n_cu, hipStream_t s)
+hipError_t launch_dock(const DockArgs& a, const LaunchShape& sh, int32_t workgroups, int side, int n_cu, hipStream_t s)
 {
     if (a.n_items <= 0) return hipSuccess;
     const unsigned grid = a.persistent ? (unsigned)workgroups : (unsigned)a.n_items;
     const bool short_m = a.sp.m <= kShortM;
     if (sh.variant == 0) {
-        if (short_m) launch_slot_dock<kShortM>(a, sh, grid, alone, n_cu, s);
-        else launch_slot_dock<kMaxM>(a, sh, grid, alone, n_cu, s);
+        if (short_m) launch_slot_dock<kShortM>(a, sh, grid, side, n_cu, s);
+        else launch_slot_dock<kMaxM>(a, sh, grid, side, n_cu, s);
     } else if (sh.variant == 1 && sh.lean && grid > (int64_t)sh.full_cu * n_cu) {
         const int lds = lean_lds(kKindDock, a.l);
         if (short_m) hipLaunchKernelGGL((dock_kernel<1, false, kShortM, kLean>), dim3(grid), dim3(64), lds, s, a);

@@ -198,24 +198,31 @@ def test_surface_launches(fake):
 
 # ---------------------------------------------------------------- helper waves
 def team_sizes(f):
-    """Teams leave room for the equal launches of other streams that fit beside a launch of one wave per chain, up to
-    four (the hardware queues of a process)."""
+    """On a caller's stream teams leave room for the equal launches of other streams that fit beside a launch of one wave
+    per chain, up to four (the hardware queues of a process); on the null stream all its chains are resident."""
     import numpy as np
     from paper_2506_20043_amd import synth as S
     pv, ctx = f.pv, f.context()
     grids = f.grids(ctx)
+    o = pv.DockOut()
     for atoms, tors in ((20, 4), (35, 8), (60, 12)):
         ligs = pv.Ligands(ctx, [S.tree_ligand(np.random.default_rng(atoms), atoms, tors)])
-        seen = set()
-        for chains in (1, 8, 40, 160, 192, 193, 240, 320, 384, 385, 500, 750, 1280, 1500):
-            plan = pv.Plan(ctx, grids, ligs, [(0, 0)], pv.dock_params(chains=chains))
-            plan.set_schedule(0, pv.VARIANT_SLOTS, 0)
-            w, one = plan.waves(), plan.schedule()["per_cu"] * 256
-            # twelve waves per CU at these kernels' registers, less where the LDS holds fewer
-            assert 12 // w * 256 >= chains * min(4, one // chains) or w == 1, (atoms, chains, w)
-            seen.add(w)
-            plan.close()
-        assert seen >= ({4, 2} if atoms < 60 else {4}), (atoms, seen)
+        for stream, side in ((None, 1), (0x77770, 4)):
+            seen = set()
+            for chains in (1, 8, 40, 160, 192, 193, 240, 320, 384, 385, 500, 750, 1280, 1500):
+                plan = pv.Plan(ctx, grids, ligs, [(0, 0)], pv.dock_params(chains=chains))
+                plan.set_schedule(0, pv.VARIANT_SLOTS, 0)
+                n, one = C.c_int32(), plan.schedule()["per_cu"] * 256
+                assert f.lib.pv_plan_waves(plan.h, 0, stream, C.byref(n)) == 0
+                w = n.value
+                # twelve waves per CU at these kernels' registers, less where the LDS holds fewer
+                assert 12 // w * 256 >= chains * min(side, one // chains) or w == 1, (atoms, chains, w)
+                f.launches()
+                assert f.lib.pv_dock_run(plan.h, C.byref(o), stream) == 0
+                assert [k[2] for k in f.launches("dock_kernel")] == [(64, w, 1)]
+                seen.add(w)
+                plan.close()
+            assert seen >= ({4, 2} if atoms < 60 else {4}), (atoms, seen)
         ligs.close()
 
 
