@@ -204,6 +204,7 @@ struct GridBuildArgs {
     const float* geom;
     const int32_t* tile_off;  // [box+1] first tile of each box
     int32_t n_boxes;
+    int32_t first_tile;       // of the launch (set by launch_build_grids)
 };
 
 hipError_t launch_build_grids(const GridBuildArgs& a, int64_t n_tiles, hipStream_t s);

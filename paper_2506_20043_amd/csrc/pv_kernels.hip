@@ -2374,10 +2374,9 @@ __global__ __launch_bounds__(kGridThreads) void gridmap_kernel(GridBuildArgs a)
     // Workgroups go round robin to the 8 XCDs: each XCD takes runs of kGridRun
     // consecutive tiles, so that tiles that share map lines write them through
     // one L2.
-    const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x, q = block >> 3;
-    const uint32_t at = (q / kGridRun) * (8 * kGridRun) + (block & 7) * kGridRun + q % kGridRun;
-    if (at >= (uint32_t)a.tile_off[a.n_boxes]) return;
-    const int tile = (int)at;
+    const int q = blockIdx.x >> 3;
+    const int tile = a.first_tile + (q / kGridRun) * (8 * kGridRun) + (blockIdx.x & 7) * kGridRun + q % kGridRun;
+    if (tile >= a.tile_off[a.n_boxes]) return;
     // which box: the boxes whose first tile is at or before this one
     int box = -1;
     for (int b0 = 0; b0 < a.n_boxes; b0 += kWave)
@@ -2818,11 +2817,17 @@ hipError_t launch_build_grids(const GridBuildArgs& a, int64_t n_tiles, hipStream
 {
     if (n_tiles <= 0) return hipSuccess;
     const int64_t runs = 8 * kGridRun;   // whole runs for every XCD; workgroups past the last tile return
-    const int64_t grid = (n_tiles + runs - 1) / runs * runs;
-    // a launch may not have 2^32 threads in a dimension: rows of at most 2^20 workgroups (whole runs too)
-    const int64_t x = std::min<int64_t>(grid, (int64_t)1 << 20);
-    hipLaunchKernelGGL(gridmap_kernel, dim3((unsigned)x, (unsigned)((grid + x - 1) / x)), dim3(kGridThreads), 0, s, a);
-    return hipGetLastError();
+    // a launch may not have 2^32 threads in a dimension: at most 2^20 workgroups each (whole runs, 8.6 GB of maps)
+    constexpr int64_t kMost = (int64_t)1 << 20;
+    GridBuildArgs b = a;
+    for (int64_t first = 0; first < n_tiles; first += kMost) {
+        const int64_t grid = (std::min<int64_t>(n_tiles - first, kMost) + runs - 1) / runs * runs;
+        b.first_tile = (int32_t)first;
+        hipLaunchKernelGGL(gridmap_kernel, dim3((unsigned)grid), dim3(kGridThreads), 0, s, b);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <typename K>

@@ -129,8 +129,8 @@ def test_gradient_scaling_launches(fake):
 
 
 def grid_launches(f):
-    """Map builds of up to 2^24 tiles (137 GB of maps), and around a row of workgroups: every tile has a workgroup, in
-    whole runs of 32."""
+    """Map builds of up to 2^24 tiles (137 GB of maps), and around a launch's most: every tile has a workgroup, in
+    whole runs of 32, in launches of at most 2^20."""
     ctx = f.context()
 
     def box(nx, ny, nz):
@@ -141,8 +141,9 @@ def grid_launches(f):
                          ([big] * 257 + [(240, 80, 260)], (1 << 24) - 31)):
         g = f.grids(ctx, boxes=[box(*s) for s in sizes])
         assert not isinstance(g, int), (tiles, f.lib.pv_last_error())
-        (k,) = f.launches("gridmap")
-        assert k[1][0] % 32 == 0 and tiles <= k[1][0] * k[1][1] < tiles + k[1][0] and k[1][2] == 1
+        grids = [k[1] for k in f.launches("gridmap")]
+        assert all(x % 32 == 0 and x <= 1 << 20 and y == z == 1 for x, y, z in grids)
+        assert all(x == 1 << 20 for x, _, _ in grids[:-1]) and tiles <= sum(x for x, _, _ in grids) < tiles + 32
         g.close()
 
 
