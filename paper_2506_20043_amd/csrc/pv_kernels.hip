@@ -3060,11 +3060,11 @@ hipError_t launch_local_opt(const OptArgs& a, int n_cu, hipStream_t s)
 // Waves per job: the fewest rounds of refinements, times the rounds of workgroups
 // that the CUs take to get through the jobs (a CU holds eight waves, two per SIMD,
 // or as many workgroups as its LDS; a started round counts as three quarters of a
-// whole one at least, since the jobs' lengths differ), each workgroup's serial
-// parts counted as 0.3 of a round of refinements; of those within 3% the most
-// waves.  Few jobs so get all eight waves for the latency, and many jobs as many as
-// keep every wave at work: jobs of 64-atom ligands x 32 chains of random poses,
-// one / two / four / eight waves each:
+// whole one at least, since the jobs' lengths differ).  In rounds of refinements, a
+// workgroup's serial parts count as 0.6 and the clustering of a chain as 0.02, shared
+// by the waves; of numbers within 6% the most waves.  Few jobs so get all eight
+// waves for the latency, and many jobs as many as keep every wave at work: jobs of
+// 64-atom ligands x 32 chains of random poses, one / two / four / eight waves each:
 //     120 x 20 modes 10.8 / 5.8 / 3.0 / 2.2 ms      1,000 x 20 modes 22.2 / 12.7 / 12.0 / 8.4 ms
 //     1,500 x 5 modes 3.5 / 3.8 / 6.6 / 4.2 ms      6,000 x 3 modes 7.9 / 9.4 / 8.1 / 14.6 ms
 // Four for every job count above the CUs took up to 1.9 times as long as one wave;
@@ -3079,12 +3079,12 @@ static int output_waves(const OutputArgs& a, int n_cu, int lds_per_block)
         const int lds = output_lds_bytes(a.l, a.chains, a.modes, w);
         if (w > 1 && lds > lds_per_block) break;
         const int held = std::max(1, std::min(kOutWaves / w, lds_per_block / lds)) * std::max(n_cu, 1);
-        const double rounds = (double)a.n_jobs / held;
-        cost[w] = (0.75 * std::ceil(rounds) + 0.25 * std::max(1.0, rounds)) * ((std::min(a.modes, a.chains) + w - 1) / w + 0.3);
+        const double x = (double)a.n_jobs / held, rounds = x > 1.0 ? 0.75 * std::ceil(x) + 0.25 * x : 1.0 + 0.05 * x;
+        cost[w] = rounds * ((std::min(a.modes, a.chains) + w - 1) / w + 0.6 + 0.02 * a.chains / w);
         if (w == 1 || cost[w] < least) least = cost[w];
         top = w;
     }
-    while (cost[top] > 1.03 * least) --top;
+    while (cost[top] > 1.06 * least) --top;
     return top;
 }
 
